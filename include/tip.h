@@ -21,6 +21,11 @@
  *   S = D_e - H_eo D_o^-1 H_oe over the even sites (half the vector length,
  *   about half the iterations), then forms x_o = D_o^-1 (b_o + H_oe x_e).  The
  *   acceptance test is the same FP64 true residual of the full system.
+ *   Small scalar lattices in FP64 (2 to 4 dimensions, V <= 32768 with power-of-two
+ *   sides, V <= 20000 otherwise) are solved with one workgroup per right-hand
+ *   side, whole solves in one launch, unless the caller fixes rhs_block,
+ *   round_tiles or march_tc; stencil_launches then counts these launches and
+ *   matvecs the iterations of each launch's longest solve.
  *
  * Conventions shared by every entry point
  * ---------------------------------------

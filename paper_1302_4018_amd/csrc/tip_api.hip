@@ -27,6 +27,7 @@
 #include "../../include/tip.h"
 #include "tip_batch.h"
 #include "tip_launch.h"
+#include "tip_resident.h"
 
 using namespace tip;
 
@@ -107,6 +108,13 @@ tip_status make_geom(int32_t ndim, const int64_t* dims, int ncomp, Geom* g) {
   return TIP_OK;
 }
 
+// Every side a power of two >= 2: the torus is bipartite.
+bool bipartite(const Geom& g) {
+  bool bip = g.pow2 != 0;
+  for (int mu = 0; mu < g.ndim; ++mu) bip = bip && g.logn[mu] >= 1;
+  return bip;
+}
+
 // Device allocation, frees, stream creation and device-wide synchronisation
 // may synchronise the device, which must not happen while another thread
 // captures a HIP graph (trace_inv_probe_batch runs calls on several threads).
@@ -167,6 +175,9 @@ struct tip_op_s {
   // lower bound of the spectrum: A = sum_e w_e L_e + diag(m) with L_e PSD, so
   // lambda_min >= min m(x) whenever every w_e >= 0 (NaN when not known)
   double lambda_lb = 0.0;
+  // tables of the resident solver (whole lattice, even-odd system), made on first use
+  DevBuf res_tab[2];
+  ResTables res[2]{};
   // workspace, grown on demand
   DevBuf vec, partial, scal;
   HostPinned host;
@@ -242,9 +253,7 @@ tip_status create_handle(const tip_operator* op, hipStream_t st, tip_op_s** out)
       return bail(fail(TIP_ENOMEM, "hipMalloc links (%zu bytes): %s", n, hipGetErrorString(e_)));
     if (launch_repack_links(g, (const double2*)op->links, (double2*)h->links.p, st) != hipSuccess)
       return bail(fail(TIP_EDEVICE, "link repack launch failed"));
-    bool bip = g.pow2 != 0;
-    for (int mu = 0; mu < g.ndim; ++mu) bip = bip && g.logn[mu] >= 1;
-    if (bip) {
+    if (bipartite(g)) {
       if (const hipError_t e_ = h->links_eo.ensure(n); e_ != hipSuccess)
       return bail(fail(TIP_ENOMEM, "hipMalloc even-odd links (%zu bytes): %s", n, hipGetErrorString(e_)));
       if (launch_repack_links_eo(g, (const double2*)h->links.p, (double2*)h->links_eo.p, st) != hipSuccess)
@@ -502,6 +511,30 @@ tip_status check_params(const tip_op_s* h, const tip_params* p, int* mask_out) {
   return TIP_OK;
 }
 
+// The stream a call works on: the caller's, or for the null stream one of the
+// handle's own (which can be captured), once the null stream's work is done.
+tip_status call_stream(tip_op_s* h, const tip_params* p, hipStream_t* out) {
+  *out = (hipStream_t)p->stream;
+  if (*out || env_off("TIP_GRAPH")) return TIP_OK;
+  if (!h->own_stream) {
+    std::lock_guard<std::mutex> lk(g_device_mu);
+    if (hipStreamCreateWithFlags(&h->own_stream, hipStreamNonBlocking) != hipSuccess) h->own_stream = nullptr;
+  }
+  if (h->own_stream) {
+    // work the caller queued on the null stream comes first
+    TIP_HIP(hipStreamSynchronize(nullptr));
+    *out = h->own_stream;
+  }
+  return TIP_OK;
+}
+
+// Complex solves: covariant operator, Z4 mask, a probe past the binary columns
+// (F_3 columns of the three-colouring level are complex), or roots of unity.
+bool complex_solves(const tip_op_s* h, const tip_params* p, int mask) {
+  const bool f3 = h->geom.has3 && p->n_vectors > (int64_t(1) << h->geom.LB);
+  return h->kind == TIP_KIND_COVARIANT || mask == TIP_MASK_Z4 || f3 || p->probe == TIP_PROBE_FOURIER;
+}
+
 // CG over blocks of right-hand sides on one prepared operator.
 //   FP64:  x, r, p, w in FP64; one FP64 true-residual check per solve.
 //   mixed: x in FP64; correction xh, r, p, w in FP32 with FP32 links; FP64
@@ -566,29 +599,15 @@ struct Solver {
     geom = h->geom;
     geom.probe = p->probe;
     geom.stop = p->stop_levels;
-    st = (hipStream_t)p->stream;
-    if (!st && !env_off("TIP_GRAPH")) {
-      if (!h->own_stream) {
-        std::lock_guard<std::mutex> lk(g_device_mu);
-        if (hipStreamCreateWithFlags(&h->own_stream, hipStreamNonBlocking) != hipSuccess) h->own_stream = nullptr;
-      }
-      if (h->own_stream) {
-        // work the caller queued on the null stream comes first
-        TIP_HIP(hipStreamSynchronize(nullptr));
-        st = h->own_stream;
-      }
-    }
+    const tip_status ss = call_stream(h, p, &st);
+    if (ss != TIP_OK) return ss;
     mixed = p->precision == TIP_PREC_MIXED;
     prec = mixed ? Prec::kF32 : Prec::kF64;
     const Geom& g = geom;
     const int64_t V = g.V;
     const int ncomp = g.ncomp;
     pl.mask = mask;
-    // complex solves: covariant operator, Z4 mask, or a probe past the binary
-    // columns (F_3 columns of the three-colouring level are complex)
-    const bool f3 = g.has3 && p->n_vectors > (int64_t(1) << g.LB);
-    const bool fourier = p->probe == TIP_PROBE_FOURIER;          // roots of unity w16^e
-    pl.elem = (h->kind == TIP_KIND_COVARIANT || mask == TIP_MASK_Z4 || f3 || fourier) ? Elem::kComplex : Elem::kReal;
+    pl.elem = complex_solves(h, p, mask) ? Elem::kComplex : Elem::kReal;
     if (force_elem >= 0) pl.elem = force_elem ? Elem::kComplex : Elem::kReal;
     const size_t esz64 = pl.elem == Elem::kReal ? sizeof(double) : sizeof(double2);
     pl.esz = mixed ? esz64 / 2 : esz64;
@@ -619,9 +638,7 @@ struct Solver {
     // even-odd reduction: bipartite torus (every side >= 2, all powers of two
     // are then even) and a positive diagonal (lambda_lb > 0 implies D > 0)
     {
-      bool bip = g.pow2 != 0;
-      for (int mu = 0; mu < g.ndim; ++mu) bip = bip && g.logn[mu] >= 1;
-      pl.eo = bip && h->lambda_lb > 0.0 && !env_off("TIP_EO") &&
+      pl.eo = bipartite(g) && h->lambda_lb > 0.0 && !env_off("TIP_EO") &&
               make_marchmap(g, pl.logB, &pl.me, true, p->round_tiles, p->march_tc);
       // the covariant half-lattice kernel stages its tile's links in LDS
       if (pl.eo && h->kind == TIP_KIND_COVARIANT && (eo_lds_bytes(g, pl.me, prec) > 65536 || !h->has_links_eo))
@@ -1124,6 +1141,228 @@ tip_status tip_op_destroy(tip_op_handle h) {
 
 namespace {
 
+// ---------------------------------------------------------------------------
+// The resident solver (tip_resident_kernel.h): real scalar systems whose CG
+// direction fits in one CU's LDS, one workgroup per system.
+// ---------------------------------------------------------------------------
+
+// Which system the resident solver would run CG on for this call: 1 the
+// even-odd one, 0 the whole lattice, -1 none.  It takes the FP64 scalar
+// operator in 2 to 4 dimensions with the library's own launch shape; a caller
+// that fixes rhs_block, round_tiles or march_tc gets the block solver those
+// describe.  The limits are the LDS of a CU: 8 bytes per site of the system.
+int resident_system(const tip_op_s* h, const tip_params* p) {
+  const Geom& g = h->geom;
+  if (h->kind != TIP_KIND_SCALAR || p->precision != TIP_PREC_FP64 || g.ndim < 2 || p->rhs_block != 0 ||
+      p->round_tiles != 0 || p->march_tc != 0 || env_off("TIP_RESIDENT"))
+    return -1;
+  if (bipartite(g) && h->lambda_lb > 0.0 && !env_off("TIP_EO")) return g.V / 2 <= kResMaxEo ? 1 : -1;
+  return g.V <= kResMaxPlain ? 0 : -1;
+}
+
+tip_status resident_tables(tip_op_s* h, int eo, hipStream_t st) {
+  if (h->res[eo].n) return TIP_OK;
+  const Geom& g = h->geom;
+  const size_t np = eo ? 2 : 1, nd = (size_t)g.ndim;
+  const uint32_t n = eo ? g.V / 2 : g.V, npad = res_npad(n);
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    const size_t o = at;
+    at += (bytes + 255) & ~size_t(255);
+    return o;
+  };
+  const size_t o_nbr = take(eo ? 0 : nd * npad * sizeof(uint32_t));
+  const size_t o_wgt = take(h->has_coupling ? np * nd * npad * sizeof(double2) : 0);
+  const size_t o_d = take(np * npad * sizeof(double)), o_i = take(np * npad * sizeof(double));
+  const size_t o_s = take(np * npad * sizeof(uint32_t));
+  if (const hipError_t e_ = h->res_tab[eo].ensure(at); e_ != hipSuccess)
+    return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of solver tables failed: %s", at, hipGetErrorString(e_));
+  char* b = (char*)h->res_tab[eo].p;
+  double2* wgt = h->has_coupling ? (double2*)(b + o_wgt) : nullptr;
+  TIP_HIP(launch_res_tables(g, eo != 0, (const double*)h->diag.p,
+                            h->has_coupling ? (const double*)h->coupling.p : nullptr, n, npad,
+                            (uint32_t*)(b + o_nbr), wgt, (double*)(b + o_d), (double*)(b + o_i), (uint32_t*)(b + o_s),
+                            st));
+  h->res[eo] = ResTables{(const uint32_t*)(b + o_nbr), wgt, (const double*)(b + o_d), (const double*)(b + o_i),
+                         (const uint32_t*)(b + o_s), n, npad};
+  return TIP_OK;
+}
+
+// The right-hand sides of a call, in launches of at most `chunk`: either
+// [r0, r1) of one element type, or with classes those of F_3 class 0 (real)
+// and class 1 (complex) together.  done(c, i, result) takes the results of
+// class c in order and stops being called for it after the first that was not
+// accepted; solved(x, logB, nb) is called after each launch with its solutions
+// ([nblk][V][2^logB] of the element type, nb right-hand sides; one class only).
+struct ResidentResult {
+  int state, iters, restarts;
+  double q, relres;              // b^H x is real: A is real and symmetric
+};
+struct ResidentRun {
+  tip_op_s* h;
+  const tip_params* p;
+  int mask, eo;
+  Geom geom;                     // with the call's probe kind and class
+  hipStream_t st = nullptr;
+  Elem elem = Elem::kReal;
+  int64_t launches = 0, matvecs = 0, restarts = 0;
+  double seconds = 0.0, bytes = 0.0, op_bytes = 0.0;
+
+  tip_status setup(tip_op_s* handle, const tip_params* params, int mask_, int eo_, int force_elem) {
+    h = handle;
+    p = params;
+    mask = mask_;
+    eo = eo_;
+    geom = h->geom;
+    geom.probe = p->probe;
+    geom.stop = p->stop_levels;
+    elem = complex_solves(h, p, mask) ? Elem::kComplex : Elem::kReal;
+    if (force_elem >= 0) elem = force_elem ? Elem::kComplex : Elem::kReal;
+    tip_status s = call_stream(h, p, &st);
+    if (s != TIP_OK) return s;
+    return resident_tables(h, eo, st);
+  }
+
+  template <class Done, class Solved>
+  tip_status run(int64_t r0, int64_t r1, int64_t s0, int64_t s1, bool cls, bool need_x, Done&& done,
+                 Solved&& solved) {
+    const ResTables& t = h->res[eo];
+    const int parts = elem == Elem::kComplex ? 2 : 1;
+    const size_t V = geom.V, esz = elem == Elem::kComplex ? 16 : 8;
+    int dev = 0, cus = 0;
+    TIP_HIP(hipGetDevice(&dev));
+    TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int slots = cus * res_wgs_per_cu(t.n);
+    // solutions are kept in blocks of 64 right-hand sides, at most 1 GiB of them
+    int logB = 0;
+    while (logB < 6 && (int64_t(1) << logB) < r1 - r0) ++logB;
+    int64_t chunk = 1 << 14;
+    if (need_x) {
+      const int64_t blk = (int64_t)std::max<size_t>(1, (size_t(1) << 30) / (V * esz << logB));
+      chunk = std::min<int64_t>(chunk, blk << logB);
+    }
+    const int64_t chunk1 = std::min(chunk, s1 - s0);
+    chunk = std::min(chunk, r1 - r0);
+    const int64_t most_sys = chunk * parts + chunk1 * 2;
+    const size_t stride = (size_t)t.npad * (eo ? 4 : 2);
+    const size_t ws_bytes = (size_t)std::min<int64_t>(slots, most_sys) * stride * sizeof(double);
+    const size_t x_bytes = need_x ? (((size_t)chunk + (size_t(1) << logB) - 1) >> logB) * (V * esz << logB) : 0;
+    if (const hipError_t e_ = h->vec.ensure(ws_bytes + x_bytes); e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of CG vectors failed: %s", ws_bytes + x_bytes,
+                  hipGetErrorString(e_));
+    const size_t nsys_max = (size_t)most_sys;
+    if (const hipError_t e_ = h->host.ensure(nsys_max * (3 * sizeof(double) + 3 * sizeof(int)) + 64); e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_));
+    if (const hipError_t e_ = h->scal.ensure(256); e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipMalloc scalars: %s", hipGetErrorString(e_));
+    int max_restarts = 8, force = 0;
+    const double tol2 = p->tol * p->tol;
+    double freeze2 = tol2;
+    if (const char* e = std::getenv("TIP_FORCE_BREAKDOWN")) force = std::max(0, std::atoi(e));
+    if (const char* e = std::getenv("TIP_FREEZE_SLACK")) {
+      const double f = std::atof(e);
+      if (f > 1.0 && std::isfinite(f)) freeze2 = tol2 * f * f;
+    }
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    if (g_profiling)
+      for (int k = 0; k < 2; ++k) {
+        if ((size_t)k == h->events.size()) {
+          hipEvent_t ne;
+          TIP_HIP(hipEventCreate(&ne));
+          h->events.push_back(ne);
+        }
+        ev[k] = h->events[(size_t)k];
+      }
+    bool failed[2] = {false, false};
+    for (int64_t c0 = r0, d0 = s0; (c0 < r1 && !failed[0]) || (d0 < s1 && !failed[1]); c0 += chunk, d0 += chunk1) {
+      const int64_t nr = failed[0] ? 0 : std::max<int64_t>(0, std::min(chunk, r1 - c0));
+      const int64_t ns = failed[1] ? 0 : std::max<int64_t>(0, std::min(chunk1, s1 - d0));
+      ResArgs a{};
+      a.g = geom;
+      a.t = t;
+      a.seed = p->seed;
+      a.mask = mask;
+      a.parts = parts;
+      a.rhs0 = c0;
+      a.rhs1 = d0;
+      a.nsys0 = (int)(nr * parts);
+      a.nsys = a.nsys0 + (int)(ns * 2);
+      a.cls = cls ? 1 : 0;
+      a.start_frozen = p->tol >= 1.0 ? 1 : 0;
+      a.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)V, 1 << 20);
+      a.max_restarts = max_restarts;
+      a.force_iter = force;
+      a.tol2 = tol2;
+      a.freeze2 = freeze2;
+      a.ws = (double*)h->vec.p;
+      a.ws_stride = stride;
+      a.xout = need_x ? (double*)((char*)h->vec.p + ws_bytes) : nullptr;
+      a.logB = logB;
+      a.out = (double*)h->host.p;                      // pinned host memory, written by the kernel
+      a.outi = (int*)(a.out + 3 * nsys_max);
+      a.first_failed = (int*)h->scal.p;
+      TIP_HIP(launch_res_reset(a.first_failed, st));
+      if (need_x && (nr & ((int64_t(1) << logB) - 1)))   // lanes past the last right-hand side
+        TIP_HIP(launch_fill(x_bytes / sizeof(double), a.xout, 0.0, st));
+      if (ev[0]) TIP_HIP(hipEventRecord(ev[0], st));
+      TIP_HIP(launch_resident(a, eo != 0, (unsigned)std::min<int64_t>(a.nsys, slots), st));
+      if (ev[1]) TIP_HIP(hipEventRecord(ev[1], st));
+      if (need_x) {
+        tip_status s = solved(a.xout, logB, (int)nr);
+        if (s != TIP_OK) return s;
+      }
+      TIP_HIP(hipStreamSynchronize(st));
+      int most = 0;
+      for (int64_t l = 0; l < nr + ns; ++l) {
+        const int c = l < nr ? 0 : 1, np = c ? 2 : parts;
+        if (failed[c]) continue;
+        const int64_t i = c ? l - nr : l;
+        ResidentResult r{kAccepted, 0, 0, 0.0, 0.0};
+        double rt2 = 0.0, bn2 = 0.0;
+        for (int k = 0; k < np; ++k) {
+          const size_t sys = (size_t)((c ? a.nsys0 : 0) + i * np + k);
+          const double* o = a.out + 3 * sys;
+          const int* oi = a.outi + 3 * sys;
+          if (r.state == kAccepted) r.state = oi[0];
+          r.iters = std::max(r.iters, oi[1]);
+          r.restarts = std::max(r.restarts, oi[2]);
+          r.q += o[0];
+          rt2 += o[1];
+          bn2 += o[2];
+        }
+        r.relres = bn2 > 0.0 ? std::sqrt(rt2 / bn2) : 0.0;
+        restarts += r.restarts;
+        most = std::max(most, r.iters);
+        done(c, (c ? d0 : c0) + i, r);
+        failed[c] = r.state != kAccepted;
+      }
+      // a launch is one block of right-hand sides: an operator application per iteration of its longest solve
+      ++launches;
+      matvecs += most;
+      const double table = (double)(eo ? 2 : 1) * t.n * ((eo ? 0.0 : 4.0 * geom.ndim) + (t.wgt ? 16.0 * geom.ndim : 0.0) + 12.0);
+      bytes += table + 8.0 * 5 * (double)a.nsys;
+      op_bytes += table;
+      if (ev[0]) {
+        float ms = 0.f;
+        TIP_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
+        seconds += ms * 1e-3;
+      }
+    }
+    return TIP_OK;
+  }
+
+  void fill_stats(tip_stats* stats) const {
+    stats->stencil_launches = launches;
+    stats->stencil_seconds = seconds;
+    stats->stencil_bytes = bytes;
+    stats->matvecs = matvecs;
+    stats->matvec_seconds = seconds;
+    stats->matvec_bytes = op_bytes;
+    stats->even_odd = eo ? 1 : 0;
+    stats->restarts = restarts;
+  }
+};
+
 // Per-rhs results of one probing run: slot k = (m - m_begin) * ncomp + c for
 // probe m and component c.
 struct RunResult {
@@ -1331,7 +1570,29 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
     }
     return TIP_OK;
   };
-  auto add_stats = [&](const Solver& sv) {
+  const int res = resident_system(h, p);
+  // Right-hand sides through the resident solver: result slot(c, i) takes
+  // right-hand side i (of class c).
+  auto run_resident = [&](int64_t r0, int64_t r1, int64_t s0, int64_t s1, bool cls, ResidentRun& rs,
+                          auto slot) -> tip_status {
+    return rs.run(
+        r0, r1, s0, s1, cls, want_grad,
+        [&](int c, int64_t r, const ResidentResult& o) {
+          const size_t k = slot(c, r);
+          rr.qre[k] = o.q;
+          rr.state[k] = o.state;
+          rr.iters[k] = o.iters;
+          rr.relres[k] = o.relres;
+        },
+        [&](double* x, int logB, int nr) -> tip_status {
+          const size_t step = (V << logB) * (rs.elem == Elem::kComplex ? 2 : 1);
+          for (int b = 0; b << logB < nr; ++b)
+            TIP_HIP(launch_grad_accum(h->dev(), gg, rs.elem, logB, std::min(1 << logB, nr - (b << logB)),
+                                      x + (size_t)b * step, grad_mass, grad_coupling, rs.st));
+          return TIP_OK;
+        });
+  };
+  auto add_stats = [&](const auto& sv) {
     tip_stats t;
     std::memset(&t, 0, sizeof t);
     sv.fill_stats(&t);
@@ -1346,42 +1607,73 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
     rr.acc.even_odd = rr.acc.even_odd || t.even_odd;
   };
   if (!conj_split(gg, h->kind, mask, p, want_grad)) {
-    Solver sv;
-    sv.need_x = want_grad;
-    s = sv.setup(h, p, mask);
-    if (s != TIP_OK) return s;
-    st_used = sv.st;
-    if (grad_mass) TIP_HIP(launch_fill(V, grad_mass, 0.0, sv.st));
-    if (grad_coupling) TIP_HIP(launch_fill((size_t)gg.ndim * V, grad_coupling, 0.0, sv.st));
     const int64_t base = p->m_begin * ncomp;
-    s = run_range(sv, base, base + n_rhs, [&](int64_t r) { return (size_t)(r - base); });
-    if (s != TIP_OK) return s;
-    add_stats(sv);
+    auto slot = [&](int64_t r) { return (size_t)(r - base); };
+    auto clear = [&](hipStream_t st) -> tip_status {
+      st_used = st;
+      if (grad_mass) TIP_HIP(launch_fill(V, grad_mass, 0.0, st));
+      if (grad_coupling) TIP_HIP(launch_fill((size_t)gg.ndim * V, grad_coupling, 0.0, st));
+      return TIP_OK;
+    };
+    if (res >= 0) {
+      ResidentRun rs;
+      s = rs.setup(h, p, mask, res, -1);
+      if (s == TIP_OK) s = clear(rs.st);
+      if (s == TIP_OK)
+        s = run_resident(base, base + n_rhs, 0, 0, false, rs, [&](int, int64_t r) { return slot(r); });
+      if (s != TIP_OK) return s;
+      add_stats(rs);
+    } else {
+      Solver sv;
+      sv.need_x = want_grad;
+      s = sv.setup(h, p, mask);
+      if (s == TIP_OK) s = clear(sv.st);
+      if (s == TIP_OK) s = run_range(sv, base, base + n_rhs, slot);
+      if (s != TIP_OK) return s;
+      add_stats(sv);
+    }
   } else {
     const ClassMap cm{(int64_t)gg.gamma, int64_t(1) << gg.LB};
     // each class runs up to its own first failure; the checkpoints then stop
     // at the first probe, in probe order, that is not accepted
-    for (int pass = 0; pass < 2; ++pass) {
-      failed = false;
-      const int64_t m0 = cm.first_member(p->m_begin, pass);
+    int64_t i0[2] = {0, 0}, i1[2] = {0, 0};
+    Geom cg[2] = {gg, gg};
+    for (int c = 0; c < 2; ++c) {
+      cg[c].cls_gamma = (int32_t)cm.gam;
+      cg[c].cls_nbc = (int32_t)cm.nbc;
+      cg[c].cls_j3 = c;
+      const int64_t m0 = cm.first_member(p->m_begin, c);
       if (m0 >= p->n_vectors) continue;
-      const int64_t i0 = cm.index(m0, pass);
-      const int64_t i1 = cm.index(cm.first_member(p->n_vectors, pass), pass);   // one past the last member
-      Solver sv;
-      sv.force_elem = pass;          // j3 = 0: real, j3 = 1: complex
-      sv.rhs_hint = (i1 - i0) * ncomp;
-      s = sv.setup(h, p, mask);
+      i0[c] = cm.index(m0, c);
+      i1[c] = cm.index(cm.first_member(p->n_vectors, c), c);      // one past the last member
+    }
+    auto slot = [&](int c, int64_t r) {
+      const int64_t m = (int64_t)class_probe((uint64_t)(r / ncomp), cg[c]);
+      return (size_t)((m - p->m_begin) * ncomp + r % ncomp);
+    };
+    if (res >= 0) {
+      ResidentRun rs;
+      s = rs.setup(h, p, mask, res, 0);
+      if (s == TIP_OK) s = run_resident(i0[0], i1[0], i0[1], i1[1], true, rs, slot);
       if (s != TIP_OK) return s;
-      sv.geom.cls_gamma = (int32_t)cm.gam;
-      sv.geom.cls_nbc = (int32_t)cm.nbc;
-      sv.geom.cls_j3 = pass;
-      st_used = sv.st;
-      s = run_range(sv, i0 * ncomp, i1 * ncomp, [&](int64_t r) {
-        const int64_t m = (int64_t)class_probe((uint64_t)(r / ncomp), sv.geom);
-        return (size_t)((m - p->m_begin) * ncomp + r % ncomp);
-      });
-      if (s != TIP_OK) return s;
-      add_stats(sv);
+      add_stats(rs);
+    } else {
+      for (int c = 0; c < 2; ++c) {
+        failed = false;
+        if (i0[c] >= i1[c]) continue;
+        Solver sv;
+        sv.force_elem = c;             // j3 = 0: real, j3 = 1: complex
+        sv.rhs_hint = (i1[c] - i0[c]) * ncomp;
+        s = sv.setup(h, p, mask);
+        if (s != TIP_OK) return s;
+        sv.geom.cls_gamma = cg[c].cls_gamma;
+        sv.geom.cls_nbc = cg[c].cls_nbc;
+        sv.geom.cls_j3 = c;
+        st_used = sv.st;
+        s = run_range(sv, i0[c] * ncomp, i1[c] * ncomp, [&](int64_t r) { return slot(c, r); });
+        if (s != TIP_OK) return s;
+        add_stats(sv);
+      }
     }
     conj_copies(gg, p, ncomp, rr);
   }
@@ -1956,6 +2248,36 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
   if (m < 0 || m >= (int64_t)g.V) return fail(TIP_EINVAL, "probe %lld outside [0, V)", (long long)m);
   if (comp < 0 || comp >= g.ncomp) return fail(TIP_EINVAL, "comp = %d out of range", comp);
   if (!x_out) return fail(TIP_EINVAL, "x_out is NULL");
+  if (const int res = resident_system(h, &one); res >= 0) {
+    ResidentRun rs;
+    ResidentResult o{};
+    s = rs.setup(h, &one, mask, res, -1);
+    if (s == TIP_OK)
+      s = rs.run(
+          m, m + 1, 0, 0, false, true, [&](int, int64_t, const ResidentResult& r) { o = r; },
+          [&](double* x, int logB, int) -> tip_status {
+            TIP_HIP(launch_layout(g, rs.elem, logB, 0, x, x_out, false, rs.st));
+            return TIP_OK;
+          });
+    if (s != TIP_OK) return s;
+    if (q_out) {
+      q_out[0] = o.q;
+      q_out[1] = 0.0;
+    }
+    if (stats) {
+      std::memset(stats, 0, sizeof *stats);
+      stats->solves = 1;
+      stats->total_iters = o.iters;
+      stats->max_iters = o.iters;
+      stats->max_true_relres = o.relres;
+      stats->max_quad_err_bound = o.relres * o.relres * (double)g.V / h->lambda_lb;
+      rs.fill_stats(stats);
+      stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
+    }
+    if (o.state == kBreakdown) return fail(TIP_EBREAKDOWN, "solve broke down (p^H A p <= 0)");
+    if (o.state != kAccepted) return fail(TIP_ENOCONV, "solve did not converge within max_iter");
+    return TIP_OK;
+  }
   Solver sv;
   sv.need_x = true;
   s = sv.setup(h, &one, mask);

@@ -1,0 +1,73 @@
+// Interface of the resident solver (tip_resident_kernel.h): CG on the real
+// scalar operator with one workgroup per right-hand side and the search
+// direction in LDS.  Not part of the public C ABI.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "tip_device.h"
+
+namespace tip {
+
+// Per-operator tables, one row per site of the system that CG runs on (the
+// whole lattice, or the sites of one parity p of the even-odd system), padded
+// to npad rows.  On the whole lattice nbr holds the two neighbours of a row
+// along mu as row numbers, forward in the low half word, backward in the high
+// one; padding rows name row n, an LDS word that is kept zero.
+struct ResTables {
+  const uint32_t* nbr;       // [ndim][npad], whole lattice only
+  const double2* wgt;        // [parities][ndim][npad] w_mu(s), w_mu(s - mu); null without couplings
+  const double* D;           // [parities][npad] diagonal, 0 in padding rows
+  const double* Dinv;        // [parities][npad] its reciprocal
+  const uint32_t* site;      // [parities][npad] lattice site of the row
+  uint32_t n, npad;
+};
+
+// One launch: systems 0 .. nsys-1, system i < nsys0 solving part i % parts (0
+// real, 1 imaginary) of right-hand side rhs0 + i / parts.  A is real, so the
+// two parts of a complex right-hand side are two real systems, and b^H A^-1 b,
+// real for any b, is the sum of their quadratures.  With cls the
+// right-hand sides are those of the F_3 classes of the conjugate split: class
+// 0 (real, parts = 1) first, then from nsys0 on class 1 (complex) from rhs1.
+struct ResArgs {
+  Geom g;
+  ResTables t;
+  uint64_t seed;
+  int mask;
+  int parts;
+  int64_t rhs0, rhs1;
+  int nsys0, nsys, cls;
+  int start_frozen, max_iter, max_restarts, force_iter;
+  double tol2, freeze2;
+  double* ws;                // per workgroup: b (per parity), x (per parity), npad values each
+  size_t ws_stride;
+  double* xout;              // [blocks][V][2^logB][parts] solutions on the lattice, or null
+  int logB;
+  double* out;               // [nsys][3]: b . x, ||b - A x||^2, ||b||^2
+  int* outi;                 // [nsys][3]: state, iterations, restarts
+  int* first_failed;         // lowest system that failed; systems above it may be skipped
+};
+
+constexpr uint32_t kResMaxPlain = 20000;     // rows of 8 bytes: p, the zero word and the sums in 160 KB of LDS
+constexpr uint32_t kResMaxEo = 16384;
+
+// Fills the tables on the device (diag: D(x) then 1 / D(x) on the lattice).
+hipError_t launch_res_tables(const Geom& g, bool eo, const double* diag, const double* coupling, uint32_t n,
+                             uint32_t npad, uint32_t* nbr, double2* wgt, double* D, double* Dinv, uint32_t* site,
+                             hipStream_t st);
+// Rows the tables are padded to, and workgroups that are resident on one CU.
+inline uint32_t res_npad(uint32_t n) { return (n + 2047u) & ~2047u; }
+int res_wgs_per_cu(uint32_t n);
+// first_failed = no system
+hipError_t launch_res_reset(int* first_failed, hipStream_t st);
+hipError_t launch_resident_2d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st);
+hipError_t launch_resident_3d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st);
+hipError_t launch_resident_4d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st);
+inline hipError_t launch_resident(const ResArgs& a, bool eo, unsigned grid, hipStream_t st) {
+  return a.g.ndim == 2 ? launch_resident_2d(a, eo, grid, st)
+         : a.g.ndim == 3 ? launch_resident_3d(a, eo, grid, st)
+                         : launch_resident_4d(a, eo, grid, st);
+}
+
+}  // namespace tip

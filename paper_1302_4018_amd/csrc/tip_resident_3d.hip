@@ -1,0 +1,10 @@
+// The resident solver on 3-dimensional lattices.
+#include "tip_resident_kernel.h"
+
+namespace tip {
+
+hipError_t launch_resident_3d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st) {
+  return launch_resident_dim<3>(a, eo, grid, st);
+}
+
+}  // namespace tip

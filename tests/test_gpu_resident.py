@@ -1,0 +1,51 @@
+"""The resident solver (one workgroup per right-hand side, direction in LDS) at
+the edges of its row counts, against the oracle: systems of 2 rows to the
+largest, whole lattices just below and above each change of shape, real and
+complex right-hand sides, with and without couplings."""
+
+import numpy as np
+import pytest
+
+from conftest import gpu_binding, to_dev
+from oracle.general import trace_inv_probe as oracle_trace
+from oracle.mask import MASK_Z2, MASK_Z4
+from oracle.operators import Operator as OracleOp
+from paper_1302_4018_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+REL = 1e-10      # both sides solve to 1e-12; a quadrature's error is second order in the residual
+
+
+@pytest.mark.parametrize("dims", [
+    # even-odd systems: V / 2 = 2, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384 rows
+    [2, 2], [4, 8], [4, 4, 4], [8, 16], [16, 16], [8, 8, 8], [32, 32], [8, 4, 8, 8], [16, 16, 16], [32, 16, 16],
+    [8, 8, 16, 16], [32, 32, 32],
+    # whole lattices: 15, 256, 264, 1023, 1056, 2025, 2052, 4096, 4097, 8190, 8448, 20000 rows
+    [3, 5], [16, 16, 1], [11, 24], [31, 33], [32, 33], [45, 45], [19, 12, 9], [64, 64, 1], [17, 241], [90, 91],
+    [4, 8, 8, 33], [20, 40, 25],
+])
+@pytest.mark.parametrize("mask,weighted", [(MASK_Z2, True), (MASK_Z4, False)])
+def test_resident_matches_oracle(dims, mask, weighted):
+    tip = gpu_binding()
+    w = inputs.couplings(dims, seed=900) if weighted else None
+    mf = inputs.mass_field(dims, m0=0.4, seed=901)
+    orc = OracleOp(dims, 0, mass_field=mf, coupling=w)
+    gop = tip.Operator(dims, 0, mass_field=to_dev(mf), coupling=to_dev(w))
+    n = min(orc.V, 5)
+    est, q, st = tip.trace_inv_probe(gop, n, 1e-12, 4018, mask=mask)
+    est_o, q_o, _ = oracle_trace(orc, n, 1e-12, 4018, mask)
+    assert st["stencil_launches"] == 1, "not the resident solver"
+    assert st["max_true_relres"] <= 1e-12
+    assert np.max(np.abs(est - est_o) / np.abs(est_o)) <= REL
+    assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL
+
+
+def test_first_lattice_past_the_limit_uses_the_block_solver():
+    tip = gpu_binding()
+    gop = tip.Operator([3, 59, 113], 0, mass=0.4)            # 20001 sites
+    _, q, st = tip.trace_inv_probe(gop, 3, 1e-12, 4018)
+    orc = OracleOp([3, 59, 113], 0, mass=0.4)
+    _, q_o, _ = oracle_trace(orc, 3, 1e-12, 4018, MASK_Z2)
+    assert st["stencil_launches"] > 1
+    assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL
