@@ -2218,6 +2218,42 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
   return TIP_OK;
 }
 
+// y = A x (tip_apply_operator, tip_apply_operator_noalloc).  The kernel reads
+// and writes the caller's arrays in place, one launch for all right-hand
+// sides; where x and y overlap each input vector is copied to `stage` first,
+// one right-hand side after another.
+tip_status validate_apply(const tip_operator* op, int32_t nrhs, const double* x, const double* y, Geom* g) {
+  tip_status s = validate_op(op, g);
+  if (s != TIP_OK) return s;
+  if (nrhs < 1) return fail(TIP_EINVAL, "nrhs = %d must be >= 1", nrhs);
+  if (!x || !y) return fail(TIP_EINVAL, "x or y is NULL");
+  return TIP_OK;
+}
+size_t apply_bytes(const Geom& g) {                      // one vector
+  return (size_t)g.ncomp * g.V * (g.ncomp == 3 ? sizeof(double2) : sizeof(double));
+}
+bool apply_overlaps(const Geom& g, int32_t nrhs, const double* x, const double* y) {
+  const uintptr_t a = (uintptr_t)x, b = (uintptr_t)y, n = (uintptr_t)nrhs * apply_bytes(g);
+  return a < b + n && b < a + n;
+}
+tip_status run_apply(const tip_operator* op, const Geom& g, int32_t nrhs, const double* x, double* y, void* stage,
+                     hipStream_t st) {
+  const size_t bytes = apply_bytes(g);
+  auto launch = [&](int n, const void* in, void* out) {
+    return launch_apply(g, op->kind, n, op->mass_field, op->mass, op->coupling, op->links, in, out, st);
+  };
+  if (!apply_overlaps(g, nrhs, x, y)) {
+    if (launch(nrhs, x, y) != hipSuccess) return fail(TIP_EDEVICE, "apply launch failed");
+  } else {
+    for (int32_t k = 0; k < nrhs; ++k)
+      if (hipMemcpyAsync(stage, (const char*)x + k * bytes, bytes, hipMemcpyDeviceToDevice, st) != hipSuccess ||
+          launch(1, stage, (char*)y + k * bytes) != hipSuccess)
+        return fail(TIP_EDEVICE, "apply launch failed");
+  }
+  if (hipStreamSynchronize(st) != hipSuccess) return fail(TIP_EDEVICE, "apply failed on the device");
+  return TIP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2256,7 +2292,7 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
       s = rs.run(
           m, m + 1, 0, 0, false, true, [&](int, int64_t, const ResidentResult& r) { o = r; },
           [&](double* x, int logB, int) -> tip_status {
-            TIP_HIP(launch_layout(g, rs.elem, logB, 0, x, x_out, false, rs.st));
+            TIP_HIP(launch_layout(g, rs.elem, logB, 0, x, x_out, rs.st));
             return TIP_OK;
           });
     if (s != TIP_OK) return s;
@@ -2284,7 +2320,7 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
   if (s != TIP_OK) return s;
   s = sv.solve_block(m * g.ncomp + comp, 1);
   if (s != TIP_OK) return s;
-  TIP_HIP(launch_layout(g, sv.pl.elem, sv.pl.logB, 0, sv.X, x_out, false, sv.st));
+  TIP_HIP(launch_layout(g, sv.pl.elem, sv.pl.logB, 0, sv.X, x_out, sv.st));
   TIP_HIP(hipStreamSynchronize(sv.st));
   if (q_out) {
     q_out[0] = sv.h_q[0];
@@ -2427,33 +2463,14 @@ tip_status tip_autotune_batch(const tip_operator* ops, const tip_params* params,
 
 tip_status tip_apply_operator(const tip_operator* op, int32_t nrhs, const double* x, double* y, void* stream) {
   Geom g;
-  tip_status s = validate_op(op, &g);
+  tip_status s = validate_apply(op, nrhs, x, y, &g);
   if (s != TIP_OK) return s;
-  if (nrhs < 1) return fail(TIP_EINVAL, "nrhs = %d must be >= 1", nrhs);
-  if (!x || !y) return fail(TIP_EINVAL, "x or y is NULL");
-  hipStream_t st = (hipStream_t)stream;
-  tip_op_s* h = nullptr;
-  s = create_handle(op, st, &h);
-  if (s != TIP_OK) return s;
-  const Elem elem = op->kind == TIP_KIND_COVARIANT ? Elem::kComplex : Elem::kReal;
-  const size_t esz = elem == Elem::kReal ? sizeof(double) : sizeof(double2);
-  const size_t bytes = (size_t)g.ncomp * g.V * esz;       // one vector
-  const TileMap tm = make_tilemap(g, 0);
-  tip_status ret = TIP_OK;
-  if (h->vec.ensure(2 * bytes) != hipSuccess) ret = fail(TIP_ENOMEM, "hipMalloc apply buffers");
-  for (int k = 0; k < nrhs && ret == TIP_OK; ++k) {
-    char* in = (char*)h->vec.p;
-    char* out = in + bytes;
-    const char* xk = (const char*)x + k * bytes;
-    char* yk = (char*)y + k * bytes;
-    if (launch_layout(g, elem, 0, 0, xk, in, true, st) != hipSuccess ||
-        launch_stencil(h->dev(), g, tm, nullptr, elem, Prec::kF64, nullptr, nullptr, in, out, nullptr, nullptr, st) != hipSuccess ||
-        launch_layout(g, elem, 0, 0, out, yk, false, st) != hipSuccess)
-      ret = fail(TIP_EDEVICE, "apply launch failed");
+  DevBuf stage;
+  if (apply_overlaps(g, nrhs, x, y)) {
+    if (const hipError_t e_ = stage.ensure(apply_bytes(g)); e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipMalloc apply buffer: %s", hipGetErrorString(e_));
   }
-  if (ret == TIP_OK && hipStreamSynchronize(st) != hipSuccess) ret = fail(TIP_EDEVICE, "apply failed on the device");
-  delete h;
-  return ret;
+  return run_apply(op, g, nrhs, x, y, stage.p, (hipStream_t)stream);
 }
 
 }  // extern "C"
@@ -2510,49 +2527,22 @@ extern "C" {
 tip_status tip_apply_operator_noalloc(const tip_operator* op, int32_t nrhs, const double* x, double* y,
                                       void* stream) {
   Geom g;
-  tip_status s = validate_op(op, &g);
+  tip_status s = validate_apply(op, nrhs, x, y, &g);
   if (s != TIP_OK) return s;
-  if (nrhs < 1) return fail(TIP_EINVAL, "nrhs = %d must be >= 1", nrhs);
-  if (!x || !y) return fail(TIP_EINVAL, "x or y is NULL");
-  const bool cov = op->kind == TIP_KIND_COVARIANT;
-  const Elem elem = cov ? Elem::kComplex : Elem::kReal;
-  const size_t esz = cov ? sizeof(double2) : sizeof(double);
-  const size_t bytes = (size_t)g.ncomp * g.V * esz;                   // one vector
-  const size_t link_bytes = cov ? (size_t)g.ndim * 9 * g.V * sizeof(double2) : 0;
+  // lattices are accepted up to the size whose links and two vectors fit the
+  // scratch; only an input that overlaps the output uses it
+  const size_t bytes = apply_bytes(g);
+  const size_t link_bytes = op->kind == TIP_KIND_COVARIANT ? (size_t)g.ndim * 9 * g.V * sizeof(double2) : 0;
   const size_t need = align256(link_bytes) + 2 * align256(bytes);
   if (need > kScratchBytes)
     return fail(TIP_EINVAL, "lattice needs %zu bytes of workspace; the no-allocation scratch holds %zu", need,
                 kScratchBytes);
-  void* base = nullptr;
-  s = scratch_address(&base);
-  if (s != TIP_OK) return s;
-  hipStream_t st = (hipStream_t)stream;
-  char* links = (char*)base;
-  char* in = links + align256(link_bytes);
-  char* out = in + align256(bytes);
-  // the caller's mass field and couplings are read in place; the links are
-  // repacked into the scratch ([ndim][9][V], as the kernels read them)
-  OpDev od{};
-  od.kind = op->kind;
-  od.mass = op->mass;
-  od.mass_field = op->mass_field;
-  od.coupling = op->coupling;
-  od.links = cov ? (const double*)links : nullptr;
-  od.links_eo = nullptr;
-  if (cov && launch_repack_links(g, (const double2*)op->links, (double2*)links, st) != hipSuccess)
-    return fail(TIP_EDEVICE, "link repack launch failed");
-  const TileMap tm = make_tilemap(g, 0);
-  for (int k = 0; k < nrhs; ++k) {
-    const char* xk = (const char*)x + k * bytes;
-    char* yk = (char*)y + k * bytes;
-    if (launch_layout(g, elem, 0, 0, xk, in, true, st) != hipSuccess ||
-        launch_stencil(od, g, tm, nullptr, elem, Prec::kF64, nullptr, nullptr, in, out, nullptr, nullptr, st) !=
-            hipSuccess ||
-        launch_layout(g, elem, 0, 0, out, yk, false, st) != hipSuccess)
-      return fail(TIP_EDEVICE, "apply launch failed");
+  void* stage = nullptr;
+  if (apply_overlaps(g, nrhs, x, y)) {
+    s = scratch_address(&stage);
+    if (s != TIP_OK) return s;
   }
-  if (hipStreamSynchronize(st) != hipSuccess) return fail(TIP_EDEVICE, "apply failed on the device");
-  return TIP_OK;
+  return run_apply(op, g, nrhs, x, y, stage, (hipStream_t)stream);
 }
 
 tip_status tip_hier_perm(int32_t ndim, const int64_t* dims, uint32_t* P_out, void* stream) {

@@ -204,8 +204,10 @@ hipError_t launch_probe_vectors(const Geom& g, uint64_t seed, int mask, int64_t 
                                 hipStream_t st);
 hipError_t launch_repack_links_eo(const Geom& g, const double2* links, double2* dst, hipStream_t st);
 hipError_t launch_repack_links(const Geom& g, const double2* src, double2* dst, hipStream_t st);
-// [V][ncomp] <-> lane `lane` of the block layout [ncomp][V][2^logB] (FP64)
-hipError_t launch_layout(const Geom& g, Elem elem, int logB, int lane, const void* src, void* dst,
-                         bool to_comp_major, hipStream_t st);
+// lane `lane` of the block layout [ncomp][V][2^logB] (FP64) -> [V][ncomp]
+hipError_t launch_layout(const Geom& g, Elem elem, int logB, int lane, const void* src, void* dst, hipStream_t st);
+// y = A x on arrays in the layout of the C ABI; x and y must not overlap
+hipError_t launch_apply(const Geom& g, int kind, int nrhs, const double* mass_field, double mass, const double* w,
+                        const double* links, const void* x, void* y, hipStream_t st);
 
 }  // namespace tip
