@@ -21,9 +21,9 @@
  *   S = D_e - H_eo D_o^-1 H_oe over the even sites (half the vector length,
  *   about half the iterations), then forms x_o = D_o^-1 (b_o + H_oe x_e).  The
  *   acceptance test is the same FP64 true residual of the full system.
- *   Small scalar lattices in FP64 (2 to 4 dimensions, V <= 32768 with power-of-two
- *   sides, V <= 20000 otherwise) are solved with one workgroup per right-hand
- *   side, whole solves in one launch, unless the caller fixes rhs_block,
+ *   Scalar lattices in FP64 whose CG vector fits the LDS of one CU (even-odd
+ *   system, V <= 32768) or of up to 32 CUs (other sides, 2 to 4 dimensions) are
+ *   solved there, whole solves in one launch, unless the caller fixes rhs_block,
  *   round_tiles or march_tc; stencil_launches then counts these launches and
  *   matvecs the iterations of each launch's longest solve.
  *
@@ -243,6 +243,10 @@ tip_status trace_inv_probe(const tip_operator* op, const tip_params* p,
  * problem's own tol and max_iter and are accepted on the FP64 true residual;
  * the batch runs plain CG (no even-odd reduction), so results agree with
  * separate trace_inv_probe calls to the solver tolerance, not bit for bit.
+ * Scalar problems of 2 to 4 dimensions that fit the LDS of up to 32 CUs are
+ * solved there instead, whatever rhs_block and item_sites say, and in FP64 in
+ * either precision (faster there than the single-precision passes): MIXED
+ * then still reports the variational quadrature, and reliable_updates is 0.
  * stats[i].seconds is the wall time of the whole call; stats[i].stencil_*
  * describe the batch's shared stencil launches (the same in every entry;
  * timed only with tip_set_profiling(1), which also turns the graph off).

@@ -26,6 +26,7 @@
 
 #include "../../include/tip.h"
 #include "tip_batch.h"
+#include "tip_cluster.h"
 #include "tip_launch.h"
 #include "tip_resident.h"
 
@@ -175,9 +176,10 @@ struct tip_op_s {
   // lower bound of the spectrum: A = sum_e w_e L_e + diag(m) with L_e PSD, so
   // lambda_min >= min m(x) whenever every w_e >= 0 (NaN when not known)
   double lambda_lb = 0.0;
-  // tables of the resident solver (whole lattice, even-odd system), made on first use
-  DevBuf res_tab[2];
-  ResTables res[2]{};
+  // tables of the resident (even-odd) and the cluster (whole lattice) solver, made on first use
+  DevBuf res_tab, cl_tab;
+  ResTables res{};
+  ClProblem cl{};
   // workspace, grown on demand
   DevBuf vec, partial, scal;
   HostPinned host;
@@ -1142,49 +1144,203 @@ tip_status tip_op_destroy(tip_op_handle h) {
 namespace {
 
 // ---------------------------------------------------------------------------
-// The resident solver (tip_resident_kernel.h): real scalar systems whose CG
-// direction fits in one CU's LDS, one workgroup per system.
+// Real scalar systems whose CG direction fits in LDS: the even-odd system of a
+// small power-of-two lattice in one CU's (tip_resident_kernel.h), any other
+// lattice in that of a cluster of CUs (tip_cluster_kernel.h).
 // ---------------------------------------------------------------------------
 
-// Which system the resident solver would run CG on for this call: 1 the
-// even-odd one, 0 the whole lattice, -1 none.  It takes the FP64 scalar
-// operator in 2 to 4 dimensions with the library's own launch shape; a caller
-// that fixes rhs_block, round_tiles or march_tc gets the block solver those
-// describe.  The limits are the LDS of a CU: 8 bytes per site of the system.
+// How the cluster solver cuts a lattice over G workgroups: planes of its
+// longest dimension.
+struct ClusterCut {
+  int cut = 0;
+  uint32_t nz = 1, A = 1;
+  explicit ClusterCut(const Geom& g) {
+    for (int mu = 0; mu < g.ndim; ++mu)
+      if (g.n[mu] >= nz) nz = g.n[mu], cut = mu;
+    A = g.V / nz;
+  }
+  uint32_t rows(int G) const { return (nz + (uint32_t)G - 1) / (uint32_t)G * A; }
+  bool fits(int G) const {
+    return G <= (int)nz && 2 * (uint64_t)A + rows(G) <= kClLdsRows && cl_lds_rows(rows(G), A) <= kClLdsRows;
+  }
+  // Fewest workgroups that hold a system, 0 when kClMaxG do not.
+  int least() const {
+    for (int G = 1; G <= kClMaxG; ++G)
+      if (fits(G)) return G;
+    return 0;
+  }
+  // Workgroups per system when nsys systems share `cus` CUs.  More than the
+  // least while CUs would stay idle, and while the rows that one of them is
+  // spared are worth the exchanges: two per iteration, 3-4 us together, the
+  // time of about 3000 rows.
+  int pick(int64_t nsys, int cus) const {
+    int G = least();
+    while (G > 0 && 2 * G <= kClMaxG && nsys * 2 * G <= cus && fits(2 * G) && rows(G) >= (G == 1 ? 6144u : 3072u)) G *= 2;
+    return G;
+  }
+};
+
+// Which system the LDS solvers would run CG on for this call: 1 the even-odd
+// one, 0 the whole lattice, -1 none.  They take the FP64 scalar operator in 2
+// to 4 dimensions with the library's own launch shape; a caller that fixes
+// rhs_block, round_tiles or march_tc gets the block solver those describe.
 int resident_system(const tip_op_s* h, const tip_params* p) {
   const Geom& g = h->geom;
   if (h->kind != TIP_KIND_SCALAR || p->precision != TIP_PREC_FP64 || g.ndim < 2 || p->rhs_block != 0 ||
       p->round_tiles != 0 || p->march_tc != 0 || env_off("TIP_RESIDENT"))
     return -1;
-  if (bipartite(g) && h->lambda_lb > 0.0 && !env_off("TIP_EO")) return g.V / 2 <= kResMaxEo ? 1 : -1;
-  return g.V <= kResMaxPlain ? 0 : -1;
+  if (bipartite(g) && h->lambda_lb > 0.0 && !env_off("TIP_EO")) return g.V / 2 <= kResMaxRows ? 1 : -1;
+  return ClusterCut(g).least() > 0 ? 0 : -1;
 }
 
-tip_status resident_tables(tip_op_s* h, int eo, hipStream_t st) {
-  if (h->res[eo].n) return TIP_OK;
+size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
+
+tip_status resident_tables(tip_op_s* h, hipStream_t st) {
+  if (h->res.n) return TIP_OK;
   const Geom& g = h->geom;
-  const size_t np = eo ? 2 : 1, nd = (size_t)g.ndim;
-  const uint32_t n = eo ? g.V / 2 : g.V, npad = res_npad(n);
-  size_t at = 0;
-  auto take = [&](size_t bytes) {
-    const size_t o = at;
-    at += (bytes + 255) & ~size_t(255);
-    return o;
-  };
-  const size_t o_nbr = take(eo ? 0 : nd * npad * sizeof(uint32_t));
-  const size_t o_wgt = take(h->has_coupling ? np * nd * npad * sizeof(double2) : 0);
-  const size_t o_d = take(np * npad * sizeof(double)), o_i = take(np * npad * sizeof(double));
-  const size_t o_s = take(np * npad * sizeof(uint32_t));
-  if (const hipError_t e_ = h->res_tab[eo].ensure(at); e_ != hipSuccess)
-    return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of solver tables failed: %s", at, hipGetErrorString(e_));
-  char* b = (char*)h->res_tab[eo].p;
-  double2* wgt = h->has_coupling ? (double2*)(b + o_wgt) : nullptr;
-  TIP_HIP(launch_res_tables(g, eo != 0, (const double*)h->diag.p,
-                            h->has_coupling ? (const double*)h->coupling.p : nullptr, n, npad,
-                            (uint32_t*)(b + o_nbr), wgt, (double*)(b + o_d), (double*)(b + o_i), (uint32_t*)(b + o_s),
-                            st));
-  h->res[eo] = ResTables{(const uint32_t*)(b + o_nbr), wgt, (const double*)(b + o_d), (const double*)(b + o_i),
-                         (const uint32_t*)(b + o_s), n, npad};
+  const size_t nd = (size_t)g.ndim;
+  const uint32_t n = g.V / 2, npad = res_npad(n);
+  const size_t o_d = align256(h->has_coupling ? 2 * nd * npad * sizeof(double2) : 0);
+  const size_t o_i = o_d + 2 * npad * sizeof(double), o_s = o_i + 2 * npad * sizeof(double);
+  if (const hipError_t e_ = h->res_tab.ensure(o_s + 2 * npad * sizeof(uint32_t)); e_ != hipSuccess)
+    return fail(TIP_ENOMEM, "hipMalloc solver tables: %s", hipGetErrorString(e_));
+  char* b = (char*)h->res_tab.p;
+  double2* wgt = h->has_coupling ? (double2*)b : nullptr;
+  TIP_HIP(launch_res_tables(g, (const double*)h->diag.p, h->has_coupling ? (const double*)h->coupling.p : nullptr, n,
+                            npad, wgt, (double*)(b + o_d), (double*)(b + o_i), (uint32_t*)(b + o_s), st));
+  h->res = ResTables{wgt, (const double*)(b + o_d), (const double*)(b + o_i), (const uint32_t*)(b + o_s), n, npad};
+  return TIP_OK;
+}
+
+size_t cluster_table_bytes(const tip_op_s* h) {
+  const size_t npad = (size_t)h->geom.V + kClPad, nd = (size_t)h->geom.ndim;
+  return align256(h->has_coupling ? nd * npad * sizeof(double2) : 0) + align256(npad * sizeof(double)) +
+         nd * npad * sizeof(uint32_t);
+}
+// The lattice's tables in `mem` (cluster_table_bytes of it).
+tip_status cluster_tables(tip_op_s* h, char* mem, hipStream_t st) {
+  const Geom& g = h->geom;
+  const ClusterCut c(g);
+  const size_t npad = (size_t)g.V + kClPad, nd = (size_t)g.ndim;
+  double2* wgt = h->has_coupling ? (double2*)mem : nullptr;
+  double* D = (double*)(mem + align256(h->has_coupling ? nd * npad * sizeof(double2) : 0));
+  uint32_t* site = (uint32_t*)((char*)D + align256(npad * sizeof(double)));
+  uint32_t* nbr = site + npad;
+  TIP_HIP(launch_cl_tables(g, c.cut, (const double*)h->diag.p,
+                           h->has_coupling ? (const double*)h->coupling.p : nullptr, npad, nbr, wgt, D, site, st));
+  ClProblem& pr = h->cl;
+  pr.nbr = nbr;
+  pr.wgt = wgt;
+  pr.D = D;
+  pr.site = site;
+  pr.npad = npad;
+  pr.A = c.A;
+  pr.nz = c.nz;
+  return TIP_OK;
+}
+
+// Freeze threshold of the first pass and the forced breakdown of the tests
+// (TIP_FREEZE_SLACK, TIP_FORCE_BREAKDOWN).
+void test_hooks(double tol2, double* freeze2, int* force) {
+  *freeze2 = tol2;
+  *force = 0;
+  if (const char* e = std::getenv("TIP_FORCE_BREAKDOWN")) *force = std::max(0, std::atoi(e));
+  if (const char* e = std::getenv("TIP_FREEZE_SLACK")) {
+    const double f = std::atof(e);
+    if (f > 1.0 && std::isfinite(f)) *freeze2 = tol2 * f * f;
+  }
+}
+
+// The cluster solver's view of a problem whose tables are made.
+ClProblem cluster_problem(const tip_op_s* h, const tip_params* p, int mask, const Geom& geom) {
+  ClProblem pr = h->cl;
+  pr.g = geom;
+  pr.tol2 = p->tol * p->tol;
+  test_hooks(pr.tol2, &pr.freeze2, &pr.force_iter);
+  pr.seed = p->seed;
+  pr.mask = mask;
+  pr.start_frozen = p->tol >= 1.0 ? 1 : 0;
+  pr.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)geom.V, 1 << 20);
+  pr.max_restarts = 8;
+  pr.variational = p->precision == TIP_PREC_MIXED ? 1 : 0;
+  return pr;
+}
+
+// One launch of the cluster solver: jobs [job0, job0 + njobs) with G workgroups each.
+struct ClusterLaunch {
+  int ndim;
+  bool weighted;
+  int G;
+  uint32_t rows, A;              // most rows of a workgroup, widest plane
+  int job0, njobs;
+};
+
+// Runs the launches one after another on st and waits for them.  host holds
+// the tables on their way to the device and the results (out, outi); dev the
+// tables, the exchange words and the vectors.  xout: solutions, or null.
+tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std::vector<ClProblem>& probs,
+                       const std::vector<ClJob>& jobs, const std::vector<ClusterLaunch>& launches, bool skip,
+                       size_t x_bytes, int logB, hipEvent_t ev0, hipEvent_t ev1, double** out, int** outi,
+                       double** xout) {
+  int devid = 0, cus = 0;
+  TIP_HIP(hipGetDevice(&devid));
+  TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, devid));
+  const size_t o_jobs = align256(probs.size() * sizeof(ClProblem));
+  const size_t tab = align256(o_jobs + jobs.size() * sizeof(ClJob));
+  size_t words = 0, ws = 0;
+  auto clusters = [&](const ClusterLaunch& l) { return std::max(1, std::min(l.njobs, cus / l.G)); };
+  auto sum_words = [](const ClusterLaunch& l, int nc) { return (size_t)nc * (4 * (size_t)l.G + 1); };
+  auto halo_words = [](const ClusterLaunch& l, int nc) { return l.G > 1 ? (size_t)nc * l.G * 8 * l.A : size_t(0); };
+  auto ws_rows = [](const ClusterLaunch& l) { return (size_t)cl_lds_rows(l.rows, 0); };
+  for (const ClusterLaunch& l : launches) {
+    const int nc = clusters(l);
+    words = std::max(words, sum_words(l, nc) + halo_words(l, nc));
+    ws = std::max(ws, (size_t)nc * l.G * 2 * ws_rows(l) * sizeof(double));
+  }
+  const size_t o_words = tab + 256, o_ws = align256(o_words + words * 8), o_x = align256(o_ws + ws);
+  if (const hipError_t e_ = dev.ensure(o_x + x_bytes); e_ != hipSuccess)
+    return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of CG vectors failed: %s", o_x + x_bytes, hipGetErrorString(e_));
+  const size_t nj = jobs.size();
+  if (const hipError_t e_ = host.ensure(tab + 64 + nj * (3 * sizeof(double) + 3 * sizeof(int))); e_ != hipSuccess)
+    return fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_));
+  char* hb = (char*)host.p;
+  std::memcpy(hb, probs.data(), probs.size() * sizeof(ClProblem));
+  std::memcpy(hb + o_jobs, jobs.data(), nj * sizeof(ClJob));
+  int* stalled = (int*)(hb + tab);
+  *stalled = 0;
+  *out = (double*)(hb + tab + 64);
+  *outi = (int*)(*out + 3 * nj);
+  char* db = (char*)dev.p;
+  TIP_HIP(hipMemcpyAsync(db, hb, tab, hipMemcpyHostToDevice, st));
+  *xout = x_bytes ? (double*)(db + o_x) : nullptr;
+  if (x_bytes) TIP_HIP(launch_fill(x_bytes / sizeof(double), *xout, 0.0, st));   // lanes past the last right-hand side
+  if (ev0) TIP_HIP(hipEventRecord(ev0, st));
+  for (const ClusterLaunch& l : launches) {
+    const int nc = clusters(l);
+    ClArgs a{};
+    a.probs = (const ClProblem*)db;
+    a.jobs = (const ClJob*)(db + o_jobs) + l.job0;
+    a.njobs = l.njobs;
+    a.G = l.G;
+    a.nclusters = nc;
+    a.logB = logB;
+    a.Amax = l.A;
+    a.queue = (int*)(db + tab);
+    a.sums = (unsigned long long*)(db + o_words);
+    a.halo = a.sums + sum_words(l, nc);
+    a.ws = (double*)(db + o_ws);
+    a.ws_rows = ws_rows(l);
+    a.xout = *xout;
+    a.out = *out + 3 * (size_t)l.job0;
+    a.outi = *outi + 3 * (size_t)l.job0;
+    a.skip = skip ? 1 : 0;
+    a.stalled = stalled;
+    TIP_HIP(launch_cl_reset(a.sums, sum_words(l, nc) + halo_words(l, nc), a.queue, st));
+    TIP_HIP(launch_cluster(l.ndim, a, l.rows, l.weighted, st));
+  }
+  if (ev1) TIP_HIP(hipEventRecord(ev1, st));
+  TIP_HIP(hipStreamSynchronize(st));
+  if (*stalled) return fail(TIP_EDEVICE, "a workgroup waited too long for its cluster");
   return TIP_OK;
 }
 
@@ -1219,20 +1375,23 @@ struct ResidentRun {
     elem = complex_solves(h, p, mask) ? Elem::kComplex : Elem::kReal;
     if (force_elem >= 0) elem = force_elem ? Elem::kComplex : Elem::kReal;
     tip_status s = call_stream(h, p, &st);
-    if (s != TIP_OK) return s;
-    return resident_tables(h, eo, st);
+    if (s != TIP_OK || eo) return s != TIP_OK ? s : resident_tables(h, st);
+    if (!h->cl.npad) {
+      if (const hipError_t e_ = h->cl_tab.ensure(cluster_table_bytes(h)); e_ != hipSuccess)
+        return fail(TIP_ENOMEM, "hipMalloc solver tables: %s", hipGetErrorString(e_));
+      s = cluster_tables(h, (char*)h->cl_tab.p, st);
+    }
+    return s;
   }
 
   template <class Done, class Solved>
   tip_status run(int64_t r0, int64_t r1, int64_t s0, int64_t s1, bool cls, bool need_x, Done&& done,
                  Solved&& solved) {
-    const ResTables& t = h->res[eo];
     const int parts = elem == Elem::kComplex ? 2 : 1;
     const size_t V = geom.V, esz = elem == Elem::kComplex ? 16 : 8;
     int dev = 0, cus = 0;
     TIP_HIP(hipGetDevice(&dev));
     TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const int slots = cus * res_wgs_per_cu(t.n);
     // solutions are kept in blocks of 64 right-hand sides, at most 1 GiB of them
     int logB = 0;
     while (logB < 6 && (int64_t(1) << logB) < r1 - r0) ++logB;
@@ -1243,26 +1402,7 @@ struct ResidentRun {
     }
     const int64_t chunk1 = std::min(chunk, s1 - s0);
     chunk = std::min(chunk, r1 - r0);
-    const int64_t most_sys = chunk * parts + chunk1 * 2;
-    const size_t stride = (size_t)t.npad * (eo ? 4 : 2);
-    const size_t ws_bytes = (size_t)std::min<int64_t>(slots, most_sys) * stride * sizeof(double);
     const size_t x_bytes = need_x ? (((size_t)chunk + (size_t(1) << logB) - 1) >> logB) * (V * esz << logB) : 0;
-    if (const hipError_t e_ = h->vec.ensure(ws_bytes + x_bytes); e_ != hipSuccess)
-      return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of CG vectors failed: %s", ws_bytes + x_bytes,
-                  hipGetErrorString(e_));
-    const size_t nsys_max = (size_t)most_sys;
-    if (const hipError_t e_ = h->host.ensure(nsys_max * (3 * sizeof(double) + 3 * sizeof(int)) + 64); e_ != hipSuccess)
-      return fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_));
-    if (const hipError_t e_ = h->scal.ensure(256); e_ != hipSuccess)
-      return fail(TIP_ENOMEM, "hipMalloc scalars: %s", hipGetErrorString(e_));
-    int max_restarts = 8, force = 0;
-    const double tol2 = p->tol * p->tol;
-    double freeze2 = tol2;
-    if (const char* e = std::getenv("TIP_FORCE_BREAKDOWN")) force = std::max(0, std::atoi(e));
-    if (const char* e = std::getenv("TIP_FREEZE_SLACK")) {
-      const double f = std::atof(e);
-      if (f > 1.0 && std::isfinite(f)) freeze2 = tol2 * f * f;
-    }
     hipEvent_t ev[2] = {nullptr, nullptr};
     if (g_profiling)
       for (int k = 0; k < 2; ++k) {
@@ -1277,41 +1417,14 @@ struct ResidentRun {
     for (int64_t c0 = r0, d0 = s0; (c0 < r1 && !failed[0]) || (d0 < s1 && !failed[1]); c0 += chunk, d0 += chunk1) {
       const int64_t nr = failed[0] ? 0 : std::max<int64_t>(0, std::min(chunk, r1 - c0));
       const int64_t ns = failed[1] ? 0 : std::max<int64_t>(0, std::min(chunk1, s1 - d0));
-      ResArgs a{};
-      a.g = geom;
-      a.t = t;
-      a.seed = p->seed;
-      a.mask = mask;
-      a.parts = parts;
-      a.rhs0 = c0;
-      a.rhs1 = d0;
-      a.nsys0 = (int)(nr * parts);
-      a.nsys = a.nsys0 + (int)(ns * 2);
-      a.cls = cls ? 1 : 0;
-      a.start_frozen = p->tol >= 1.0 ? 1 : 0;
-      a.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)V, 1 << 20);
-      a.max_restarts = max_restarts;
-      a.force_iter = force;
-      a.tol2 = tol2;
-      a.freeze2 = freeze2;
-      a.ws = (double*)h->vec.p;
-      a.ws_stride = stride;
-      a.xout = need_x ? (double*)((char*)h->vec.p + ws_bytes) : nullptr;
-      a.logB = logB;
-      a.out = (double*)h->host.p;                      // pinned host memory, written by the kernel
-      a.outi = (int*)(a.out + 3 * nsys_max);
-      a.first_failed = (int*)h->scal.p;
-      TIP_HIP(launch_res_reset(a.first_failed, st));
-      if (need_x && (nr & ((int64_t(1) << logB) - 1)))   // lanes past the last right-hand side
-        TIP_HIP(launch_fill(x_bytes / sizeof(double), a.xout, 0.0, st));
-      if (ev[0]) TIP_HIP(hipEventRecord(ev[0], st));
-      TIP_HIP(launch_resident(a, eo != 0, (unsigned)std::min<int64_t>(a.nsys, slots), st));
-      if (ev[1]) TIP_HIP(hipEventRecord(ev[1], st));
-      if (need_x) {
-        tip_status s = solved(a.xout, logB, (int)nr);
-        if (s != TIP_OK) return s;
-      }
-      TIP_HIP(hipStreamSynchronize(st));
+      const int nsys0 = (int)(nr * parts), nsys = nsys0 + (int)(ns * 2);
+      const double* out = nullptr;
+      const int* outi = nullptr;
+      double* x = nullptr;
+      tip_status s = eo ? run_eo(c0, d0, nsys0, nsys, parts, cls, x_bytes, logB, cus, ev, &out, &outi, &x)
+                        : run_plain(c0, d0, nsys0, nsys, parts, cls, x_bytes, logB, cus, ev, &out, &outi, &x);
+      if (s == TIP_OK && need_x) s = solved(x, logB, (int)nr);
+      if (s != TIP_OK) return s;
       int most = 0;
       for (int64_t l = 0; l < nr + ns; ++l) {
         const int c = l < nr ? 0 : 1, np = c ? 2 : parts;
@@ -1320,9 +1433,9 @@ struct ResidentRun {
         ResidentResult r{kAccepted, 0, 0, 0.0, 0.0};
         double rt2 = 0.0, bn2 = 0.0;
         for (int k = 0; k < np; ++k) {
-          const size_t sys = (size_t)((c ? a.nsys0 : 0) + i * np + k);
-          const double* o = a.out + 3 * sys;
-          const int* oi = a.outi + 3 * sys;
+          const size_t sys = (size_t)((c ? nsys0 : 0) + i * np + k);
+          const double* o = out + 3 * sys;
+          const int* oi = outi + 3 * sys;
           if (r.state == kAccepted) r.state = oi[0];
           r.iters = std::max(r.iters, oi[1]);
           r.restarts = std::max(r.restarts, oi[2]);
@@ -1339,8 +1452,9 @@ struct ResidentRun {
       // a launch is one block of right-hand sides: an operator application per iteration of its longest solve
       ++launches;
       matvecs += most;
-      const double table = (double)(eo ? 2 : 1) * t.n * ((eo ? 0.0 : 4.0 * geom.ndim) + (t.wgt ? 16.0 * geom.ndim : 0.0) + 12.0);
-      bytes += table + 8.0 * 5 * (double)a.nsys;
+      const double nd = geom.ndim, w = h->has_coupling ? 16.0 * nd : 0.0;
+      const double table = (double)V * (eo ? w + 20.0 : w + 4.0 * nd + 8.0);
+      bytes += table + 8.0 * 5 * (double)nsys;
       op_bytes += table;
       if (ev[0]) {
         float ms = 0.f;
@@ -1349,6 +1463,81 @@ struct ResidentRun {
       }
     }
     return TIP_OK;
+  }
+
+  // Systems 0 .. nsys - 1 of a chunk (the first nsys0 from right-hand side c0
+  // on, the others of class 1 from d0 on), solved when it returns.
+  tip_status run_eo(int64_t c0, int64_t d0, int nsys0, int nsys, int parts, bool cls, size_t x_bytes, int logB, int cus,
+                    hipEvent_t* ev, const double** out, const int** outi, double** x) {
+    const ResTables& t = h->res;
+    const size_t slots = (size_t)std::min(nsys, cus * res_wgs_per_cu(t.n));
+    const size_t stride = (size_t)t.npad * 4, ws_bytes = slots * stride * sizeof(double);
+    if (const hipError_t e_ = h->vec.ensure(ws_bytes + x_bytes); e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of CG vectors failed: %s", ws_bytes + x_bytes,
+                  hipGetErrorString(e_));
+    if (const hipError_t e_ = h->host.ensure((size_t)nsys * (3 * sizeof(double) + 3 * sizeof(int)) + 64);
+        e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_));
+    if (const hipError_t e_ = h->scal.ensure(256); e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipMalloc scalars: %s", hipGetErrorString(e_));
+    ResArgs a{};
+    a.g = geom;
+    a.t = t;
+    a.seed = p->seed;
+    a.mask = mask;
+    a.parts = parts;
+    a.rhs0 = c0;
+    a.rhs1 = d0;
+    a.nsys0 = nsys0;
+    a.nsys = nsys;
+    a.cls = cls ? 1 : 0;
+    a.start_frozen = p->tol >= 1.0 ? 1 : 0;
+    a.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)geom.V, 1 << 20);
+    a.max_restarts = 8;
+    a.tol2 = p->tol * p->tol;
+    test_hooks(a.tol2, &a.freeze2, &a.force_iter);
+    a.ws = (double*)h->vec.p;
+    a.ws_stride = stride;
+    a.xout = x_bytes ? (double*)((char*)h->vec.p + ws_bytes) : nullptr;
+    a.logB = logB;
+    a.out = (double*)h->host.p;                        // pinned host memory, written by the kernel
+    a.outi = (int*)(a.out + 3 * (size_t)nsys);
+    a.first_failed = (int*)h->scal.p;
+    TIP_HIP(launch_res_reset(a.first_failed, st));
+    if (x_bytes) TIP_HIP(launch_fill(x_bytes / sizeof(double), a.xout, 0.0, st));   // lanes past the last right-hand side
+    if (ev[0]) TIP_HIP(hipEventRecord(ev[0], st));
+    TIP_HIP(launch_resident(a, (unsigned)slots, st));
+    if (ev[1]) TIP_HIP(hipEventRecord(ev[1], st));
+    TIP_HIP(hipStreamSynchronize(st));
+    *out = a.out;
+    *outi = a.outi;
+    *x = a.xout;
+    return TIP_OK;
+  }
+
+  tip_status run_plain(int64_t c0, int64_t d0, int nsys0, int nsys, int parts, bool cls, size_t x_bytes, int logB,
+                       int cus, hipEvent_t* ev, const double** out, const int** outi, double** x) {
+    const std::vector<ClProblem> probs{cluster_problem(h, p, mask, geom)};
+    std::vector<ClJob> jobs((size_t)nsys);
+    Geom cg = geom;
+    cg.cls_gamma = cls ? (int32_t)geom.gamma : 0;
+    cg.cls_nbc = cls ? (int32_t)(1u << geom.LB) : 0;
+    for (int i = 0; i < nsys; ++i) {
+      const int c = i >= nsys0 ? 1 : 0, l = i - (c ? nsys0 : 0), np = c ? 2 : parts;
+      cg.cls_j3 = c;
+      const int64_t j = l / np;
+      const int64_t lane = (((j >> logB) * (int64_t)geom.V) << logB) + (j & ((int64_t(1) << logB) - 1));
+      jobs[(size_t)i] = ClJob{0, l % np, np, (int64_t)class_probe((uint64_t)((c ? d0 : c0) + j), cg), lane * np + l % np};
+    }
+    const ClusterCut cut(geom);
+    const int G = cut.pick(nsys, cus);
+    const std::vector<ClusterLaunch> launches{{geom.ndim, h->has_coupling, G, cut.rows(G), cut.A, 0, nsys}};
+    double* o = nullptr;
+    int* oi = nullptr;
+    tip_status s = run_cluster(h->vec, h->host, st, probs, jobs, launches, true, x_bytes, logB, ev[0], ev[1], &o, &oi, x);
+    *out = o;
+    *outi = oi;
+    return s;
   }
 
   void fill_stats(tip_stats* stats) const {
@@ -1734,6 +1923,162 @@ struct BatchClass {
   int B;
 };
 
+// The problems marked in `clustered`, through the cluster solver: all their
+// real systems, in one launch per dimension, presence of couplings and size of
+// cluster, the largest clusters first and the longest solves of a launch first.
+tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>>& hs, const tip_params* params,
+                          const std::vector<int>& masks, const std::vector<char>& clustered, hipStream_t st,
+                          std::vector<RunResult>& results) {
+  struct System {
+    int prob, part, parts;
+    int64_t m;
+    size_t slot;
+  };
+  int cus = 0, devid = 0;
+  TIP_HIP(hipGetDevice(&devid));
+  TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, devid));
+  std::vector<ClProblem> probs(hs.size());
+  std::vector<System> systems;
+  size_t table_bytes = 0;
+  for (size_t i = 0; i < hs.size(); ++i)
+    if (clustered[i]) table_bytes += align256(cluster_table_bytes(hs[i].get()));
+  if (!table_bytes) return TIP_OK;
+  DevBuf tables;
+  if (const hipError_t e_ = tables.ensure(table_bytes); e_ != hipSuccess)
+    return fail(TIP_ENOMEM, "hipMalloc solver tables: %s", hipGetErrorString(e_));
+  char* mem = (char*)tables.p;
+  struct Key {                   // problems that share a launch
+    int G, ndim;
+    bool weighted;
+  };
+  std::vector<Key> key(hs.size());
+  for (size_t i = 0; i < hs.size(); ++i) {
+    if (!clustered[i]) continue;
+    tip_op_s* h = hs[i].get();
+    const tip_params& p = params[i];
+    tip_status s = cluster_tables(h, mem, st);
+    if (s != TIP_OK) return s;
+    mem += align256(cluster_table_bytes(h));
+    Geom g = h->geom;
+    g.probe = p.probe;
+    g.stop = p.stop_levels;
+    probs[i] = cluster_problem(h, &p, masks[i], g);
+    key[i] = Key{ClusterCut(g).least(), g.ndim, h->has_coupling};
+    const bool split = conj_split(g, h->kind, masks[i], &p, false);
+    const bool cplx = complex_solves(h, &p, masks[i]);
+    const int64_t nbc = int64_t(1) << g.LB;
+    for (int64_t m = p.m_begin; m < p.n_vectors; ++m) {
+      const int64_t j3 = split ? (m % (int64_t)g.gamma) / nbc : 0;
+      if (j3 == 2) continue;                           // the conjugate of its partner
+      const int parts = (split ? j3 == 1 : cplx) ? 2 : 1;
+      for (int k = 0; k < parts; ++k) systems.push_back({(int)i, k, parts, m, (size_t)(m - p.m_begin)});
+    }
+  }
+  // iterations grow with 1 / sqrt(m): systems of one launch in falling order of sites / sqrt(m)
+  std::vector<double> cost(hs.size(), 0.0);
+  for (size_t i = 0; i < hs.size(); ++i)
+    if (clustered[i]) cost[i] = hs[i]->geom.V / std::sqrt(std::max(1e-12, hs[i]->lambda_lb));
+  auto less = [&](const System& a, const System& b) {
+    const Key &x = key[(size_t)a.prob], &y = key[(size_t)b.prob];
+    if (x.G != y.G) return x.G > y.G;
+    if (x.ndim != y.ndim) return x.ndim > y.ndim;
+    if (x.weighted != y.weighted) return x.weighted;
+    if (a.prob != b.prob) {
+      const double ca = cost[(size_t)a.prob], cb = cost[(size_t)b.prob];
+      return ca != cb ? ca > cb : a.prob < b.prob;
+    }
+    return false;
+  };
+  std::stable_sort(systems.begin(), systems.end(), less);
+  std::vector<ClJob> jobs(systems.size());
+  std::vector<ClusterLaunch> launches;
+  for (size_t k = 0; k < systems.size(); ++k) {
+    const System& y = systems[k];
+    const Key& q = key[(size_t)y.prob];
+    jobs[k] = ClJob{y.prob, y.part, y.parts, y.m, 0};
+    if (launches.empty() || launches.back().G != q.G || launches.back().ndim != q.ndim ||
+        launches.back().weighted != q.weighted)
+      launches.push_back(ClusterLaunch{q.ndim, q.weighted, q.G, 0, 0, (int)k, 0});
+    ClusterLaunch& l = launches.back();
+    const ClusterCut c(hs[(size_t)y.prob]->geom);
+    l.rows = std::max(l.rows, c.rows(q.G));
+    l.A = std::max(l.A, c.A);
+    ++l.njobs;
+  }
+  // a launch keeps room for its widest plane and its most rows together
+  for (size_t k = 0; k < launches.size(); ++k) {
+    ClusterLaunch& l = launches[k];
+    if (cl_lds_rows(l.rows, l.A) <= kClLdsRows) continue;
+    // cut off the problem that made it too large: a launch of its own after this one
+    const int last = systems[(size_t)(l.job0 + l.njobs - 1)].prob;
+    int n = 0;
+    while (n < l.njobs && systems[(size_t)(l.job0 + l.njobs - 1 - n)].prob == last) ++n;
+    ClusterLaunch tail = l;
+    tail.job0 = l.job0 + l.njobs - n;
+    tail.njobs = n;
+    l.njobs -= n;
+    for (ClusterLaunch* q : {&l, &tail}) {
+      q->rows = q->A = 0;
+      for (int j = 0; j < q->njobs; ++j) {
+        const ClusterCut c(hs[(size_t)systems[(size_t)(q->job0 + j)].prob]->geom);
+        q->rows = std::max(q->rows, c.rows(q->G));
+        q->A = std::max(q->A, c.A);
+      }
+    }
+    launches.insert(launches.begin() + (ptrdiff_t)k + 1, tail);
+    --k;
+  }
+  DevBuf work;
+  HostPinned host;
+  hipEvent_t ev[2] = {nullptr, nullptr};
+  struct EventDel {
+    hipEvent_t* e;
+    ~EventDel() {
+      for (int k = 0; k < 2; ++k)
+        if (e[k]) (void)hipEventDestroy(e[k]);
+    }
+  } ev_del{ev};
+  if (g_profiling)
+    for (hipEvent_t& e : ev) TIP_HIP(hipEventCreate(&e));
+  double *out = nullptr, *x = nullptr;
+  int* outi = nullptr;
+  tip_status s = run_cluster(work, host, st, probs, jobs, launches, false, 0, 0, ev[0], ev[1], &out, &outi, &x);
+  if (s != TIP_OK) return s;
+  std::vector<double> bn2(0), rt2(0);
+  for (size_t i = 0; i < results.size(); ++i)
+    if (clustered[i]) {
+      RunResult& rr = results[i];
+      rt2.assign(rr.qre.size(), 0.0);
+      bn2.assign(rr.qre.size(), 0.0);
+      for (size_t k = 0; k < systems.size(); ++k) {
+        const System& y = systems[k];
+        if (y.prob != (int)i) continue;
+        const double* o = out + 3 * k;
+        const int* oi = outi + 3 * k;
+        if (y.part == 0 || rr.state[y.slot] == kAccepted) rr.state[y.slot] = oi[0];
+        rr.iters[y.slot] = std::max(rr.iters[y.slot], oi[1]);
+        rr.qre[y.slot] += o[0];
+        rt2[y.slot] += o[1];
+        bn2[y.slot] += o[2];
+        rr.acc.restarts += oi[2];
+      }
+      for (size_t k = 0; k < rt2.size(); ++k) rr.relres[k] = bn2[k] > 0.0 ? std::sqrt(rt2[k] / bn2[k]) : 0.0;
+    }
+  float ms = 0.f;
+  if (ev[0]) TIP_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
+  double bytes = 0.0;
+  for (const System& y : systems)
+    if (y.part == 0) bytes += 8.0 * 5 * y.parts;
+  for (size_t i = 0; i < hs.size(); ++i)
+    if (clustered[i]) bytes += (double)cluster_table_bytes(hs[i].get());
+  for (RunResult& rr : results) {
+    rr.acc.stencil_launches += (int64_t)launches.size();
+    rr.acc.stencil_seconds += ms * 1e-3;
+    rr.acc.stencil_bytes += bytes;
+  }
+  return TIP_OK;
+}
+
 constexpr int kBatchChunk = 8;              // CG iterations per poll of the active counter
 constexpr int kBatchItemSites = 512;        // default sites per work item
 
@@ -1778,9 +2123,23 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
       h->has_links32 = true;
     }
   }
+  // scalar lattices that a cluster of CUs holds are solved there, system by
+  // system; the others in blocks
+  std::vector<RunResult> results;
+  results.reserve((size_t)count);
+  for (int32_t i = 0; i < count; ++i)
+    results.emplace_back((params[i].n_vectors - params[i].m_begin) * hs[(size_t)i]->geom.ncomp);
+  std::vector<char> clustered((size_t)count, 0);
+  for (int32_t i = 0; i < count; ++i) {
+    const Geom& g = hs[(size_t)i]->geom;
+    clustered[(size_t)i] = hs[(size_t)i]->kind == TIP_KIND_SCALAR && g.ndim >= 2 && ClusterCut(g).least() > 0 &&
+                           !env_off("TIP_RESIDENT");
+  }
+  if (const tip_status s = batch_clusters(hs, params, masks, clustered, st, results); s != TIP_OK) return s;
   // classes of right-hand sides
   std::vector<BatchClass> classes;
   for (int32_t i = 0; i < count; ++i) {
+    if (clustered[(size_t)i]) continue;
     const tip_op_s* h = hs[(size_t)i].get();
     const tip_params& p = params[i];
     const Geom& g = h->geom;
@@ -1892,10 +2251,6 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
     group_elems.push_back(off);
   }
   const int L = (int)lane_job.size();
-  std::vector<RunResult> results;
-  results.reserve((size_t)count);
-  for (int32_t i = 0; i < count; ++i)
-    results.emplace_back((params[i].n_vectors - params[i].m_begin) * hs[(size_t)i]->geom.ncomp);
   if (L > 0) {
     // device memory: per group x (FP64) and r, p, w (and x_h in mixed precision)
     // in the working precision; 6 partial rows; the CG scalars; the tables
@@ -2196,9 +2551,9 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
     }
     for (int32_t i = 0; i < count; ++i) {
       tip_stats& a = results[(size_t)i].acc;
-      a.stencil_launches = stencil_launches;
-      a.stencil_seconds = g_profiling ? stencil_seconds : 0.0;
-      a.stencil_bytes = (double)bytes_moved;
+      a.stencil_launches += stencil_launches;
+      a.stencil_seconds += g_profiling ? stencil_seconds : 0.0;
+      a.stencil_bytes += (double)bytes_moved;
     }
   }
   // estimates and stats per problem; conjugate F_3 columns from their partners
@@ -2517,8 +2872,6 @@ tip_status scratch_address(void** out) {
   *out = g_scratch_addr[dev];
   return TIP_OK;
 }
-
-size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 
 }  // namespace
 

@@ -1,0 +1,82 @@
+// Interface of the cluster solver (tip_cluster_kernel.h): CG on the real scalar
+// operator of a whole lattice with any sides, each system solved by G
+// workgroups that keep a slab of it each.  Not part of the public C ABI.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "tip_device.h"
+
+namespace tip {
+
+// One lattice.  Its rows are its sites with the longest dimension moved last;
+// they are cut along it into planes (A sites, nz planes), and a slab is a run
+// of planes.  The tables are indexed by row and padded by kClPad rows.  The
+// longest dimension leaves the smallest planes, so the least halo.
+struct ClProblem {
+  Geom g;                        // with the probe kind of the call
+  const uint32_t* nbr;           // [ndim - 1][npad] distances to the two neighbours along each dimension of the
+                                 // plane: forward in the low half word, backward in the high one, both signed
+  const double2* wgt;            // [ndim][npad] couplings to the two neighbours; null without couplings
+  const double* D;               // [npad] diagonal
+  const uint32_t* site;          // [npad] lattice site of the row
+  size_t npad;
+  double tol2, freeze2;
+  uint64_t seed;
+  int mask, start_frozen, max_iter, max_restarts, force_iter;
+  int variational;               // report b . x + x . r instead of b . x
+  uint32_t A, nz;
+};
+constexpr uint32_t kClPad = 2048;
+
+// One real system: part `part` (0 real, 1 imaginary) of right-hand side m.
+struct ClJob {
+  int prob, part, parts;
+  int64_t m;                     // probe index
+  int64_t x;                     // first element of its solution in xout (step parts << logB per site)
+};
+
+// G workgroups for each of njobs systems; all of them run at the same time.
+struct ClArgs {
+  const ClProblem* probs;
+  const ClJob* jobs;
+  int njobs, G, nclusters, logB;
+  uint32_t Amax;                 // widest plane of the launch
+  double* ws;                    // per workgroup: b, x, ws_rows values each
+  size_t ws_rows;
+  unsigned long long* sums;      // per cluster [2][G][2], then per cluster one job word
+  unsigned long long* halo;      // per workgroup [2][2][2][Amax]
+  double* xout;                  // or null
+  double* out;                   // [njobs][3]: quadrature, ||b - A x||^2, ||b||^2
+  int* outi;                     // [njobs][3]: state, iterations, restarts
+  int* queue;                    // [0] next job, [1] lowest failed job (jobs above it may be skipped)
+  int skip;                      // whether they are
+  int* stalled;                  // host memory: set when a wait ran into its limit
+};
+
+// p with its two halo planes, in 160 KB of LDS beside the sums
+constexpr uint32_t kClLdsRows = 20400;
+constexpr int kClMaxG = 32;
+
+hipError_t launch_cl_tables(const Geom& g, int cut, const double* diag, const double* coupling, size_t npad,
+                            uint32_t* nbr, double2* wgt, double* D, uint32_t* site, hipStream_t st);
+// Clears the exchange words and the queue.
+hipError_t launch_cl_reset(unsigned long long* words, size_t n, int* queue, hipStream_t st);
+// Threads of the kernel that takes `rows` rows per workgroup, and the rows it
+// keeps in LDS for them (whole rounds of its threads).
+int cl_threads(uint32_t rows);
+inline uint32_t cl_lds_rows(uint32_t rows, uint32_t A) {
+  const uint32_t nt = (uint32_t)cl_threads(rows);
+  return 2 * A + (rows + nt - 1) / nt * nt;
+}
+hipError_t launch_cluster_2d(const ClArgs& a, uint32_t rows, bool weighted, hipStream_t st);
+hipError_t launch_cluster_3d(const ClArgs& a, uint32_t rows, bool weighted, hipStream_t st);
+hipError_t launch_cluster_4d(const ClArgs& a, uint32_t rows, bool weighted, hipStream_t st);
+inline hipError_t launch_cluster(int ndim, const ClArgs& a, uint32_t rows, bool weighted, hipStream_t st) {
+  return ndim == 2 ? launch_cluster_2d(a, rows, weighted, st)
+         : ndim == 3 ? launch_cluster_3d(a, rows, weighted, st)
+                     : launch_cluster_4d(a, rows, weighted, st);
+}
+
+}  // namespace tip

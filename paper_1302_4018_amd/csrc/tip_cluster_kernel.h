@@ -1,0 +1,388 @@
+// CG on the real scalar operator of a whole lattice, one system solved by G
+// workgroups, each with a slab of planes of the longest dimension.
+//
+// A workgroup keeps its slab of p and the two planes beside it in LDS and r and
+// A p in registers, and runs the whole solve in one launch.  With G > 1 an
+// iteration exchanges two sums (p^H A p, ||r||^2) and, with the second, the
+// boundary planes of r: a neighbour forms p = r + beta p on its halo planes by
+// itself.  All exchanges go through self-validating words in memory, 3-4 us an
+// iteration; the workgroups of a cluster are resident together by a cooperative
+// launch, and every wait has a limit.
+//
+// Bound, like the resident solver, by the tables each CU reads from L2: 20 ndim
+// + 4 bytes per row and iteration with couplings.  The least G that holds a
+// lattice is used; more only when CUs would idle.  Measured (block solver ->
+// this): 16 uneven 3-D tori, sides 8..48, 1180 systems, 83 -> 25 ms in FP64 and,
+// in place of the single-precision passes, 75 -> 25 ms; 21x34x15, 50 probes,
+// set-up included, 8.6 -> 1.2 ms (2.7 ms with one workgroup per system).
+#pragma once
+
+#include "tip_cluster.h"
+#include "tip_lds_common.h"
+
+namespace tip {
+
+// A word that carries its own validity: 32 bits of payload under a 32-bit tag
+// (the exchange's number).  A reader polls the word itself, so a value needs
+// no flag and no order among stores; relaxed accesses of agent scope, which
+// go past the XCDs' separate L2s, are enough.
+__device__ __forceinline__ void put_word(unsigned long long* w, uint32_t v, uint32_t tag) {
+  __hip_atomic_store(w, ((unsigned long long)tag << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put_double(unsigned long long* w, size_t hi, double v, uint32_t tag) {
+  put_word(w, (uint32_t)__double2loint(v), tag);
+  put_word(w + hi, (uint32_t)__double2hiint(v), tag);
+}
+// Waits for the word's tag, at most kClPolls polls and not past another
+// thread's stall: every wait ends.
+constexpr int kClPolls = 1 << 22;
+__device__ __forceinline__ bool get_word(const unsigned long long* w, uint32_t tag, int* stalled, uint32_t& v) {
+  for (int n = 0; n < kClPolls; ++n) {
+    const unsigned long long x = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v = (uint32_t)x;
+    if ((uint32_t)(x >> 32) == tag) return true;
+    if ((n & 1023) == 1023 && __hip_atomic_load(stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) return false;
+  }
+  __hip_atomic_store(stalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return false;
+}
+// NaN when the wait ran into its limit; the solve then ends as a breakdown.
+__device__ __forceinline__ double get_double(const unsigned long long* w, size_t hi, uint32_t tag, int* stalled) {
+  uint32_t l = 0, h = 0;
+  const bool ok = get_word(w, tag, stalled, l) && get_word(w + hi, tag, stalled, h);
+  return ok ? __hiloint2double((int)h, (int)l) : __longlong_as_double(0x7ff8000000000000ll);
+}
+
+// NT threads, K rows per thread; workgroup b is member b / nclusters of cluster
+// b mod nclusters.  S holds the plane below the slab, the slab, the plane above.
+template <int ND, bool W, int NT, int K>
+__global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
+  constexpr int PF = K >= 16 ? 2 : 3;                 // rows whose table loads run ahead of the arithmetic
+  constexpr bool XREG = K <= 8;                       // x in registers, else in the workgroup's memory
+  double* const S = reinterpret_cast<double*>(tip_dyn_lds);
+  __shared__ double red[2][NT / 64];
+  __shared__ int s_job;
+  const uint32_t tid = threadIdx.x;
+  const int G = a.G, cluster = (int)blockIdx.x % a.nclusters, member = (int)blockIdx.x / a.nclusters;
+  double* const bw = a.ws + (size_t)blockIdx.x * 2 * a.ws_rows;
+  double* const xw = bw + a.ws_rows;
+  unsigned long long* const sums = a.sums + (size_t)cluster * 4 * G;
+  unsigned long long* const jobw = a.sums + (size_t)a.nclusters * 4 * G + cluster;
+  auto halo_of = [&](int mem) {
+    return a.halo + ((size_t)mem * a.nclusters + cluster) * 8 * (size_t)a.Amax;
+  };
+  unsigned long long* const halo_me = halo_of(member);
+  const unsigned long long* const halo_dn = halo_of((member + G - 1) % G);
+  const unsigned long long* const halo_up = halo_of((member + 1) % G);
+  uint32_t sum_tag = 0, halo_tag = 0, job_tag = 0;
+
+  // Sum over the cluster, the same bits in every thread of every workgroup.
+  // Two buffers: nobody is more than one sum ahead of another.
+  auto total = [&](double v, double* buf) {
+    const double mine = wg_total<NT>(v, buf);
+    if (G == 1) return mine;
+    ++sum_tag;
+    unsigned long long* const w = sums + (sum_tag & 1) * 2 * G;
+    if (tid == 0) put_double(w + 2 * member, 1, mine, sum_tag);
+    const int l = (int)(tid & 63);
+    return wave_total(l < G ? get_double(w + 2 * l, 1, sum_tag, a.stalled) : 0.0);
+  };
+
+  for (;;) {
+    // the next system: taken by the cluster's first workgroup
+    ++job_tag;
+    if (tid == 0) {
+      uint32_t j = 0;
+      if (member == 0) {
+        for (;;) {
+          j = (uint32_t)atomicAdd(&a.queue[0], 1);
+          if ((int)j >= a.njobs || !a.skip ||
+              __hip_atomic_load(&a.queue[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (int)j)
+            break;
+          a.outi[3 * (size_t)j] = kPadding;
+        }
+        if (G > 1) put_word(jobw, j, job_tag);
+      } else if (!get_word(jobw, job_tag, a.stalled, j)) {
+        j = (uint32_t)a.njobs;
+      }
+      if (G > 1 && __hip_atomic_load(a.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) j = (uint32_t)a.njobs;
+      s_job = (int)j;
+    }
+    __syncthreads();
+    const int job = __builtin_amdgcn_readfirstlane(s_job);
+    if (job >= a.njobs) return;
+    const ClJob J = a.jobs[job];
+    const ClProblem& pr = a.probs[__builtin_amdgcn_readfirstlane(J.prob)];
+    const uint32_t A = scalar(pr.A);
+    const uint32_t z0 = scalar((uint32_t)member * pr.nz / (uint32_t)G);
+    const uint32_t z1 = scalar((uint32_t)(member + 1) * pr.nz / (uint32_t)G);
+    const uint32_t n = (z1 - z0) * A, s0 = z0 * A;
+    const uint32_t npad = scalar((uint32_t)pr.npad);
+    const uint32_t* const t_nbr = scalar(pr.nbr) + s0;
+    const Double2* const t_wgt = scalar(reinterpret_cast<const Double2*>(pr.wgt)) + s0;
+    const double* const t_D = scalar(pr.D) + s0;
+    double* const P = S + A;                          // the slab
+    auto in = [&](uint32_t e) { return e < n; };
+
+    // fin(k, row, hop sum, diagonal) for the thread's rows, from S.  Rows past
+    // the slab read table rows and LDS words that exist; fin drops them.
+    auto hop = [&](auto&& fin) {
+      const GlobalPtr<uint32_t> nb = opaque(t_nbr);
+      const GlobalPtr<Double2> wg = opaque(t_wgt);
+      const GlobalPtr<double> d = opaque(t_D);
+      uint32_t at = tid;
+      asm volatile("" : "+v"(at));
+      constexpr int NB = PF + 1;
+      uint32_t ix[NB][ND - 1];
+      Double2 wt[NB][ND];
+      double dv[NB];
+      auto load = [&](int k) {
+        if ((uint32_t)(k * NT) >= n) return;
+#pragma unroll
+        for (int mu = 0; mu < ND; ++mu) {
+          const uint32_t row = (uint32_t)mu * npad + (uint32_t)(k * NT);
+          if (mu + 1 < ND) ix[k % NB][mu] = load_row(nb, row, at);
+          if constexpr (W) wt[k % NB][mu] = load_row(wg, row, at);
+        }
+        dv[k % NB] = load_row(d, (uint32_t)(k * NT), at);
+      };
+#pragma unroll
+      for (int k = 0; k < PF; ++k) load(k);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        if ((uint32_t)(k * NT) >= n) break;
+        if (k + PF < K) load(k + PF);
+        asm volatile("" ::: "memory");                // keep the loads where they are
+        double f[ND], b[ND], h = 0.0;
+        const int l = (int)(at + (uint32_t)(k * NT));
+#pragma unroll
+        for (int mu = 0; mu < ND; ++mu) {
+          if (mu + 1 < ND) {
+            const int v = (int)ix[k % NB][mu];
+            f[mu] = P[l + (int)(short)(v & 0xffff)];
+            b[mu] = P[l + (v >> 16)];
+          } else {
+            f[mu] = P[l + (int)A];
+            b[mu] = P[l - (int)A];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);            // all LDS reads of the row in flight together
+#pragma unroll
+        for (int mu = 0; mu < ND; ++mu) {
+          if constexpr (W) {
+            h = fma(wt[k % NB][mu].x, f[mu], h);
+            h = fma(wt[k % NB][mu].y, b[mu], h);
+          } else {
+            h += f[mu];
+            h += b[mu];
+          }
+        }
+        fin(k, at + (uint32_t)(k * NT), h, dv[k % NB]);
+      }
+    };
+    auto rows = [&](auto&& f) {
+      uint32_t at = tid;
+      asm volatile("" : "+v"(at));
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        if ((uint32_t)(k * NT) >= n) break;
+        if (k % 8 == 0) asm volatile("" ::: "memory");
+        f(k, at + (uint32_t)(k * NT));
+      }
+    };
+    auto row_of = [&](auto* v, int k, uint32_t e) -> auto& { return (v + k * NT)[e - (uint32_t)(k * NT)]; };
+
+    // The boundary planes of a vector, one number per plane site and side
+    // (0 the slab's first plane, 1 its last), in one of two buffers: between
+    // two exchanges lies a sum.
+    auto put_halo = [&](int side, uint32_t i, double v) {
+      put_double(halo_me + ((size_t)(halo_tag & 1) * 2 + side) * 2 * a.Amax + i, a.Amax, v, halo_tag);
+    };
+    // f(word of S, neighbour's value) for the words of the two halo planes
+    auto halo_words = [&](auto&& f) {
+      for (uint32_t i = tid; i < 2 * A; i += NT) {
+        const bool up = i >= A;
+        const uint32_t q = up ? i - A : i;
+        double v;
+        if (G == 1) v = up ? P[q] : P[n - A + q];
+        else
+          v = get_double((up ? halo_up : halo_dn) + ((size_t)(halo_tag & 1) * 2 + (up ? 0 : 1)) * 2 * a.Amax + q, a.Amax,
+                         halo_tag, a.stalled);
+        f(up ? P[n + q] : S[q], v);
+      }
+    };
+    // the halo planes of the vector whose slab is in P
+    auto fill_halo = [&]() {
+      __syncthreads();
+      ++halo_tag;
+      if (G > 1)
+        for (uint32_t i = tid; i < A; i += NT) {
+          put_halo(0, i, P[i]);
+          put_halo(1, i, P[n - A + i]);
+        }
+      halo_words([](double& w, double v) { w = v; });
+      __syncthreads();
+    };
+
+    // right-hand side
+    double r[K], t[K], x[XREG ? K : 1];
+    double acc = 0.0;
+    for (uint32_t e = tid; e < n; e += NT) {
+      const double2 v = probe_entry(pr.site[s0 + e], (uint64_t)J.m, 0, pr.g, pr.seed, pr.mask);
+      const double b = J.part ? v.y : v.x;
+      bw[e] = b;
+      P[e] = b;
+      acc = fma(b, b, acc);
+    }
+    const double bnorm2 = total(acc, red[0]);
+    rows([&](int k, uint32_t e) {
+      r[k] = in(e) ? row_of(bw, k, e) : 0.0;
+      if constexpr (XREG) x[k] = 0.0;
+      else if (in(e)) st_nt(&row_of(xw, k, e), 0.0);
+    });
+    fill_halo();
+    double rho = bnorm2;
+    int it = 0, restarts = 0;
+    int state = (pr.start_frozen || bnorm2 == 0.0) ? kFrozen : kActive;
+    double q = 0.0, rt2 = 0.0;
+    for (;;) {
+      while (state == kActive) {
+        acc = 0.0;
+        hop([&](int k, uint32_t e, double h, double d) {
+          const double pk = in(e) ? row_of(P, k, e) : 0.0;
+          t[k] = in(e) ? fma(d, pk, -h) : 0.0;
+          acc = fma(pk, t[k], acc);
+        });
+        const double pAp = total(acc, red[0]);
+        if (!(pAp > 0.0) || !isfinite(pAp) || (pr.force_iter > 0 && restarts == 0 && it + 1 == pr.force_iter)) {
+          state = kBreakdown;
+          break;
+        }
+        const double alpha = rho / pAp;
+        acc = 0.0;
+        ++halo_tag;
+        rows([&](int k, uint32_t e) {
+          r[k] = fma(-alpha, t[k], r[k]);
+          acc = fma(r[k], r[k], acc);
+          // x on its way while the sum is formed
+          if constexpr (!XREG) t[k] = in(e) ? ld_nt(&row_of(xw, k, e)) : 0.0;
+          if (G > 1) {
+            if ((uint32_t)(k * NT) < A && e < A) put_halo(0, e, r[k]);
+            if ((uint32_t)(k * NT + NT) > n - A && in(e) && e >= n - A) put_halo(1, e - (n - A), r[k]);
+          }
+        });
+        const double rho_new = total(acc, red[1]);
+        ++it;
+        if (!isfinite(rho_new)) state = kBreakdown;
+        else if (rho_new <= (restarts == 0 ? pr.freeze2 : pr.tol2) * bnorm2) state = kFrozen;
+        else if (it >= pr.max_iter) state = kNoConv;
+        const double beta = rho_new / rho;
+        rho = rho_new;
+        // x += alpha p; p = r + beta p, on the halo planes from the neighbours' r
+        rows([&](int k, uint32_t e) {
+          const double pk = in(e) ? row_of(P, k, e) : 0.0;
+          if constexpr (XREG) x[k] = fma(alpha, pk, x[k]);
+          else if (in(e)) st_nt(&row_of(xw, k, e), fma(alpha, pk, t[k]));
+          if (in(e)) row_of(P, k, e) = fma(beta, pk, r[k]);
+        });
+        if (G == 1) __syncthreads();
+        if (state == kActive) {
+          if (G == 1) halo_words([](double& w, double v) { w = v; });
+          else halo_words([&](double& w, double v) { w = fma(beta, w, v); });
+        }
+        __syncthreads();
+      }
+      if (state != kFrozen) break;
+      // the FP64 true residual b - A x
+      rows([&](int k, uint32_t e) {
+        double v;
+        if constexpr (XREG) v = x[k];
+        else v = in(e) ? row_of(xw, k, e) : 0.0;
+        if (in(e)) row_of(P, k, e) = v;
+      });
+      fill_halo();
+      double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+      hop([&](int k, uint32_t e, double h, double d) {
+        r[k] = 0.0;
+        if (!in(e)) return;
+        const double xk = row_of(P, k, e), b = row_of(bw, k, e);
+        r[k] = b - fma(d, xk, -h);
+        a0 = fma(r[k], r[k], a0);
+        a1 = fma(b, xk, a1);
+        a2 = fma(xk, r[k], a2);
+      });
+      rt2 = total(a0, red[0]);
+      q = total(pr.variational ? a1 + a2 : a1, red[1]);
+      if (rt2 <= pr.tol2 * bnorm2) {
+        state = kAccepted;
+        break;
+      }
+      if (restarts >= pr.max_restarts || it >= pr.max_iter || !isfinite(rt2)) {
+        state = kNoConv;
+        break;
+      }
+      // restart CG from x: r = p = b - A x
+      state = kActive;
+      ++restarts;
+      rho = rt2;
+      rows([&](int k, uint32_t e) {
+        if (in(e)) row_of(P, k, e) = r[k];
+      });
+      fill_halo();
+    }
+    if (state == kAccepted && a.xout) {
+      if constexpr (XREG)
+        rows([&](int k, uint32_t e) {
+          if (in(e)) row_of(xw, k, e) = x[k];
+        });
+      for (uint32_t e = tid; e < n; e += NT)
+        a.xout[(size_t)J.x + ((size_t)pr.site[s0 + e] << a.logB) * (size_t)J.parts] = xw[e];
+    }
+    if (tid == 0 && member == 0) {
+      if (state != kAccepted) atomicMin(&a.queue[1], job);
+      double* const oo = a.out + 3 * (size_t)job;
+      int* const oi = a.outi + 3 * (size_t)job;
+      oo[0] = q;
+      oo[1] = rt2;
+      oo[2] = bnorm2;
+      oi[0] = state;
+      oi[1] = it;
+      oi[2] = restarts;
+    }
+    __syncthreads();                                  // S, red and s_job are free for the next system
+  }
+}
+
+// Up to 1024 rows four per thread, up to 2048 eight, then 512 threads: two
+// waves per SIMD, whose 256 registers hold two vectors of 40 rows.
+template <int ND, bool W>
+hipError_t launch_cluster_nd(const ClArgs& a, uint32_t rows, hipStream_t st) {
+  const size_t lds = (size_t)cl_lds_rows(rows, a.Amax) * sizeof(double);
+  auto go = [&](auto kernel, int nt) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const unsigned grid = (unsigned)(a.nclusters * a.G);
+    if (a.G == 1) {
+      kernel<<<grid, nt, lds, st>>>(a);
+      return hipGetLastError();
+    }
+    // the workgroups of a cluster wait for one another: all must be resident
+    void* args[] = {const_cast<ClArgs*>(&a)};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(kernel), dim3(grid), dim3((unsigned)nt), args,
+                                      (unsigned)lds, st);
+  };
+  if (rows <= 1024) return go(k_cluster<ND, W, 256, 4>, 256);
+  if (rows <= 2048) return go(k_cluster<ND, W, 256, 8>, 256);
+  if (rows <= 4096) return go(k_cluster<ND, W, 512, 8>, 512);
+  if (rows <= 8192) return go(k_cluster<ND, W, 512, 16>, 512);
+  if (rows <= 20480) return go(k_cluster<ND, W, 512, 40>, 512);
+  return hipErrorInvalidValue;
+}
+
+template <int ND>
+hipError_t launch_cluster_dim(const ClArgs& a, uint32_t rows, bool weighted, hipStream_t st) {
+  return weighted ? launch_cluster_nd<ND, true>(a, rows, st) : launch_cluster_nd<ND, false>(a, rows, st);
+}
+
+}  // namespace tip

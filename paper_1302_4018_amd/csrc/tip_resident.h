@@ -1,6 +1,7 @@
-// Interface of the resident solver (tip_resident_kernel.h): CG on the real
-// scalar operator with one workgroup per right-hand side and the search
-// direction in LDS.  Not part of the public C ABI.
+// Interface of the resident solver (tip_resident_kernel.h): CG on the even-odd
+// system of the real scalar operator (power-of-two sides) with one workgroup
+// per right-hand side and the search direction in LDS.  Not part of the public
+// C ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -10,17 +11,13 @@
 
 namespace tip {
 
-// Per-operator tables, one row per site of the system that CG runs on (the
-// whole lattice, or the sites of one parity p of the even-odd system), padded
-// to npad rows.  On the whole lattice nbr holds the two neighbours of a row
-// along mu as row numbers, forward in the low half word, backward in the high
-// one; padding rows name row n, an LDS word that is kept zero.
+// Per-operator tables, one row per site of one parity P (row e of k_eo_hop's
+// half-lattice numbering), padded to npad rows.
 struct ResTables {
-  const uint32_t* nbr;       // [ndim][npad], whole lattice only
-  const double2* wgt;        // [parities][ndim][npad] w_mu(s), w_mu(s - mu); null without couplings
-  const double* D;           // [parities][npad] diagonal, 0 in padding rows
-  const double* Dinv;        // [parities][npad] its reciprocal
-  const uint32_t* site;      // [parities][npad] lattice site of the row
+  const double2* wgt;        // [2][ndim][npad] w_mu(s), w_mu(s - mu); null without couplings
+  const double* D;           // [2][npad] diagonal, 0 in padding rows
+  const double* Dinv;        // [2][npad] its reciprocal
+  const uint32_t* site;      // [2][npad] lattice site of the row
   uint32_t n, npad;
 };
 
@@ -49,25 +46,23 @@ struct ResArgs {
   int* first_failed;         // lowest system that failed; systems above it may be skipped
 };
 
-constexpr uint32_t kResMaxPlain = 20000;     // rows of 8 bytes: p, the zero word and the sums in 160 KB of LDS
-constexpr uint32_t kResMaxEo = 16384;
+constexpr uint32_t kResMaxRows = 16384;      // 8 bytes each in LDS
 
 // Fills the tables on the device (diag: D(x) then 1 / D(x) on the lattice).
-hipError_t launch_res_tables(const Geom& g, bool eo, const double* diag, const double* coupling, uint32_t n,
-                             uint32_t npad, uint32_t* nbr, double2* wgt, double* D, double* Dinv, uint32_t* site,
-                             hipStream_t st);
+hipError_t launch_res_tables(const Geom& g, const double* diag, const double* coupling, uint32_t n, uint32_t npad,
+                             double2* wgt, double* D, double* Dinv, uint32_t* site, hipStream_t st);
 // Rows the tables are padded to, and workgroups that are resident on one CU.
 inline uint32_t res_npad(uint32_t n) { return (n + 2047u) & ~2047u; }
 int res_wgs_per_cu(uint32_t n);
 // first_failed = no system
 hipError_t launch_res_reset(int* first_failed, hipStream_t st);
-hipError_t launch_resident_2d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st);
-hipError_t launch_resident_3d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st);
-hipError_t launch_resident_4d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st);
-inline hipError_t launch_resident(const ResArgs& a, bool eo, unsigned grid, hipStream_t st) {
-  return a.g.ndim == 2 ? launch_resident_2d(a, eo, grid, st)
-         : a.g.ndim == 3 ? launch_resident_3d(a, eo, grid, st)
-                         : launch_resident_4d(a, eo, grid, st);
+hipError_t launch_resident_2d(const ResArgs& a, unsigned grid, hipStream_t st);
+hipError_t launch_resident_3d(const ResArgs& a, unsigned grid, hipStream_t st);
+hipError_t launch_resident_4d(const ResArgs& a, unsigned grid, hipStream_t st);
+inline hipError_t launch_resident(const ResArgs& a, unsigned grid, hipStream_t st) {
+  return a.g.ndim == 2 ? launch_resident_2d(a, grid, st)
+         : a.g.ndim == 3 ? launch_resident_3d(a, grid, st)
+                         : launch_resident_4d(a, grid, st);
 }
 
 }  // namespace tip

@@ -6,48 +6,33 @@ namespace tip {
 
 // Row e of parity P of the even-odd system is the half-lattice index of
 // k_eo_hop: x + V3 (t >> 1), x the index of all coordinates but the last.
-__global__ __launch_bounds__(kBlock) void k_res_tables(Geom g, int eo, const double* __restrict__ diag,
+__global__ __launch_bounds__(kBlock) void k_res_tables(Geom g, const double* __restrict__ diag,
                                                        const double* __restrict__ w, uint32_t n, uint32_t npad,
-                                                       uint32_t* __restrict__ nbr, double2* __restrict__ wgt,
-                                                       double* __restrict__ D, double* __restrict__ Dinv,
-                                                       uint32_t* __restrict__ site) {
+                                                       double2* __restrict__ wgt, double* __restrict__ D,
+                                                       double* __restrict__ Dinv, uint32_t* __restrict__ site) {
   const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
   const uint32_t P = blockIdx.y;
   if (e >= npad) return;
   const size_t V = g.V, nd = (size_t)g.ndim;
+  const bool pad = e >= n;
   const uint32_t V3 = g.stride[g.ndim - 1];
-  if (e >= n) {
-    site[P * npad + e] = 0u;
-    D[P * npad + e] = 0.0;
-    Dinv[P * npad + e] = 0.0;
-    for (size_t mu = 0; mu < nd; ++mu) {
-      if (!eo) nbr[(P * nd + mu) * npad + e] = n | (n << 16);
-      if (w) wgt[(P * nd + mu) * npad + e] = make_double2(0.0, 0.0);
-    }
-    return;
-  }
-  uint32_t s = e;
-  if (eo) {
-    const uint32_t x3 = e % V3, tau = e / V3;
-    uint32_t sum = P;
-    for (int mu = 0; mu + 1 < g.ndim; ++mu) sum += coord(x3, g, mu);
-    s = x3 + V3 * (2u * tau + (sum & 1u));
-  }
+  const uint32_t x3 = e % V3, tau = e / V3;
+  uint32_t sum = P;
+  for (int mu = 0; mu + 1 < g.ndim; ++mu) sum += coord(x3, g, mu);
+  const uint32_t s = pad ? 0u : x3 + V3 * (2u * tau + (sum & 1u));
   site[P * npad + e] = s;
-  D[P * npad + e] = diag[s];
-  Dinv[P * npad + e] = diag[V + s];
-  for (size_t mu = 0; mu < nd; ++mu) {
-    const uint32_t f = nbr_fwd(s, g, (int)mu), b = nbr_bwd(s, g, (int)mu);
-    if (!eo) nbr[(P * nd + mu) * npad + e] = f | (b << 16);
-    if (w) wgt[(P * nd + mu) * npad + e] = make_double2(w[mu * V + s], w[mu * V + b]);
-  }
+  D[P * npad + e] = pad ? 0.0 : diag[s];
+  Dinv[P * npad + e] = pad ? 0.0 : diag[V + s];
+  if (w)
+    for (size_t mu = 0; mu < nd; ++mu)
+      wgt[(P * nd + mu) * npad + e] =
+          pad ? make_double2(0.0, 0.0) : make_double2(w[mu * V + s], w[mu * V + nbr_bwd(s, g, (int)mu)]);
 }
 
-hipError_t launch_res_tables(const Geom& g, bool eo, const double* diag, const double* coupling, uint32_t n,
-                             uint32_t npad, uint32_t* nbr, double2* wgt, double* D, double* Dinv, uint32_t* site,
-                             hipStream_t st) {
-  const dim3 grid((npad + kBlock - 1) / kBlock, eo ? 2 : 1);
-  k_res_tables<<<grid, kBlock, 0, st>>>(g, eo ? 1 : 0, diag, coupling, n, npad, nbr, wgt, D, Dinv, site);
+hipError_t launch_res_tables(const Geom& g, const double* diag, const double* coupling, uint32_t n, uint32_t npad,
+                             double2* wgt, double* D, double* Dinv, uint32_t* site, hipStream_t st) {
+  const dim3 grid((npad + kBlock - 1) / kBlock, 2);
+  k_res_tables<<<grid, kBlock, 0, st>>>(g, diag, coupling, n, npad, wgt, D, Dinv, site);
   return hipGetLastError();
 }
 

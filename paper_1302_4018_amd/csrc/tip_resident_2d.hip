@@ -3,8 +3,8 @@
 
 namespace tip {
 
-hipError_t launch_resident_2d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st) {
-  return launch_resident_dim<2>(a, eo, grid, st);
+hipError_t launch_resident_2d(const ResArgs& a, unsigned grid, hipStream_t st) {
+  return launch_resident_dim<2>(a, grid, st);
 }
 
 }  // namespace tip

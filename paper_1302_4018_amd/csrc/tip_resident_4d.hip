@@ -3,8 +3,8 @@
 
 namespace tip {
 
-hipError_t launch_resident_4d(const ResArgs& a, bool eo, unsigned grid, hipStream_t st) {
-  return launch_resident_dim<4>(a, eo, grid, st);
+hipError_t launch_resident_4d(const ResArgs& a, unsigned grid, hipStream_t st) {
+  return launch_resident_dim<4>(a, grid, st);
 }
 
 }  // namespace tip

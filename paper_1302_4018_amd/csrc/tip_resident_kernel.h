@@ -1,4 +1,5 @@
-// CG on the real scalar operator with one workgroup per right-hand side.
+// CG on the even-odd system of the real scalar operator (power-of-two sides)
+// with one workgroup per right-hand side.
 //
 // A lattice whose search direction fits in the LDS of one CU needs no launch,
 // no reduction over workgroups and no vector traffic between the passes of an
@@ -8,75 +9,20 @@
 // block solver spends six launches of 3-6 us on an iteration of such a lattice.
 //
 // What bounds it is the operator's tables, read from L2 by every workgroup:
-// on the even-odd system 16 ndim + 8 bytes per row and hop, on the whole
-// lattice 4 ndim more.  At 32^3 with couplings an iteration moves 2.3 MB per CU
-// in 25.6 us: 10 of the 16 lines an XCD's L2 delivers per cycle.  Measured, one
-// call with a prepared operator (block solver -> this): 16^2, 256 probes 2.66
-// -> 0.051 ms; 32^3 with couplings, 512 probes 36.8 -> 3.5 ms; 21x34x15, 50
-// probes (51 systems, a fifth of the chip), operator set-up included, 8.6 -> 2.7
-// ms.  On the way, 32^3: tables hoisted out of the iteration by the compiler and
-// spilled 5.4 ms; their addresses formed from scalars where they are used, x
-// fetched during the sum of ||r||^2 and seven rows of r in LDS 3.9 ms; neighbour
-// rows computed instead of read 3.5 ms.
+// 16 ndim + 8 bytes per row and hop.  At 32^3 with couplings an iteration moves
+// 2.3 MB per CU in 25.6 us: 10 of the 16 lines an XCD's L2 delivers per cycle.
+// Measured, one call with a prepared operator (block solver -> this): 16^2, 256
+// probes 2.66 -> 0.051 ms; 32^3 with couplings, 512 probes 36.8 -> 3.5 ms.  On
+// the way, 32^3: tables hoisted out of the iteration by the compiler and spilled
+// 5.4 ms; their addresses formed from scalars where they are used, x fetched
+// during the sum of ||r||^2 and seven rows of r in LDS 3.9 ms; neighbour rows
+// computed instead of read 3.5 ms.
 #pragma once
 
-#include "tip_kernel_common.h"
+#include "tip_lds_common.h"
 #include "tip_resident.h"
 
 namespace tip {
-
-// Sum over a wave, in every lane: DPP adds inside rows of 16, across them,
-// and the last lane's total read back.  The order is fixed.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
-  return v + __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_total(double v) {
-  v = dpp_add<0x111, 0xf>(v);      // row_shr:1
-  v = dpp_add<0x112, 0xf>(v);      // row_shr:2
-  v = dpp_add<0x114, 0xf>(v);      // row_shr:4
-  v = dpp_add<0x118, 0xf>(v);      // row_shr:8
-  v = dpp_add<0x142, 0xa>(v);      // row_bcast:15
-  v = dpp_add<0x143, 0xc>(v);      // row_bcast:31
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
-                          __builtin_amdgcn_readlane(__double2loint(v), 63));
-}
-
-// Sum over the workgroup, in every thread, with one barrier.  red is not
-// written again before another barrier has passed (the callers alternate).
-template <int NT>
-__device__ __forceinline__ double wg_total(double v, double* red /* [NT / 64] */) {
-  v = wave_total(v);
-  if constexpr (NT == 64) return v;
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) s += red[w];
-  return s;
-}
-
-// A uniform pointer whose value the compiler cannot carry out of a loop: the
-// addresses of a thread's rows are then formed where they are used, instead of
-// being kept in registers for the whole solve.  It stays a pointer to global
-// memory, so its loads count with the vector memory's own counter.
-template <class T>
-using GlobalPtr = const T __attribute__((address_space(1)))*;
-typedef double Double2 __attribute__((ext_vector_type(2)));
-template <class T>
-__device__ __forceinline__ GlobalPtr<T> opaque(const T* p) {
-  asm volatile("" : "+s"(p));
-  return (GlobalPtr<T>)p;
-}
-// p[row + at] with row uniform: a scalar base and a 32-bit byte offset
-template <class T>
-__device__ __forceinline__ T load_row(GlobalPtr<T> p, uint32_t row, uint32_t at) {
-  GlobalPtr<char> base = (GlobalPtr<char>)(p + row);
-  asm("" : "+s"(base));                               // formed with scalar adds
-  return *(GlobalPtr<T>)(base + at * (uint32_t)sizeof(T));
-}
 
 // Probe of right-hand side i of F_3 class j3 (class_probe with the class a
 // value of the right-hand side).
@@ -87,66 +33,40 @@ __device__ __forceinline__ uint64_t res_class_probe(uint64_t i, uint32_t j3, con
 
 // NT threads, K rows per thread: thread t owns rows t, t + NT, ...  FULL: the
 // system has exactly NT K rows, so no row is tested.
-template <int ND, bool EO, bool W, int NT, int K, bool FULL>
+template <int ND, bool W, int NT, int K, bool FULL>
 __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
   constexpr bool HOIST = K <= 4;                      // the thread's table rows stay in registers for the whole solve
-  constexpr int PF = K >= 32 && EO ? 2 : (K >= 16 ? 2 : 3); // else rows whose table loads run ahead of the arithmetic
+  constexpr int PF = K >= 16 ? 2 : 3;                  // else rows whose table loads run ahead of the arithmetic
   constexpr bool XREG = K <= 8;                       // x in registers, else in the workgroup's memory
-  constexpr int RL = EO && K >= 32 ? 7 : 0;           // rows of r in the LDS that p leaves free (28 KB)
+  constexpr int RL = K >= 32 ? 7 : 0;                 // rows of r in the LDS that p leaves free (28 KB)
   double* S = reinterpret_cast<double*>(tip_dyn_lds);
   __shared__ double red[2][NT / 64];
   const uint32_t tid = threadIdx.x;
   const uint32_t n = FULL ? (uint32_t)(NT * K) : a.t.n;
   const uint32_t npad = FULL ? (uint32_t)((NT * K + 2047) & ~2047) : a.t.npad;
   double* const be = a.ws + (size_t)blockIdx.x * a.ws_stride;
-  double* const bo = be + npad;                       // EO only
-  double* const xe = be + (EO ? 2 : 1) * (size_t)npad;
-  double* const xo = xe + npad;                       // EO only
+  double* const bo = be + npad;
+  double* const xe = be + 2 * (size_t)npad;
+  double* const xo = xe + npad;
 
-  static_assert(!EO || FULL || K == 1, "an even-odd system of 64 rows or more is a power of two: FULL");
+  static_assert(FULL || K == 1, "a system of 64 rows or more is a power of two: FULL");
   auto in = [&](uint32_t e) { return FULL || e < n; };
-  // Neighbours of row e of parity P in the other parity's system (all sides
-  // powers of two): along the last dimension slices tau + delta and
-  // tau - 1 + delta, delta the parity of P and the other coordinates.
-  // Computed, not read: 12 of 68 bytes per row and hop in three dimensions, and
-  // the LDS reads would wait for them.
-  auto eo_nbr = [&](int P, uint32_t e, int mu, uint32_t& fwd, uint32_t& bwd) {
-    const uint32_t step = 1u << a.g.shift[mu];
-    if (mu + 1 < ND) {
-      const uint32_t m = ((1u << a.g.logn[mu]) - 1u) << a.g.shift[mu];
-      fwd = (m & (e + step)) | (~m & e);
-      bwd = (m & (e - step)) | (~m & e);
-    } else {
-      uint32_t par = e ^ (uint32_t)P;
-#pragma unroll
-      for (int nu = 1; nu + 1 < ND; ++nu) par ^= e >> a.g.shift[nu];
-      const uint32_t up = e + ((par & 1u) << a.g.shift[mu]);
-      fwd = up & (n - 1u);
-      bwd = (up - step) & (n - 1u);
-    }
-  };
   // fin(k, row, sum_mu [w_mu(s) S(s + mu) + w_mu(s - mu) S(s - mu)], d[row])
   // for the thread's rows of parity P, from the other parity's vector in S
   auto hop = [&](int P, const double* d_, auto&& fin) {
-    const uint32_t* const nb_ = a.t.nbr + (size_t)P * ND * npad;
     const Double2* const wg_ = reinterpret_cast<const Double2*>(a.t.wgt) + (size_t)P * ND * npad;
-    const GlobalPtr<uint32_t> nb = HOIST ? (GlobalPtr<uint32_t>)nb_ : opaque(nb_);
     const GlobalPtr<Double2> wg = HOIST ? (GlobalPtr<Double2>)wg_ : opaque(wg_);
     const GlobalPtr<double> d = HOIST ? (GlobalPtr<double>)d_ : opaque(d_);
     uint32_t at = tid;
     if constexpr (!HOIST) asm volatile("" : "+v"(at));
     constexpr int NB = HOIST ? K : PF + 1;
-    uint32_t ix[NB][ND];
     Double2 wt[NB][ND];
     double dv[NB];
     auto load = [&](int k) {
       if (!FULL && (uint32_t)(k * NT) >= n) return;
 #pragma unroll
-      for (int mu = 0; mu < ND; ++mu) {
-        const uint32_t row = (uint32_t)mu * npad + (uint32_t)(k * NT);       // uniform
-        if constexpr (!EO) ix[k % NB][mu] = load_row(nb, row, at);
-        if constexpr (W) wt[k % NB][mu] = load_row(wg, row, at);
-      }
+      for (int mu = 0; mu < ND; ++mu)
+        if constexpr (W) wt[k % NB][mu] = load_row(wg, (uint32_t)mu * npad + (uint32_t)(k * NT), at);
       dv[k % NB] = load_row(d, (uint32_t)(k * NT), at);
     };
 #pragma unroll
@@ -163,14 +83,11 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
       double f[ND], b[ND], h = 0.0;
 #pragma unroll
       for (int mu = 0; mu < ND; ++mu) {
-        if constexpr (EO) {
-          uint32_t fwd, bwd;
-          // rows past the system read its own words and are zeroed below
-          eo_nbr(P, FULL ? at + (uint32_t)(k * NT) : at & (n - 1u), mu, fwd, bwd);
-          f[mu] = S[fwd], b[mu] = S[bwd];
-        } else {
-          f[mu] = S[ix[k % NB][mu] & 0xffffu], b[mu] = S[ix[k % NB][mu] >> 16];
-        }
+        // computed, not read: 12 of 68 bytes per row and hop in three dimensions, and
+        // the LDS reads would wait for them; rows past the system read its own
+        // words and are zeroed below
+        const EoNeighbours q = eo_neighbours<ND>(a.g, P, FULL ? at + (uint32_t)(k * NT) : at & (n - 1u), n, mu);
+        f[mu] = S[q.fwd], b[mu] = S[q.bwd];
       }
       __builtin_amdgcn_sched_barrier(0);              // all LDS reads of the row in flight together
 #pragma unroll
@@ -183,7 +100,7 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
           h += b[mu];
         }
       }
-      if constexpr (EO && !FULL) h = in(at) ? h : 0.0;   // K = 1 there
+      if constexpr (!FULL) h = in(at) ? h : 0.0;   // K = 1 there
       fin(k, at + (uint32_t)(k * NT), h, dv[k % NB]);
     }
   };
@@ -227,34 +144,25 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
     auto entry = [&](uint32_t s) { return probe_entry(s, m, 0, a.g, a.seed, a.mask); };
     double bn = 0.0;
     for (uint32_t e = tid; e < n; e += NT)
-      for (int P = 0; P < (EO ? 2 : 1); ++P) {
+      for (int P = 0; P < 2; ++P) {
         const double2 v = entry(a.t.site[(size_t)P * npad + e]);
         const double b = part ? v.y : v.x;
         be[(size_t)P * npad + e] = b;
         bn = fma(b, b, bn);
       }
-    if (!FULL && tid == 0) S[n] = 0.0;
     const double bnorm2 = wg_total<NT>(bn, red[0]);
-    double p[EO ? K : 1], t[K], x[XREG ? K : 1];
+    double p[K], t[K], x[XREG ? K : 1];
     double acc = 0.0;
-    if constexpr (EO) {
-      // reduced right-hand side b_e + H_eo D_o^-1 b_o
-      rows([&](int k, uint32_t e) {
-        if (in(e)) S[e] = row_of(I1, k, e) * row_of(bo, k, e);
-      });
-      __syncthreads();
-      hop(0, D0, [&](int k, uint32_t e, double h, double) {
-        p[k] = in(e) ? row_of(be, k, e) + h : 0.0;
-        set_r(k, p[k]);
-        acc = fma(p[k], p[k], acc);
-      });
-    } else {
-      rows([&](int k, uint32_t e) {
-        const double b = in(e) ? row_of(be, k, e) : 0.0;
-        set_r(k, b);
-        acc = fma(b, b, acc);
-      });
-    }
+    // reduced right-hand side b_e + H_eo D_o^-1 b_o
+    rows([&](int k, uint32_t e) {
+      if (in(e)) S[e] = row_of(I1, k, e) * row_of(bo, k, e);
+    });
+    __syncthreads();
+    hop(0, D0, [&](int k, uint32_t e, double h, double) {
+      p[k] = in(e) ? row_of(be, k, e) + h : 0.0;
+      set_r(k, p[k]);
+      acc = fma(p[k], p[k], acc);
+    });
     rows([&](int k, uint32_t e) {
       if constexpr (XREG) x[k] = 0.0;
       else if (in(e)) st_nt(&row_of(xe, k, e), 0.0);
@@ -270,24 +178,16 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
     for (;;) {
       while (state == kActive) {
         acc = 0.0;
-        if constexpr (EO) {
-          hop(1, I1, [&](int k, uint32_t, double h, double d) { t[k] = d * h; });
-          __syncthreads();
-          rows([&](int k, uint32_t e) {
-            if (in(e)) S[e] = t[k];
-          });
-          __syncthreads();
-          hop(0, D0, [&](int k, uint32_t, double h, double d) {
-            t[k] = fma(d, p[k], -h);
-            acc = fma(p[k], t[k], acc);
-          });
-        } else {
-          hop(0, D0, [&](int k, uint32_t e, double h, double d) {
-            const double pk = in(e) ? S[e] : 0.0;
-            t[k] = fma(d, pk, -h);
-            acc = fma(pk, t[k], acc);
-          });
-        }
+        hop(1, I1, [&](int k, uint32_t, double h, double d) { t[k] = d * h; });
+        __syncthreads();
+        rows([&](int k, uint32_t e) {
+          if (in(e)) S[e] = t[k];
+        });
+        __syncthreads();
+        hop(0, D0, [&](int k, uint32_t, double h, double d) {
+          t[k] = fma(d, p[k], -h);
+          acc = fma(p[k], t[k], acc);
+        });
         const double pAp = wg_total<NT>(acc, red[0]);
         if (!(pAp > 0.0) || !isfinite(pAp) || (a.force_iter > 0 && restarts == 0 && it + 1 == a.force_iter)) {
           state = kBreakdown;
@@ -311,14 +211,10 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
         rho = rho_new;
         // x += alpha p; p = r + beta p (the last reads of S lie before the sums)
         rows([&](int k, uint32_t e) {
-          double pk;
-          if constexpr (EO) pk = p[k];
-          else pk = in(e) ? S[e] : 0.0;
-          if constexpr (XREG) x[k] = fma(alpha, pk, x[k]);
-          else if (in(e)) st_nt(&row_of(xe, k, e), fma(alpha, pk, t[k]));
-          const double pn = fma(beta, pk, get_r(k));
-          if constexpr (EO) p[k] = pn;
-          if (in(e)) S[e] = pn;
+          if constexpr (XREG) x[k] = fma(alpha, p[k], x[k]);
+          else if (in(e)) st_nt(&row_of(xe, k, e), fma(alpha, p[k], t[k]));
+          p[k] = fma(beta, p[k], get_r(k));
+          if (in(e)) S[e] = p[k];
         });
         __syncthreads();
       }
@@ -332,32 +228,29 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
       });
       __syncthreads();
       double a0 = 0.0, a1 = 0.0;
-      if constexpr (EO) {
-        // x_o = D_o^-1 (b_o + H_oe x_e) and the odd sites' part, then the even sites' part
-        hop(1, I1, [&](int k, uint32_t e, double h, double d) {
-          t[k] = 0.0;
-          if (!in(e)) return;
-          const double b = row_of(bo, k, e), y = b + h;
-          t[k] = d * y;
-          const double ro = fma(-row_of(D1, k, e), t[k], y);
-          a0 = fma(ro, ro, a0);
-          a1 = fma(b, t[k], a1);
-          if (a.xout) row_of(xo, k, e) = t[k];
-        });
-        __syncthreads();
-        rows([&](int k, uint32_t e) {
-          if constexpr (!XREG) p[k] = in(e) ? S[e] : 0.0;    // x_e
-          if (in(e)) S[e] = t[k];
-        });
-        __syncthreads();
-      }
+      // x_o = D_o^-1 (b_o + H_oe x_e) and the odd sites' part, then the even sites' part
+      hop(1, I1, [&](int k, uint32_t e, double h, double d) {
+        t[k] = 0.0;
+        if (!in(e)) return;
+        const double b = row_of(bo, k, e), y = b + h;
+        t[k] = d * y;
+        const double ro = fma(-row_of(D1, k, e), t[k], y);
+        a0 = fma(ro, ro, a0);
+        a1 = fma(b, t[k], a1);
+        if (a.xout) row_of(xo, k, e) = t[k];
+      });
+      __syncthreads();
+      rows([&](int k, uint32_t e) {
+        if constexpr (!XREG) p[k] = in(e) ? S[e] : 0.0;    // x_e
+        if (in(e)) S[e] = t[k];
+      });
+      __syncthreads();
       hop(0, D0, [&](int k, uint32_t e, double h, double d) {
         double rk = 0.0;
         if (in(e)) {
           double xk;
           if constexpr (XREG) xk = x[k];
-          else if constexpr (EO) xk = p[k];
-          else xk = S[e];
+          else xk = p[k];
           const double b = row_of(be, k, e);
           rk = b - fma(d, xk, -h);
           a0 = fma(rk, rk, a0);
@@ -380,9 +273,8 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
       ++restarts;
       rho = rt2;
       rows([&](int k, uint32_t e) {
-        const double rk = get_r(k);
-        if constexpr (EO) p[k] = rk;
-        if (in(e)) S[e] = rk;
+        p[k] = get_r(k);
+        if (in(e)) S[e] = p[k];
       });
       __syncthreads();
     }
@@ -394,7 +286,7 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
       const int j = local / parts;
       const size_t lane = (((size_t)(j >> a.logB) * a.g.V) << a.logB) + (size_t)(j & ((1 << a.logB) - 1));
       for (uint32_t e = tid; e < n; e += NT)
-        for (int P = 0; P < (EO ? 2 : 1); ++P) {
+        for (int P = 0; P < 2; ++P) {
           const uint32_t s = a.t.site[(size_t)P * npad + e];
           a.xout[(lane + ((size_t)s << a.logB)) * (size_t)parts + (size_t)part] = xe[(size_t)P * npad + e];
         }
@@ -416,11 +308,11 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
 // barrier.  Up to 2048 rows 256 threads with 8 rows each, above that 512
 // threads, two waves per SIMD, whose 256 registers hold the three vectors of
 // 32 rows.
-template <int ND, bool EO, bool W>
+template <int ND, bool W>
 hipError_t launch_resident_nd(const ResArgs& a, unsigned grid, hipStream_t st) {
   const uint32_t n = a.t.n;
   size_t lds = ((size_t)n + 1) * sizeof(double);
-  if (EO && n == 16384) lds += 7 * 512 * sizeof(double);     // rows of r
+  if (n == 16384) lds += 7 * 512 * sizeof(double);           // rows of r
   auto go = [&](auto kernel, int nt) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -428,32 +320,22 @@ hipError_t launch_resident_nd(const ResArgs& a, unsigned grid, hipStream_t st) {
     kernel<<<grid, nt, lds, st>>>(a);
     return hipGetLastError();
   };
-  if constexpr (EO) {                                // a power of two
-    if (n < 64) return go(k_resident<ND, EO, W, 64, 1, false>, 64);
-    if (n == 64) return go(k_resident<ND, EO, W, 64, 1, true>, 64);
-    if (n == 128) return go(k_resident<ND, EO, W, 64, 2, true>, 64);
-    if (n == 256) return go(k_resident<ND, EO, W, 64, 4, true>, 64);
-    if (n == 512) return go(k_resident<ND, EO, W, 256, 2, true>, 256);
-    if (n == 1024) return go(k_resident<ND, EO, W, 256, 4, true>, 256);
-    if (n == 2048) return go(k_resident<ND, EO, W, 256, 8, true>, 256);
-    if (n == 4096) return go(k_resident<ND, EO, W, 512, 8, true>, 512);
-    if (n == 8192) return go(k_resident<ND, EO, W, 512, 16, true>, 512);
-    if (n == 16384) return go(k_resident<ND, EO, W, 512, 32, true>, 512);
-  } else {
-    if (n <= 256) return go(k_resident<ND, EO, W, 64, 4, false>, 64);
-    if (n <= 1024) return go(k_resident<ND, EO, W, 256, 4, false>, 256);
-    if (n <= 2048) return go(k_resident<ND, EO, W, 256, 8, false>, 256);
-    if (n <= 4096) return go(k_resident<ND, EO, W, 512, 8, false>, 512);
-    if (n <= 8192) return go(k_resident<ND, EO, W, 512, 16, false>, 512);
-    if (n <= kResMaxPlain) return go(k_resident<ND, EO, W, 512, 40, false>, 512);
-  }
+  if (n < 64) return go(k_resident<ND, W, 64, 1, false>, 64);
+  if (n == 64) return go(k_resident<ND, W, 64, 1, true>, 64);
+  if (n == 128) return go(k_resident<ND, W, 64, 2, true>, 64);
+  if (n == 256) return go(k_resident<ND, W, 64, 4, true>, 64);
+  if (n == 512) return go(k_resident<ND, W, 256, 2, true>, 256);
+  if (n == 1024) return go(k_resident<ND, W, 256, 4, true>, 256);
+  if (n == 2048) return go(k_resident<ND, W, 256, 8, true>, 256);
+  if (n == 4096) return go(k_resident<ND, W, 512, 8, true>, 512);
+  if (n == 8192) return go(k_resident<ND, W, 512, 16, true>, 512);
+  if (n == 16384) return go(k_resident<ND, W, 512, 32, true>, 512);
   return hipErrorInvalidValue;
 }
 
 template <int ND>
-hipError_t launch_resident_dim(const ResArgs& a, bool eo, unsigned grid, hipStream_t st) {
-  if (eo) return a.t.wgt ? launch_resident_nd<ND, true, true>(a, grid, st) : launch_resident_nd<ND, true, false>(a, grid, st);
-  return a.t.wgt ? launch_resident_nd<ND, false, true>(a, grid, st) : launch_resident_nd<ND, false, false>(a, grid, st);
+hipError_t launch_resident_dim(const ResArgs& a, unsigned grid, hipStream_t st) {
+  return a.t.wgt ? launch_resident_nd<ND, true>(a, grid, st) : launch_resident_nd<ND, false>(a, grid, st);
 }
 
 }  // namespace tip

@@ -1,7 +1,8 @@
-"""The resident solver (one workgroup per right-hand side, direction in LDS) at
-the edges of its row counts, against the oracle: systems of 2 rows to the
-largest, whole lattices just below and above each change of shape, real and
-complex right-hand sides, with and without couplings."""
+"""The solvers that keep a system in LDS (one workgroup per even-odd system, a
+cluster of workgroups per whole lattice) at the edges of their row counts,
+against the oracle: systems of 2 rows to the largest, whole lattices just below
+and above each change of shape, real and complex right-hand sides, with and
+without couplings, clusters of 1 to 32 workgroups."""
 
 import numpy as np
 import pytest
@@ -35,17 +36,37 @@ def test_resident_matches_oracle(dims, mask, weighted):
     n = min(orc.V, 5)
     est, q, st = tip.trace_inv_probe(gop, n, 1e-12, 4018, mask=mask)
     est_o, q_o, _ = oracle_trace(orc, n, 1e-12, 4018, mask)
-    assert st["stencil_launches"] == 1, "not the resident solver"
+    assert st["stencil_launches"] == 1, "not solved in LDS"
     assert st["max_true_relres"] <= 1e-12
     assert np.max(np.abs(est - est_o) / np.abs(est_o)) <= REL
     assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL
 
 
-def test_first_lattice_past_the_limit_uses_the_block_solver():
+@pytest.mark.parametrize("dims", [
+    # clusters of 2, 2, 3, 6 and 8 workgroups at the least, cut along each dimension in turn
+    [3, 59, 113], [150, 9, 16], [30, 47, 31], [9, 101, 101], [48, 48, 48],
+    # and lattices that fewer would hold, split over idle CUs
+    [7, 11, 100], [12000, 1], [6, 5, 90, 3],
+])
+@pytest.mark.parametrize("n,weighted", [(1, True), (4, False)])
+def test_cluster_matches_oracle(dims, n, weighted):
     tip = gpu_binding()
-    gop = tip.Operator([3, 59, 113], 0, mass=0.4)            # 20001 sites
-    _, q, st = tip.trace_inv_probe(gop, 3, 1e-12, 4018)
-    orc = OracleOp([3, 59, 113], 0, mass=0.4)
-    _, q_o, _ = oracle_trace(orc, 3, 1e-12, 4018, MASK_Z2)
+    w = inputs.couplings(dims, seed=902) if weighted else None
+    mf = inputs.mass_field(dims, m0=0.5, seed=903)
+    orc = OracleOp(dims, 0, mass_field=mf, coupling=w)
+    gop = tip.Operator(dims, 0, mass_field=to_dev(mf), coupling=to_dev(w))
+    est, q, st = tip.trace_inv_probe(gop, n, 1e-12, 4018, mask=MASK_Z2)
+    est_o, q_o, _ = oracle_trace(orc, n, 1e-12, 4018, MASK_Z2)
+    assert st["stencil_launches"] == 1 and st["max_true_relres"] <= 1e-12
+    assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL
+    assert np.array_equal(tip.trace_inv_probe(gop, n, 1e-12, 4018, mask=MASK_Z2)[1], q), "not reproducible"
+
+
+def test_lattice_past_every_limit_uses_the_block_solver():
+    tip = gpu_binding()
+    dims = [83, 84, 85]                                      # three planes of 6972 sites do not fit one CU
+    gop = tip.Operator(dims, 0, mass=2.0)
+    _, q, st = tip.trace_inv_probe(gop, 1, 1e-12, 4018)
+    _, q_o, _ = oracle_trace(OracleOp(dims, 0, mass=2.0), 1, 1e-12, 4018, MASK_Z2)
     assert st["stencil_launches"] > 1
     assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL
