@@ -21,9 +21,9 @@
  *   S = D_e - H_eo D_o^-1 H_oe over the even sites (half the vector length,
  *   about half the iterations), then forms x_o = D_o^-1 (b_o + H_oe x_e).  The
  *   acceptance test is the same FP64 true residual of the full system.
- *   Scalar lattices in FP64 whose CG vector fits the LDS of one CU (even-odd
- *   system, V <= 32768) or of up to 32 CUs (other sides, 2 to 4 dimensions) are
- *   solved there, whole solves in one launch, unless the caller fixes rhs_block,
+ *   Lattices in FP64 whose CG vector fits the LDS of one CU (even-odd system, V <=
+ *   32768 scalar, 4096 covariant) or of up to 32 CUs (scalar, other sides), 2 to 4
+ *   dimensions, are solved there, whole solves in one launch, unless the caller fixes rhs_block,
  *   round_tiles or march_tc; stencil_launches then counts these launches and
  *   matvecs the iterations of each launch's longest solve.
  *

@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libtip.so")
-SOURCES = ["tip_kernels.hip", "tip_api.hip", "tip_bandwidth.hip", "tip_batch.hip", "tip_resident.hip",
+SOURCES = ["tip_kernels.hip", "tip_api.hip", "tip_bandwidth.hip", "tip_batch.hip", "tip_resident.hip", "tip_resident_cov.hip",
            "tip_resident_2d.hip", "tip_resident_3d.hip", "tip_resident_4d.hip", "tip_cluster.hip",
            "tip_cluster_2d.hip", "tip_cluster_3d.hip", "tip_cluster_4d.hip"]
 

@@ -1181,16 +1181,18 @@ struct ClusterCut {
 };
 
 // Which system the LDS solvers would run CG on for this call: 1 the even-odd
-// one, 0 the whole lattice, -1 none.  They take the FP64 scalar operator in 2
-// to 4 dimensions with the library's own launch shape; a caller that fixes
+// one, 0 the whole lattice (scalar operator), -1 none.  They run in FP64 in 2 to
+// 4 dimensions with the library's own launch shape; a caller that fixes
 // rhs_block, round_tiles or march_tc gets the block solver those describe.
 int resident_system(const tip_op_s* h, const tip_params* p) {
   const Geom& g = h->geom;
-  if (h->kind != TIP_KIND_SCALAR || p->precision != TIP_PREC_FP64 || g.ndim < 2 || p->rhs_block != 0 ||
-      p->round_tiles != 0 || p->march_tc != 0 || env_off("TIP_RESIDENT"))
+  const bool cov = h->kind == TIP_KIND_COVARIANT;
+  if (p->precision != TIP_PREC_FP64 || g.ndim < 2 || p->rhs_block != 0 || p->round_tiles != 0 || p->march_tc != 0 ||
+      env_off("TIP_RESIDENT"))
     return -1;
-  if (bipartite(g) && h->lambda_lb > 0.0 && !env_off("TIP_EO")) return g.V / 2 <= kResMaxRows ? 1 : -1;
-  return ClusterCut(g).least() > 0 ? 0 : -1;
+  if (bipartite(g) && h->lambda_lb > 0.0 && !env_off("TIP_EO"))
+    return g.V / 2 <= (cov ? kResMaxRowsCov : kResMaxRows) ? 1 : -1;
+  return !cov && ClusterCut(g).least() > 0 ? 0 : -1;
 }
 
 size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
@@ -1352,7 +1354,7 @@ tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std:
 // ([nblk][V][2^logB] of the element type, nb right-hand sides; one class only).
 struct ResidentResult {
   int state, iters, restarts;
-  double q, relres;              // b^H x is real: A is real and symmetric
+  double q, qim, relres;         // b^H x; real for the scalar operator, which is real and symmetric
 };
 struct ResidentRun {
   tip_op_s* h;
@@ -1387,8 +1389,9 @@ struct ResidentRun {
   template <class Done, class Solved>
   tip_status run(int64_t r0, int64_t r1, int64_t s0, int64_t s1, bool cls, bool need_x, Done&& done,
                  Solved&& solved) {
-    const int parts = elem == Elem::kComplex ? 2 : 1;
-    const size_t V = geom.V, esz = elem == Elem::kComplex ? 16 : 8;
+    const bool cov = h->kind == TIP_KIND_COVARIANT;
+    const int parts = elem == Elem::kComplex && !cov ? 2 : 1;      // real systems per right-hand side (covariant: one complex)
+    const size_t V = geom.V, esz = (elem == Elem::kComplex ? 16 : 8) * (size_t)geom.ncomp, os = cov ? 4 : 3;
     int dev = 0, cus = 0;
     TIP_HIP(hipGetDevice(&dev));
     TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1430,12 +1433,13 @@ struct ResidentRun {
         const int c = l < nr ? 0 : 1, np = c ? 2 : parts;
         if (failed[c]) continue;
         const int64_t i = c ? l - nr : l;
-        ResidentResult r{kAccepted, 0, 0, 0.0, 0.0};
+        ResidentResult r{kAccepted, 0, 0, 0.0, 0.0, 0.0};
         double rt2 = 0.0, bn2 = 0.0;
         for (int k = 0; k < np; ++k) {
           const size_t sys = (size_t)((c ? nsys0 : 0) + i * np + k);
-          const double* o = out + 3 * sys;
+          const double* o = out + os * sys;
           const int* oi = outi + 3 * sys;
+          if (cov) r.qim = o[3];
           if (r.state == kAccepted) r.state = oi[0];
           r.iters = std::max(r.iters, oi[1]);
           r.restarts = std::max(r.restarts, oi[2]);
@@ -1453,7 +1457,7 @@ struct ResidentRun {
       ++launches;
       matvecs += most;
       const double nd = geom.ndim, w = h->has_coupling ? 16.0 * nd : 0.0;
-      const double table = (double)V * (eo ? w + 20.0 : w + 4.0 * nd + 8.0);
+      const double table = (double)V * (eo ? w + 20.0 : w + 4.0 * nd + 8.0) + (cov ? 144.0 * nd * (double)V : 0.0);
       bytes += table + 8.0 * 5 * (double)nsys;
       op_bytes += table;
       if (ev[0]) {
@@ -1470,12 +1474,14 @@ struct ResidentRun {
   tip_status run_eo(int64_t c0, int64_t d0, int nsys0, int nsys, int parts, bool cls, size_t x_bytes, int logB, int cus,
                     hipEvent_t* ev, const double** out, const int** outi, double** x) {
     const ResTables& t = h->res;
-    const size_t slots = (size_t)std::min(nsys, cus * res_wgs_per_cu(t.n));
-    const size_t stride = (size_t)t.npad * 4, ws_bytes = slots * stride * sizeof(double);
+    const bool cov = h->kind == TIP_KIND_COVARIANT;
+    const size_t slots = (size_t)std::min(nsys, cus * (cov ? res_cov_wgs_per_cu(t.n) : res_wgs_per_cu(t.n)));
+    const size_t stride = (size_t)t.npad * (cov ? 8 : 4);
+    const size_t ws_bytes = slots * stride * (cov ? sizeof(double2) : sizeof(double)), os = cov ? 4 : 3;
     if (const hipError_t e_ = h->vec.ensure(ws_bytes + x_bytes); e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of CG vectors failed: %s", ws_bytes + x_bytes,
                   hipGetErrorString(e_));
-    if (const hipError_t e_ = h->host.ensure((size_t)nsys * (3 * sizeof(double) + 3 * sizeof(int)) + 64);
+    if (const hipError_t e_ = h->host.ensure((size_t)nsys * (os * sizeof(double) + 3 * sizeof(int)) + 64);
         e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_));
     if (const hipError_t e_ = h->scal.ensure(256); e_ != hipSuccess)
@@ -1501,12 +1507,13 @@ struct ResidentRun {
     a.xout = x_bytes ? (double*)((char*)h->vec.p + ws_bytes) : nullptr;
     a.logB = logB;
     a.out = (double*)h->host.p;                        // pinned host memory, written by the kernel
-    a.outi = (int*)(a.out + 3 * (size_t)nsys);
+    a.outi = (int*)(a.out + os * (size_t)nsys);
+    a.links = cov ? (const double*)h->links_eo.p : nullptr;
     a.first_failed = (int*)h->scal.p;
     TIP_HIP(launch_res_reset(a.first_failed, st));
     if (x_bytes) TIP_HIP(launch_fill(x_bytes / sizeof(double), a.xout, 0.0, st));   // lanes past the last right-hand side
     if (ev[0]) TIP_HIP(hipEventRecord(ev[0], st));
-    TIP_HIP(launch_resident(a, (unsigned)slots, st));
+    TIP_HIP(cov ? launch_resident_cov(a, (unsigned)slots, st) : launch_resident(a, (unsigned)slots, st));
     if (ev[1]) TIP_HIP(hipEventRecord(ev[1], st));
     TIP_HIP(hipStreamSynchronize(st));
     *out = a.out;
@@ -1769,12 +1776,13 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
         [&](int c, int64_t r, const ResidentResult& o) {
           const size_t k = slot(c, r);
           rr.qre[k] = o.q;
+          rr.qim[k] = o.qim;
           rr.state[k] = o.state;
           rr.iters[k] = o.iters;
           rr.relres[k] = o.relres;
         },
         [&](double* x, int logB, int nr) -> tip_status {
-          const size_t step = (V << logB) * (rs.elem == Elem::kComplex ? 2 : 1);
+          const size_t step = (V * (size_t)ncomp << logB) * (rs.elem == Elem::kComplex ? 2 : 1);
           for (int b = 0; b << logB < nr; ++b)
             TIP_HIP(launch_grad_accum(h->dev(), gg, rs.elem, logB, std::min(1 << logB, nr - (b << logB)),
                                       x + (size_t)b * step, grad_mass, grad_coupling, rs.st));
@@ -2645,7 +2653,7 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
     s = rs.setup(h, &one, mask, res, -1);
     if (s == TIP_OK)
       s = rs.run(
-          m, m + 1, 0, 0, false, true, [&](int, int64_t, const ResidentResult& r) { o = r; },
+          m * g.ncomp + comp, m * g.ncomp + comp + 1, 0, 0, false, true, [&](int, int64_t, const ResidentResult& r) { o = r; },
           [&](double* x, int logB, int) -> tip_status {
             TIP_HIP(launch_layout(g, rs.elem, logB, 0, x, x_out, rs.st));
             return TIP_OK;
@@ -2653,7 +2661,7 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
     if (s != TIP_OK) return s;
     if (q_out) {
       q_out[0] = o.q;
-      q_out[1] = 0.0;
+      q_out[1] = o.qim;
     }
     if (stats) {
       std::memset(stats, 0, sizeof *stats);

@@ -37,11 +37,13 @@ struct ResArgs {
   int nsys0, nsys, cls;
   int start_frozen, max_iter, max_restarts, force_iter;
   double tol2, freeze2;
-  double* ws;                // per workgroup: b (per parity), x (per parity), npad values each
-  size_t ws_stride;
+  const double* links;       // covariant: the even-odd link layout [2][ndim][9][n] double2
+  double* ws;                // per workgroup: b (per parity), x (per parity), npad values each (covariant: npad
+                             // and 3 npad complex ones)
+  size_t ws_stride;          // values per workgroup
   double* xout;              // [blocks][V][2^logB][parts] solutions on the lattice, or null
   int logB;
-  double* out;               // [nsys][3]: b . x, ||b - A x||^2, ||b||^2
+  double* out;               // [nsys][3]: b . x, ||b - A x||^2, ||b||^2 (covariant: [nsys][4], Im b^H x last)
   int* outi;                 // [nsys][3]: state, iterations, restarts
   int* first_failed;         // lowest system that failed; systems above it may be skipped
 };
@@ -54,11 +56,14 @@ hipError_t launch_res_tables(const Geom& g, const double* diag, const double* co
 // Rows the tables are padded to, and workgroups that are resident on one CU.
 inline uint32_t res_npad(uint32_t n) { return (n + 2047u) & ~2047u; }
 int res_wgs_per_cu(uint32_t n);
+int res_cov_wgs_per_cu(uint32_t n);
 // first_failed = no system
 hipError_t launch_res_reset(int* first_failed, hipStream_t st);
 hipError_t launch_resident_2d(const ResArgs& a, unsigned grid, hipStream_t st);
 hipError_t launch_resident_3d(const ResArgs& a, unsigned grid, hipStream_t st);
 hipError_t launch_resident_4d(const ResArgs& a, unsigned grid, hipStream_t st);
+constexpr uint32_t kResMaxRowsCov = 2048;    // 48 bytes each
+hipError_t launch_resident_cov(const ResArgs& a, unsigned grid, hipStream_t st);
 inline hipError_t launch_resident(const ResArgs& a, unsigned grid, hipStream_t st) {
   return a.g.ndim == 2 ? launch_resident_2d(a, grid, st)
          : a.g.ndim == 3 ? launch_resident_3d(a, grid, st)

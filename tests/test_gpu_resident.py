@@ -62,6 +62,28 @@ def test_cluster_matches_oracle(dims, n, weighted):
     assert np.array_equal(tip.trace_inv_probe(gop, n, 1e-12, 4018, mask=MASK_Z2)[1], q), "not reproducible"
 
 
+@pytest.mark.parametrize("dims,launches", [
+    # even-odd systems of 2, 8, 32, 64, 128, 256, 512, 1024 and 2048 rows, then one past the limit
+    ([2, 2], 1), ([2, 2, 2, 2], 1), ([8, 8], 1), ([4, 4, 8], 1), ([4, 4, 4, 4], 1), ([8, 8, 8], 1), ([4, 8, 8, 4], 1),
+    ([32, 64], 1), ([8, 8, 8, 8], 1), ([16, 16, 32], 2),
+])
+@pytest.mark.parametrize("weighted", [True, False])
+def test_resident_covariant_matches_oracle(dims, launches, weighted):
+    tip = gpu_binding()
+    w = inputs.couplings(dims, seed=905) if weighted else None
+    mf = inputs.mass_field(dims, m0=0.3, seed=906)
+    U = inputs.haar_links(dims, seed=907)
+    orc = OracleOp(dims, 1, mass_field=mf, coupling=w, links=U)
+    gop = tip.Operator(dims, 1, mass_field=to_dev(mf), coupling=to_dev(w), links=to_dev(U))
+    n = 3
+    est, q, st = tip.trace_inv_probe(gop, n, 1e-12, 4018, mask=MASK_Z4)
+    est_o, q_o, _ = oracle_trace(orc, n, 1e-12, 4018, MASK_Z4)
+    assert (st["stencil_launches"] == 1) == (launches == 1) and st["even_odd"] == 1
+    assert st["max_true_relres"] <= 1e-12
+    assert np.max(np.abs(est - est_o) / np.abs(est_o)) <= REL
+    assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL
+
+
 def test_lattice_past_every_limit_uses_the_block_solver():
     tip = gpu_binding()
     dims = [83, 84, 85]                                      # three planes of 6972 sites do not fit one CU
