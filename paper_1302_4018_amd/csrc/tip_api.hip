@@ -122,40 +122,172 @@ bool bipartite(const Geom& g) {
 // They and the captures take this lock.
 std::mutex g_device_mu;
 
-struct DevBuf {
-  void* p = nullptr;
-  size_t n = 0;
-  ~DevBuf() {
-    if (!p) return;
-    std::lock_guard<std::mutex> lk(g_device_mu);
-    (void)hipFree(p);
+// Device memory, pinned host memory and non-blocking streams that a handle or
+// a call is done with, kept for the next one: a call that builds its own
+// operator spent 0.4-0.8 ms on allocating, freeing and creating them.  What is
+// kept is bounded (kPoolBytes a device, kPoolPinned, kPoolStreams; what has lain
+// longest goes first), nothing is given in that still has work queued on it (the
+// giver has synchronised), and all memory kept is freed when an allocation
+// fails.  One lock for all threads.
+constexpr size_t kPoolBytes = size_t(512) << 20, kPoolBlock = size_t(128) << 20;
+constexpr size_t kPoolPinned = size_t(32) << 20, kPoolPinnedBlock = size_t(8) << 20;
+constexpr size_t kPoolStreams = 16;
+
+class Pool {
+ public:
+  static Pool& get() {
+    static Pool* p = new Pool();                 // lives as long as the process: the runtime may end before static objects
+    return *p;
   }
-  hipError_t ensure(size_t bytes) {
-    if (bytes <= n) return hipSuccess;
+  // at least `bytes`, and what was given in *n
+  hipError_t take(size_t bytes, bool pinned, void** p, size_t* n) {
+    int dev = 0;
+    if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+    if (pinned) dev = -1;
+    size_t want = (bytes + 4095) & ~size_t(4095);
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto best = kept_.end();
+      for (auto it = kept_.begin(); it != kept_.end(); ++it)
+        if (it->dev == dev && it->n >= want && it->n <= 2 * want + (size_t(1) << 16) &&
+            (best == kept_.end() || it->n < best->n))
+          best = it;
+      if (best != kept_.end()) {
+        *p = best->p;
+        *n = best->n;
+        kept_.erase(best);
+        return hipSuccess;
+      }
+    }
     std::lock_guard<std::mutex> lk(g_device_mu);
-    if (p) { (void)hipFree(p); p = nullptr; n = 0; }
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e == hipSuccess) n = bytes;
+    hipError_t e = alloc(want, pinned, p);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      trim();
+      e = alloc(want, pinned, p);
+    }
+    if (e == hipSuccess) *n = want;
     return e;
   }
+  void give(void* p, size_t n, bool pinned) {
+    int dev = -1;
+    bool keep = pinned || hipGetDevice(&dev) == hipSuccess;
+    if (keep && !pinned) {                       // kept under the device that holds it
+      hipPointerAttribute_t at;
+      keep = hipPointerGetAttributes(&at, p) == hipSuccess;
+      if (keep) dev = at.device;
+    }
+    std::vector<Block> out;
+    if (keep && n <= (pinned ? kPoolPinnedBlock : kPoolBlock)) {
+      std::lock_guard<std::mutex> lk(mu_);
+      kept_.push_back({p, n, dev});
+      size_t sum = 0;
+      for (const Block& b : kept_)
+        if (b.dev == dev) sum += b.n;
+      for (auto it = kept_.begin(); sum > (pinned ? kPoolPinned : kPoolBytes);) {
+        if (it->dev != dev) {
+          ++it;
+          continue;
+        }
+        sum -= it->n;
+        out.push_back(*it);
+        it = kept_.erase(it);
+      }
+    } else {
+      out.push_back({p, n, pinned ? -1 : 0});
+    }
+    if (out.empty()) return;
+    std::lock_guard<std::mutex> lk(g_device_mu);
+    for (const Block& b : out) (void)(b.dev < 0 ? hipHostFree(b.p) : hipFree(b.p));
+  }
+  hipStream_t take_stream() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      for (auto it = streams_.begin(); it != streams_.end(); ++it)
+        if (it->dev == dev) {
+          const hipStream_t s = it->s;
+          streams_.erase(it);
+          return s;
+        }
+    }
+    std::lock_guard<std::mutex> lk(g_device_mu);
+    hipStream_t s = nullptr;
+    if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    return s;
+  }
+  void give_stream(hipStream_t s) {
+    int dev = 0;
+    if (hipStreamGetDevice(s, &dev) == hipSuccess) {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (streams_.size() < kPoolStreams) {
+        streams_.push_back({s, dev});
+        return;
+      }
+    }
+    std::lock_guard<std::mutex> lk(g_device_mu);
+    (void)hipStreamDestroy(s);
+  }
+
+ private:
+  struct Block {
+    void* p;
+    size_t n;
+    int dev;                                     // -1: pinned host memory
+  };
+  struct Stream {
+    hipStream_t s;
+    int dev;
+  };
+  static hipError_t alloc(size_t n, bool pinned, void** p) {
+    return pinned ? hipHostMalloc(p, n, hipHostMallocDefault) : hipMalloc(p, n);
+  }
+  void trim() {
+    std::vector<Block> all;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      all.swap(kept_);
+    }
+    for (const Block& b : all) (void)(b.dev < 0 ? hipHostFree(b.p) : hipFree(b.p));
+  }
+  std::mutex mu_;
+  std::vector<Block> kept_;
+  std::vector<Stream> streams_;
 };
 
-struct HostPinned {
+// Memory of a handle or a call, from the pool and back.  Whoever destroys or
+// grows one has synchronised the work that uses it.
+template <bool kPinned>
+struct PoolBuf {
   void* p = nullptr;
   size_t n = 0;
-  ~HostPinned() {
-    if (!p) return;
-    std::lock_guard<std::mutex> lk(g_device_mu);
-    (void)hipHostFree(p);
+  PoolBuf() = default;
+  PoolBuf(const PoolBuf&) = delete;
+  PoolBuf& operator=(const PoolBuf&) = delete;
+  ~PoolBuf() { reset(); }
+  void reset() {
+    if (p) Pool::get().give(p, n, kPinned);
+    p = nullptr;
+    n = 0;
   }
   hipError_t ensure(size_t bytes) {
     if (bytes <= n) return hipSuccess;
-    std::lock_guard<std::mutex> lk(g_device_mu);
-    if (p) { (void)hipHostFree(p); p = nullptr; n = 0; }
-    hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocDefault);
-    if (e == hipSuccess) n = bytes;
-    return e;
+    reset();
+    return Pool::get().take(bytes, kPinned, &p, &n);
   }
+};
+using DevBuf = PoolBuf<false>;
+using HostPinned = PoolBuf<true>;
+
+// Waits for a stream when it goes out of scope, before the buffers declared
+// ahead of it are given back: also after an error that left work queued.
+struct StreamWait {
+  hipStream_t st;
+  ~StreamWait() { (void)hipStreamSynchronize(st); }
 };
 
 }  // namespace
@@ -173,12 +305,15 @@ struct tip_op_s {
   DevBuf links_eo32;           // its single-precision copy, made on first mixed-precision use
   bool has_links_eo = false, has_links_eo32 = false;
   bool has_mass_field = false, has_coupling = false, has_links32 = false;
+  HostPinned low;              // least mass and coupling of each workgroup of launch_lows, until finish_handle reads them
   // lower bound of the spectrum: A = sum_e w_e L_e + diag(m) with L_e PSD, so
   // lambda_min >= min m(x) whenever every w_e >= 0 (NaN when not known)
   double lambda_lb = 0.0;
   // tables of the resident (even-odd) and the cluster (whole lattice) solver, made on first use
   DevBuf res_tab, cl_tab;
   ResTables res{};
+  DevBuf failed;               // the resident solver's first failed system
+  bool res_clean = false;      // it says none
   ClProblem cl{};
   // workspace, grown on demand
   DevBuf vec, partial, scal;
@@ -201,11 +336,12 @@ struct tip_op_s {
                           : (has_links_eo ? (const double*)links_eo.p : nullptr);
     return o;
   }
+  // the caller has synchronised the work of its own streams
   ~tip_op_s() {
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
     if (own_stream) {
-      std::lock_guard<std::mutex> lk(g_device_mu);
-      (void)hipStreamDestroy(own_stream);
+      (void)hipStreamSynchronize(own_stream);
+      Pool::get().give_stream(own_stream);
     }
   }
 };
@@ -223,7 +359,8 @@ tip_status validate_op(const tip_operator* op, Geom* g) {
   return TIP_OK;
 }
 
-tip_status create_handle(const tip_operator* op, hipStream_t st, tip_op_s** out) {
+// The handle's device work is queued on st; finish_handle waits for it.
+tip_status start_handle(const tip_operator* op, hipStream_t st, tip_op_s** out) {
   Geom g;
   tip_status s = validate_op(op, &g);
   if (s != TIP_OK) return s;
@@ -233,7 +370,7 @@ tip_status create_handle(const tip_operator* op, hipStream_t st, tip_op_s** out)
   h->kind = op->kind;
   h->mass = op->mass;
   const size_t V = g.V;
-  auto bail = [&](tip_status code) { delete h; return code; };
+  auto bail = [&](tip_status code) { (void)hipStreamSynchronize(st); delete h; return code; };
   if (op->mass_field) {
     if (const hipError_t e_ = h->mass_field.ensure(V * sizeof(double)); e_ != hipSuccess)
       return bail(fail(TIP_ENOMEM, "hipMalloc mass_field: %s", hipGetErrorString(e_)));
@@ -268,30 +405,44 @@ tip_status create_handle(const tip_operator* op, hipStream_t st, tip_op_s** out)
   if (launch_diag(g, h->has_mass_field ? (const double*)h->mass_field.p : nullptr, op->mass,
                   h->has_coupling ? (const double*)h->coupling.p : nullptr, (double*)h->diag.p, st) != hipSuccess)
     return bail(fail(TIP_EDEVICE, "diagonal launch failed"));
-  if (hipStreamSynchronize(st) != hipSuccess) return bail(fail(TIP_EDEVICE, "operator setup failed on the device"));
-  {
-    double lb = op->mass;
-    if (op->mass_field) {
-      std::vector<double> m(V);
-      hipError_t e;
-      {
-        std::lock_guard<std::mutex> lk(g_device_mu);   // a null-stream copy
-        e = hipMemcpy(m.data(), op->mass_field, V * sizeof(double), hipMemcpyDeviceToHost);
-      }
-      if (e != hipSuccess) return bail(fail(TIP_EDEVICE, "reading mass_field failed"));
-      lb = *std::min_element(m.begin(), m.end());
-    }
-    if (op->coupling) {
-      std::vector<double> w((size_t)g.ndim * V);
-      hipError_t e;
-      {
-        std::lock_guard<std::mutex> lk(g_device_mu);   // a null-stream copy
-        e = hipMemcpy(w.data(), op->coupling, w.size() * sizeof(double), hipMemcpyDeviceToHost);
-      }
-      if (e != hipSuccess) return bail(fail(TIP_EDEVICE, "reading coupling failed"));
-      if (*std::min_element(w.begin(), w.end()) < 0.0) lb = std::nan("");
-    }
-    h->lambda_lb = lb;
+  if (op->mass_field || op->coupling) {
+    if (const hipError_t e_ = h->low.ensure(2 * kLowGroups * sizeof(double)); e_ != hipSuccess)
+      return bail(fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_)));
+    double* low = (double*)h->low.p;
+    if ((op->mass_field && launch_lows(V, (const double*)h->mass_field.p, low, st) != hipSuccess) ||
+        (op->coupling &&
+         launch_lows((size_t)g.ndim * V, (const double*)h->coupling.p, low + kLowGroups, st) != hipSuccess))
+      return bail(fail(TIP_EDEVICE, "spectral bound launch failed"));
+  }
+  *out = h;
+  return TIP_OK;
+}
+
+// Least of launch_lows' values: as std::min_element over the array, NaN when
+// its first entry is (other NaNs compare as not less).
+double least(const double* low) {
+  double v = low[0];
+  for (int k = 1; k < kLowGroups; ++k)
+    if (low[k] < v) v = low[k];
+  return v;
+}
+
+tip_status finish_handle(tip_op_s* h, hipStream_t st) {
+  if (hipStreamSynchronize(st) != hipSuccess) return fail(TIP_EDEVICE, "operator setup failed on the device");
+  const double* low = (const double*)h->low.p;
+  h->lambda_lb = h->has_mass_field ? least(low) : h->mass;
+  if (h->has_coupling && least(low + kLowGroups) < 0.0) h->lambda_lb = std::nan("");
+  return TIP_OK;
+}
+
+tip_status create_handle(const tip_operator* op, hipStream_t st, tip_op_s** out) {
+  tip_op_s* h = nullptr;
+  tip_status s = start_handle(op, st, &h);
+  if (s != TIP_OK) return s;
+  s = finish_handle(h, st);
+  if (s != TIP_OK) {
+    delete h;
+    return s;
   }
   *out = h;
   return TIP_OK;
@@ -518,10 +669,7 @@ tip_status check_params(const tip_op_s* h, const tip_params* p, int* mask_out) {
 tip_status call_stream(tip_op_s* h, const tip_params* p, hipStream_t* out) {
   *out = (hipStream_t)p->stream;
   if (*out || env_off("TIP_GRAPH")) return TIP_OK;
-  if (!h->own_stream) {
-    std::lock_guard<std::mutex> lk(g_device_mu);
-    if (hipStreamCreateWithFlags(&h->own_stream, hipStreamNonBlocking) != hipSuccess) h->own_stream = nullptr;
-  }
+  if (!h->own_stream) h->own_stream = Pool::get().take_stream();
   if (h->own_stream) {
     // work the caller queued on the null stream comes first
     TIP_HIP(hipStreamSynchronize(nullptr));
@@ -1484,7 +1632,7 @@ struct ResidentRun {
     if (const hipError_t e_ = h->host.ensure((size_t)nsys * (os * sizeof(double) + 3 * sizeof(int)) + 64);
         e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_));
-    if (const hipError_t e_ = h->scal.ensure(256); e_ != hipSuccess)
+    if (const hipError_t e_ = h->failed.ensure(sizeof(int)); e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipMalloc scalars: %s", hipGetErrorString(e_));
     ResArgs a{};
     a.g = geom;
@@ -1509,13 +1657,15 @@ struct ResidentRun {
     a.out = (double*)h->host.p;                        // pinned host memory, written by the kernel
     a.outi = (int*)(a.out + os * (size_t)nsys);
     a.links = cov ? (const double*)h->links_eo.p : nullptr;
-    a.first_failed = (int*)h->scal.p;
-    TIP_HIP(launch_res_reset(a.first_failed, st));
+    a.first_failed = (int*)h->failed.p;
+    if (!h->res_clean) TIP_HIP(launch_res_reset(a.first_failed, st));
+    h->res_clean = false;
     if (x_bytes) TIP_HIP(launch_fill(x_bytes / sizeof(double), a.xout, 0.0, st));   // lanes past the last right-hand side
     if (ev[0]) TIP_HIP(hipEventRecord(ev[0], st));
     TIP_HIP(cov ? launch_resident_cov(a, (unsigned)slots, st) : launch_resident(a, (unsigned)slots, st));
     if (ev[1]) TIP_HIP(hipEventRecord(ev[1], st));
     TIP_HIP(hipStreamSynchronize(st));
+    h->res_clean = std::all_of(a.outi, a.outi + 3 * (size_t)nsys, [n = 0](int v) mutable { return n++ % 3 != 0 || v == kAccepted; });
     *out = a.out;
     *outi = a.outi;
     *x = a.xout;
@@ -1951,7 +2101,9 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
   for (size_t i = 0; i < hs.size(); ++i)
     if (clustered[i]) table_bytes += align256(cluster_table_bytes(hs[i].get()));
   if (!table_bytes) return TIP_OK;
-  DevBuf tables;
+  DevBuf tables, work;
+  HostPinned host;
+  const StreamWait wait{st};
   if (const hipError_t e_ = tables.ensure(table_bytes); e_ != hipSuccess)
     return fail(TIP_ENOMEM, "hipMalloc solver tables: %s", hipGetErrorString(e_));
   char* mem = (char*)tables.p;
@@ -2036,8 +2188,6 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
     launches.insert(launches.begin() + (ptrdiff_t)k + 1, tail);
     --k;
   }
-  DevBuf work;
-  HostPinned host;
   hipEvent_t ev[2] = {nullptr, nullptr};
   struct EventDel {
     hipEvent_t* e;
@@ -2099,26 +2249,23 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
     hipStream_t s = nullptr;
     ~OwnStream() {
       if (!s) return;
-      std::lock_guard<std::mutex> lk(g_device_mu);
       (void)hipStreamSynchronize(s);
-      (void)hipStreamDestroy(s);
+      Pool::get().give_stream(s);
     }
   } own;
   if (!st) {
-    {
-      std::lock_guard<std::mutex> lk(g_device_mu);
-      if (hipStreamCreateWithFlags(&own.s, hipStreamNonBlocking) != hipSuccess)
-        return fail(TIP_EDEVICE, "hipStreamCreateWithFlags failed");
-    }
+    own.s = Pool::get().take_stream();
+    if (!own.s) return fail(TIP_EDEVICE, "hipStreamCreateWithFlags failed");
     TIP_HIP(hipStreamSynchronize(nullptr));        // work queued on the null stream comes first
     st = own.s;
   }
   // operators: link repack, diagonal, lower spectral bound; the call's masks
   std::vector<std::unique_ptr<tip_op_s, HandleDel>> hs((size_t)count);
+  const StreamWait hs_wait{st};
   std::vector<int> masks((size_t)count);
   for (int32_t i = 0; i < count; ++i) {
     tip_op_s* h = nullptr;
-    tip_status s = create_handle(&ops[i], st, &h);
+    tip_status s = start_handle(&ops[i], st, &h);
     if (s != TIP_OK) return fail(s, "torus %d: %s", i, g_err.c_str());
     hs[(size_t)i].reset(h);
     s = check_params(h, &params[i], &masks[(size_t)i]);
@@ -2131,6 +2278,9 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
       h->has_links32 = true;
     }
   }
+  for (int32_t i = 0; i < count; ++i)
+    if (const tip_status s = finish_handle(hs[(size_t)i].get(), st); s != TIP_OK)
+      return fail(s, "torus %d: %s", i, g_err.c_str());
   // scalar lattices that a cluster of CUs holds are solved there, system by
   // system; the others in blocks
   std::vector<RunResult> results;
@@ -2283,6 +2433,8 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
     }
     const size_t rowstride = (size_t)L * PI;
     DevBuf vec, part, scal, tab;
+    HostPinned host;
+    const StreamWait work_wait{st};
     if (const hipError_t e_ = vec.ensure(vec_bytes); e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipMalloc of %zu bytes of batch vectors failed: %s", vec_bytes, hipGetErrorString(e_));
     if (const hipError_t e_ = part.ensure(6 * rowstride * sizeof(double)); e_ != hipSuccess)
@@ -2358,7 +2510,6 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
     if (args.bytes) TIP_HIP(hipMemsetAsync(args.bytes, 0, sizeof(unsigned long long), st));
     int live_lanes = 0;
     for (const BatchJob& J : jobs) live_lanes += J.nb;
-    HostPinned host;
     if (const hipError_t e_ = host.ensure((size_t)L * (3 * sizeof(double) + 4 * sizeof(int)) + 256); e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e_));
     int* h_active = (int*)host.p;
@@ -2610,8 +2761,10 @@ tip_status run_apply(const tip_operator* op, const Geom& g, int32_t nrhs, const 
   } else {
     for (int32_t k = 0; k < nrhs; ++k)
       if (hipMemcpyAsync(stage, (const char*)x + k * bytes, bytes, hipMemcpyDeviceToDevice, st) != hipSuccess ||
-          launch(1, stage, (char*)y + k * bytes) != hipSuccess)
+          launch(1, stage, (char*)y + k * bytes) != hipSuccess) {
+        (void)hipStreamSynchronize(st);                  // stage goes when this returns
         return fail(TIP_EDEVICE, "apply launch failed");
+      }
   }
   if (hipStreamSynchronize(st) != hipSuccess) return fail(TIP_EDEVICE, "apply failed on the device");
   return TIP_OK;

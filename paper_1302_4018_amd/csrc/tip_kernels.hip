@@ -1898,6 +1898,29 @@ hipError_t launch_scale(size_t n, double* a, double f, hipStream_t st) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(kWideBlock) void k_lows(size_t n, const double* __restrict__ a, double* __restrict__ low) {
+  __shared__ double lds[kWideBlock / 64];
+  double v = a[0];
+  for (size_t i = (size_t)blockIdx.x * kWideBlock + threadIdx.x; i < n; i += (size_t)kLowGroups * kWideBlock) {
+    const double x = a[i];
+    v = (x < v || v != v) ? x : v;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double x = __shfl_down(v, off, 64);
+    v = (x < v || v != v) ? x : v;
+  }
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < kWideBlock / 64; ++w) v = (lds[w] < v || v != v) ? lds[w] : v;
+  low[blockIdx.x] = blockIdx.x == 0 && a[0] != a[0] ? a[0] : v;
+}
+hipError_t launch_lows(size_t n, const double* a, double* low, hipStream_t st) {
+  k_lows<<<kLowGroups, kWideBlock, 0, st>>>(n, a, low);
+  return hipGetLastError();
+}
+
 hipError_t launch_fill(size_t n, double* a, double v, hipStream_t st) {
   k_fill<<<cdiv(n, kBlock), kBlock, 0, st>>>(n, a, v);
   return hipGetLastError();

@@ -186,6 +186,10 @@ hipError_t launch_eo_scatter_even(const Geom& g, Elem elem, Prec prec, int logB,
 // out [2][V]: D(x), then 1 / D(x)
 hipError_t launch_diag(const Geom& g, const double* mass_field, double mass, const double* w, double* out,
                        hipStream_t st);
+// Least value of a[0 .. n) by workgroup, into kLowGroups doubles of pinned host
+// memory; the first is NaN when a[0] is
+constexpr int kLowGroups = 64;
+hipError_t launch_lows(size_t n, const double* a, double* low, hipStream_t st);
 hipError_t launch_reduce_rho0(const CgScalars& sc, int B, const double* partial, int gx, hipStream_t st);
 hipError_t launch_fill(size_t n, double* a, double v, hipStream_t st);
 hipError_t launch_scalars_init(const CgScalars& sc, int nb, int B, double bnorm2, int start_frozen, hipStream_t st);
