@@ -1309,11 +1309,11 @@ struct ClusterCut {
   }
   uint32_t rows(int G) const { return (nz + (uint32_t)G - 1) / (uint32_t)G * A; }
   bool fits(int G) const {
-    return G <= (int)nz && 2 * (uint64_t)A + rows(G) <= kClLdsRows && cl_lds_rows(rows(G), A) <= kClLdsRows;
+    return G <= (int)nz && rows(G) <= kClMaxRows && A <= kClMaxRows && cl_lds_rows(rows(G), A) <= kClLdsRows;
   }
-  // Fewest workgroups that hold a system, 0 when kClMaxG do not.
+  // Fewest workgroups, a power of two, that hold a system, 0 when kClMaxG do not.
   int least() const {
-    for (int G = 1; G <= kClMaxG; ++G)
+    for (int G = 1; G <= kClMaxG; G *= 2)
       if (fits(G)) return G;
     return 0;
   }
@@ -1416,36 +1416,42 @@ ClProblem cluster_problem(const tip_op_s* h, const tip_params* p, int mask, cons
   return pr;
 }
 
-// One launch of the cluster solver: jobs [job0, job0 + njobs) with G workgroups each.
+// One launch of the cluster solver: packets [packet0, packet0 + npackets), taken by teams of T workgroups.
 struct ClusterLaunch {
   int ndim;
   bool weighted;
-  int G;
+  int T;
   uint32_t rows, A;              // most rows of a workgroup, widest plane
-  int job0, njobs;
+  int packet0, npackets;
 };
 
 // Runs the launches one after another on st and waits for them.  host holds
 // the tables on their way to the device and the results (out, outi); dev the
 // tables, the exchange words and the vectors.  xout: solutions, or null.
 tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std::vector<ClProblem>& probs,
-                       const std::vector<ClJob>& jobs, const std::vector<ClusterLaunch>& launches, bool skip,
+                       const std::vector<ClJob>& jobs, const std::vector<ClPacket>& packets,
+                       const std::vector<ClusterLaunch>& launches, bool skip,
                        size_t x_bytes, int logB, hipEvent_t ev0, hipEvent_t ev1, double** out, int** outi,
                        double** xout) {
   int devid = 0, cus = 0;
   TIP_HIP(hipGetDevice(&devid));
   TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, devid));
   const size_t o_jobs = align256(probs.size() * sizeof(ClProblem));
-  const size_t tab = align256(o_jobs + jobs.size() * sizeof(ClJob));
+  const size_t o_packets = o_jobs + align256(jobs.size() * sizeof(ClJob));
+  const size_t tab = o_packets + align256(packets.size() * sizeof(ClPacket));
   size_t words = 0, ws = 0;
-  auto clusters = [&](const ClusterLaunch& l) { return std::max(1, std::min(l.njobs, cus / l.G)); };
-  auto sum_words = [](const ClusterLaunch& l, int nc) { return (size_t)nc * (4 * (size_t)l.G + 1); };
-  auto halo_words = [](const ClusterLaunch& l, int nc) { return l.G > 1 ? (size_t)nc * l.G * 8 * l.A : size_t(0); };
+  // teams of a launch: one workgroup per CU at most, places spread over the XCDs as cl_place wants them
+  auto teams = [&](const ClusterLaunch& l) {
+    const int step = cl_team_step(l.T), most = std::max(1, cus / l.T / step) * step;
+    return std::min(most, (l.npackets + step - 1) / step * step);
+  };
+  auto team_words = [](const ClusterLaunch& l, int nt) { return (size_t)nt * cl_team_words(l.T); };
+  auto halo_words = [](const ClusterLaunch& l, int nt) { return l.T > 1 ? (size_t)nt * l.T * 8 * l.A : size_t(0); };
   auto ws_rows = [](const ClusterLaunch& l) { return (size_t)cl_lds_rows(l.rows, 0); };
   for (const ClusterLaunch& l : launches) {
-    const int nc = clusters(l);
-    words = std::max(words, sum_words(l, nc) + halo_words(l, nc));
-    ws = std::max(ws, (size_t)nc * l.G * 2 * ws_rows(l) * sizeof(double));
+    const int nt = teams(l);
+    words = std::max(words, team_words(l, nt) + halo_words(l, nt));
+    ws = std::max(ws, (size_t)nt * l.T * ws_rows(l) * sizeof(double));
   }
   const size_t o_words = tab + 256, o_ws = align256(o_words + words * 8), o_x = align256(o_ws + ws);
   if (const hipError_t e_ = dev.ensure(o_x + x_bytes); e_ != hipSuccess)
@@ -1456,6 +1462,7 @@ tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std:
   char* hb = (char*)host.p;
   std::memcpy(hb, probs.data(), probs.size() * sizeof(ClProblem));
   std::memcpy(hb + o_jobs, jobs.data(), nj * sizeof(ClJob));
+  std::memcpy(hb + o_packets, packets.data(), packets.size() * sizeof(ClPacket));
   int* stalled = (int*)(hb + tab);
   *stalled = 0;
   *out = (double*)(hb + tab + 64);
@@ -1466,26 +1473,27 @@ tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std:
   if (x_bytes) TIP_HIP(launch_fill(x_bytes / sizeof(double), *xout, 0.0, st));   // lanes past the last right-hand side
   if (ev0) TIP_HIP(hipEventRecord(ev0, st));
   for (const ClusterLaunch& l : launches) {
-    const int nc = clusters(l);
+    const int nt = teams(l);
     ClArgs a{};
     a.probs = (const ClProblem*)db;
-    a.jobs = (const ClJob*)(db + o_jobs) + l.job0;
-    a.njobs = l.njobs;
-    a.G = l.G;
-    a.nclusters = nc;
+    a.jobs = (const ClJob*)(db + o_jobs);
+    a.packets = (const ClPacket*)(db + o_packets) + l.packet0;
+    a.npackets = l.npackets;
+    a.T = l.T;
+    a.nteams = nt;
     a.logB = logB;
     a.Amax = l.A;
     a.queue = (int*)(db + tab);
-    a.sums = (unsigned long long*)(db + o_words);
-    a.halo = a.sums + sum_words(l, nc);
+    a.words = (unsigned long long*)(db + o_words);
+    a.halo = a.words + team_words(l, nt);
     a.ws = (double*)(db + o_ws);
     a.ws_rows = ws_rows(l);
     a.xout = *xout;
-    a.out = *out + 3 * (size_t)l.job0;
-    a.outi = *outi + 3 * (size_t)l.job0;
+    a.out = *out;
+    a.outi = *outi;
     a.skip = skip ? 1 : 0;
     a.stalled = stalled;
-    TIP_HIP(launch_cl_reset(a.sums, sum_words(l, nc) + halo_words(l, nc), a.queue, st));
+    TIP_HIP(launch_cl_reset(a.words, team_words(l, nt) + halo_words(l, nt), a.queue, st));
     TIP_HIP(launch_cluster(l.ndim, a, l.rows, l.weighted, st));
   }
   if (ev1) TIP_HIP(hipEventRecord(ev1, st));
@@ -1688,10 +1696,13 @@ struct ResidentRun {
     }
     const ClusterCut cut(geom);
     const int G = cut.pick(nsys, cus);
+    std::vector<ClPacket> packets((size_t)nsys);
+    for (int i = 0; i < nsys; ++i) packets[(size_t)i] = ClPacket{i, 1, G};
     const std::vector<ClusterLaunch> launches{{geom.ndim, h->has_coupling, G, cut.rows(G), cut.A, 0, nsys}};
     double* o = nullptr;
     int* oi = nullptr;
-    tip_status s = run_cluster(h->vec, h->host, st, probs, jobs, launches, true, x_bytes, logB, ev[0], ev[1], &o, &oi, x);
+    tip_status s = run_cluster(h->vec, h->host, st, probs, jobs, packets, launches, true, x_bytes, logB, ev[0], ev[1],
+                               &o, &oi, x);
     *out = o;
     *outi = oi;
     return s;
@@ -2082,8 +2093,9 @@ struct BatchClass {
 };
 
 // The problems marked in `clustered`, through the cluster solver: all their
-// real systems, in one launch per dimension, presence of couplings and size of
-// cluster, the largest clusters first and the longest solves of a launch first.
+// real systems, in one launch per dimension and presence of couplings for the
+// lattices that up to four CUs hold (teams of four) and one for larger ones; a
+// launch takes the largest clusters first, and among them the longest solves.
 tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>>& hs, const tip_params* params,
                           const std::vector<int>& masks, const std::vector<char>& clustered, hipStream_t st,
                           std::vector<RunResult>& results) {
@@ -2107,8 +2119,8 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
   if (const hipError_t e_ = tables.ensure(table_bytes); e_ != hipSuccess)
     return fail(TIP_ENOMEM, "hipMalloc solver tables: %s", hipGetErrorString(e_));
   char* mem = (char*)tables.p;
-  struct Key {                   // problems that share a launch
-    int G, ndim;
+  struct Key {
+    int T, G, ndim;              // T, ndim, weighted: problems that share a launch
     bool weighted;
   };
   std::vector<Key> key(hs.size());
@@ -2123,7 +2135,8 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
     g.probe = p.probe;
     g.stop = p.stop_levels;
     probs[i] = cluster_problem(h, &p, masks[i], g);
-    key[i] = Key{ClusterCut(g).least(), g.ndim, h->has_coupling};
+    const int G = ClusterCut(g).least();
+    key[i] = Key{G <= 4 ? 4 : kClMaxG, G, g.ndim, h->has_coupling};
     const bool split = conj_split(g, h->kind, masks[i], &p, false);
     const bool cplx = complex_solves(h, &p, masks[i]);
     const int64_t nbc = int64_t(1) << g.LB;
@@ -2140,9 +2153,10 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
     if (clustered[i]) cost[i] = hs[i]->geom.V / std::sqrt(std::max(1e-12, hs[i]->lambda_lb));
   auto less = [&](const System& a, const System& b) {
     const Key &x = key[(size_t)a.prob], &y = key[(size_t)b.prob];
-    if (x.G != y.G) return x.G > y.G;
+    if (x.T != y.T) return x.T > y.T;
     if (x.ndim != y.ndim) return x.ndim > y.ndim;
     if (x.weighted != y.weighted) return x.weighted;
+    if (x.G != y.G) return x.G > y.G;
     if (a.prob != b.prob) {
       const double ca = cost[(size_t)a.prob], cb = cost[(size_t)b.prob];
       return ca != cb ? ca > cb : a.prob < b.prob;
@@ -2151,42 +2165,28 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
   };
   std::stable_sort(systems.begin(), systems.end(), less);
   std::vector<ClJob> jobs(systems.size());
+  std::vector<ClPacket> packets;
   std::vector<ClusterLaunch> launches;
   for (size_t k = 0; k < systems.size(); ++k) {
     const System& y = systems[k];
     const Key& q = key[(size_t)y.prob];
-    jobs[k] = ClJob{y.prob, y.part, y.parts, y.m, 0};
-    if (launches.empty() || launches.back().G != q.G || launches.back().ndim != q.ndim ||
-        launches.back().weighted != q.weighted)
-      launches.push_back(ClusterLaunch{q.ndim, q.weighted, q.G, 0, 0, (int)k, 0});
-    ClusterLaunch& l = launches.back();
     const ClusterCut c(hs[(size_t)y.prob]->geom);
+    jobs[k] = ClJob{y.prob, y.part, y.parts, y.m, 0};
+    // a launch keeps room for its widest plane and its most rows together
+    const uint32_t rows = launches.empty() ? 0 : std::max(launches.back().rows, c.rows(q.G));
+    const uint32_t A = launches.empty() ? 0 : std::max(launches.back().A, c.A);
+    if (launches.empty() || launches.back().T != q.T || launches.back().ndim != q.ndim ||
+        launches.back().weighted != q.weighted || cl_lds_rows(rows, A) > kClLdsRows)
+      launches.push_back(ClusterLaunch{q.ndim, q.weighted, q.T, c.rows(q.G), c.A, (int)packets.size(), 0});
+    ClusterLaunch& l = launches.back();
     l.rows = std::max(l.rows, c.rows(q.G));
     l.A = std::max(l.A, c.A);
-    ++l.njobs;
-  }
-  // a launch keeps room for its widest plane and its most rows together
-  for (size_t k = 0; k < launches.size(); ++k) {
-    ClusterLaunch& l = launches[k];
-    if (cl_lds_rows(l.rows, l.A) <= kClLdsRows) continue;
-    // cut off the problem that made it too large: a launch of its own after this one
-    const int last = systems[(size_t)(l.job0 + l.njobs - 1)].prob;
-    int n = 0;
-    while (n < l.njobs && systems[(size_t)(l.job0 + l.njobs - 1 - n)].prob == last) ++n;
-    ClusterLaunch tail = l;
-    tail.job0 = l.job0 + l.njobs - n;
-    tail.njobs = n;
-    l.njobs -= n;
-    for (ClusterLaunch* q : {&l, &tail}) {
-      q->rows = q->A = 0;
-      for (int j = 0; j < q->njobs; ++j) {
-        const ClusterCut c(hs[(size_t)systems[(size_t)(q->job0 + j)].prob]->geom);
-        q->rows = std::max(q->rows, c.rows(q->G));
-        q->A = std::max(q->A, c.A);
-      }
+    if (l.npackets > 0 && jobs[(size_t)packets.back().job].prob == y.prob && packets.back().count < q.T / q.G) {
+      ++packets.back().count;
+    } else {
+      packets.push_back(ClPacket{(int)k, 1, q.G});
+      ++l.npackets;
     }
-    launches.insert(launches.begin() + (ptrdiff_t)k + 1, tail);
-    --k;
   }
   hipEvent_t ev[2] = {nullptr, nullptr};
   struct EventDel {
@@ -2200,7 +2200,7 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
     for (hipEvent_t& e : ev) TIP_HIP(hipEventCreate(&e));
   double *out = nullptr, *x = nullptr;
   int* outi = nullptr;
-  tip_status s = run_cluster(work, host, st, probs, jobs, launches, false, 0, 0, ev[0], ev[1], &out, &outi, &x);
+  tip_status s = run_cluster(work, host, st, probs, jobs, packets, launches, false, 0, 0, ev[0], ev[1], &out, &outi, &x);
   if (s != TIP_OK) return s;
   std::vector<double> bn2(0), rt2(0);
   for (size_t i = 0; i < results.size(); ++i)

@@ -37,27 +37,58 @@ struct ClJob {
   int64_t x;                     // first element of its solution in xout (step parts << logB per site)
 };
 
-// G workgroups for each of njobs systems; all of them run at the same time.
+// Systems that a team of T workgroups solves at the same time, T / G of them at
+// most: jobs job, job + 1, .. of one problem, G workgroups each.
+struct ClPacket {
+  int job, count, G;
+};
+
+// The packets of a launch are taken in order by its teams; every workgroup of
+// the launch is resident from start to end.
 struct ClArgs {
   const ClProblem* probs;
   const ClJob* jobs;
-  int njobs, G, nclusters, logB;
+  const ClPacket* packets;
+  int npackets, T, nteams, logB;
   uint32_t Amax;                 // widest plane of the launch
-  double* ws;                    // per workgroup: b, x, ws_rows values each
+  double* ws;                    // per workgroup: b, ws_rows values
   size_t ws_rows;
-  unsigned long long* sums;      // per cluster [2][G][2], then per cluster one job word
+  unsigned long long* words;     // per team: two buffers of T sums and of T pairs of counters, the packet
   unsigned long long* halo;      // per workgroup [2][2][2][Amax]
   double* xout;                  // or null
-  double* out;                   // [njobs][3]: quadrature, ||b - A x||^2, ||b||^2
-  int* outi;                     // [njobs][3]: state, iterations, restarts
-  int* queue;                    // [0] next job, [1] lowest failed job (jobs above it may be skipped)
+  double* out;                   // [jobs][3]: quadrature, ||b - A x||^2, ||b||^2
+  int* outi;                     // [jobs][3]: state, iterations, restarts
+  int* queue;                    // [0] next packet, [1] lowest failed job (packets above it may be skipped)
   int skip;                      // whether they are
   int* stalled;                  // host memory: set when a wait ran into its limit
 };
+__host__ __device__ inline size_t cl_team_words(int T) { return (size_t)T * 8 + 1; }
+
+// Team and place in it of workgroup b.  Workgroups go round robin over the XCDs
+// (b mod 8), each with its own L2: the workgroups in one place of their teams,
+// which read the same slab of a lattice's tables, share 8 / T XCDs, so that an L2
+// holds one slab and not the whole lattice.  (22x36x39 in clusters of two, 128
+// systems: 33.5 us an iteration, 35.7 with every place on every XCD.)  nteams is a
+// multiple of cl_team_step(T).
+__host__ __device__ inline int cl_team_step(int T) { return T >= kNumXcd ? 1 : kNumXcd / T; }
+__host__ __device__ inline void cl_place(int T, int b, int& team, int& mate) {
+  const int xcd = b % kNumXcd, turn = b / kNumXcd;
+  if (T >= kNumXcd) {
+    const int turns = T / kNumXcd;
+    mate = xcd + kNumXcd * (turn % turns);
+    team = turn / turns;
+  } else {
+    const int per = kNumXcd / T;
+    mate = xcd / per;
+    team = turn * per + xcd % per;
+  }
+}
 
 // p with its two halo planes, in 160 KB of LDS beside the sums
-constexpr uint32_t kClLdsRows = 20400;
+constexpr uint32_t kClLdsRows = 20440;
 constexpr int kClMaxG = 32;
+constexpr int kClRows = 30;                  // rows of r, A p and x in the registers of each of 512 threads
+constexpr uint32_t kClMaxRows = kClRows * 512;
 
 hipError_t launch_cl_tables(const Geom& g, int cut, const double* diag, const double* coupling, size_t npad,
                             uint32_t* nbr, double2* wgt, double* D, uint32_t* site, hipStream_t st);

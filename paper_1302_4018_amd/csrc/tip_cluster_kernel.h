@@ -12,9 +12,10 @@
 // Bound, like the resident solver, by the tables each CU reads from L2: 20 ndim
 // + 4 bytes per row and iteration with couplings.  The least G that holds a
 // lattice is used; more only when CUs would idle.  Measured (block solver ->
-// this): 16 uneven 3-D tori, sides 8..48, 1180 systems, 83 -> 25 ms in FP64 and,
-// in place of the single-precision passes, 75 -> 25 ms; 21x34x15, 50 probes,
-// set-up included, 8.6 -> 1.2 ms (2.7 ms with one workgroup per system).
+// this): 16 uneven 3-D tori, sides 8..48, 1180 systems, 86.5 -> 21.9 ms in FP64
+// and, in place of the single-precision passes, 76.9 -> 21.9 ms; 21x34x15, 50
+// probes, set-up included, 8.4 -> 1.03 ms.  An iteration of one system alone
+// takes 8.1 us with 7500 rows and 9.4 with 15000, on a loaded chip 10.5 and 21.4.
 #pragma once
 
 #include "tip_cluster.h"
@@ -46,71 +47,133 @@ __device__ __forceinline__ bool get_word(const unsigned long long* w, uint32_t t
   __hip_atomic_store(stalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   return false;
 }
-// NaN when the wait ran into its limit; the solve then ends as a breakdown.
-__device__ __forceinline__ double get_double(const unsigned long long* w, size_t hi, uint32_t tag, int* stalled) {
-  uint32_t l = 0, h = 0;
-  const bool ok = get_word(w, tag, stalled, l) && get_word(w + hi, tag, stalled, h);
-  return ok ? __hiloint2double((int)h, (int)l) : __longlong_as_double(0x7ff8000000000000ll);
+// M numbers at once, word i at w(i) and w(i) + hi where want(i): every word is
+// asked for before any is waited for, so that M numbers cost one trip to
+// memory, not 2 M.  NaN when the wait ran into its limit; the solve then ends as
+// a breakdown.
+template <int M, class Want, class At>
+__device__ __forceinline__ void get_doubles(size_t hi, uint32_t tag, int* stalled, double (&out)[M], Want&& want,
+                                            At&& w) {
+  bool got[M];
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    got[i] = !want(i);
+    out[i] = 0.0;
+  }
+  for (int n = 0;; ++n) {
+    unsigned long long l[M], h[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+      if (!got[i]) {
+        l[i] = __hip_atomic_load(w(i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        h[i] = __hip_atomic_load(w(i) + hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    bool all = true;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+      if (!got[i]) {
+        got[i] = (uint32_t)(l[i] >> 32) == tag && (uint32_t)(h[i] >> 32) == tag;
+        out[i] = __hiloint2double((int)(uint32_t)h[i], (int)(uint32_t)l[i]);
+        all = all && got[i];
+      }
+    if (all) return;
+    const bool last = n >= kClPolls;
+    if (last) __hip_atomic_store(stalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (last || ((n & 1023) == 1023 && __hip_atomic_load(stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))) {
+#pragma unroll
+      for (int i = 0; i < M; ++i)
+        if (!got[i]) out[i] = __longlong_as_double(0x7ff8000000000000ll);
+      return;
+    }
+  }
 }
 
-// NT threads, K rows per thread; workgroup b is member b / nclusters of cluster
-// b mod nclusters.  S holds the plane below the slab, the slab, the plane above.
+// NT threads, K rows per thread; cl_place gives a workgroup its place in a team.
+// A team takes a packet of systems and splits into clusters of G workgroups, so
+// that lattices of every size share one launch and keep all CUs busy.  S holds
+// the plane below the slab, the slab, the plane above.
 template <int ND, bool W, int NT, int K>
 __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
   constexpr int PF = K >= 16 ? 2 : 3;                 // rows whose table loads run ahead of the arithmetic
-  constexpr bool XREG = K <= 8;                       // x in registers, else in the workgroup's memory
   double* const S = reinterpret_cast<double*>(tip_dyn_lds);
   __shared__ double red[2][NT / 64];
-  __shared__ int s_job;
+  __shared__ uint32_t s_word[3];
   const uint32_t tid = threadIdx.x;
-  const int G = a.G, cluster = (int)blockIdx.x % a.nclusters, member = (int)blockIdx.x / a.nclusters;
-  double* const bw = a.ws + (size_t)blockIdx.x * 2 * a.ws_rows;
-  double* const xw = bw + a.ws_rows;
-  unsigned long long* const sums = a.sums + (size_t)cluster * 4 * G;
-  unsigned long long* const jobw = a.sums + (size_t)a.nclusters * 4 * G + cluster;
-  auto halo_of = [&](int mem) {
-    return a.halo + ((size_t)mem * a.nclusters + cluster) * 8 * (size_t)a.Amax;
-  };
-  unsigned long long* const halo_me = halo_of(member);
-  const unsigned long long* const halo_dn = halo_of((member + G - 1) % G);
-  const unsigned long long* const halo_up = halo_of((member + 1) % G);
-  uint32_t sum_tag = 0, halo_tag = 0, job_tag = 0;
-
-  // Sum over the cluster, the same bits in every thread of every workgroup.
-  // Two buffers: nobody is more than one sum ahead of another.
-  auto total = [&](double v, double* buf) {
-    const double mine = wg_total<NT>(v, buf);
-    if (G == 1) return mine;
-    ++sum_tag;
-    unsigned long long* const w = sums + (sum_tag & 1) * 2 * G;
-    if (tid == 0) put_double(w + 2 * member, 1, mine, sum_tag);
-    const int l = (int)(tid & 63);
-    return wave_total(l < G ? get_double(w + 2 * l, 1, sum_tag, a.stalled) : 0.0);
-  };
+  const int T = a.T;
+  int team, mate;
+  cl_place(T, (int)blockIdx.x, team, mate);
+  double* const bw = a.ws + (size_t)blockIdx.x * a.ws_rows;
+  unsigned long long* const words = a.words + (size_t)team * cl_team_words(T);
+  unsigned long long* const packet_word = words + 8 * T;
+  auto halo_of = [&](int m) { return a.halo + ((size_t)m * a.nteams + team) * 8 * (size_t)a.Amax; };
+  uint32_t sum_tag = 0, halo_tag = 0, packet_tag = 0;
 
   for (;;) {
-    // the next system: taken by the cluster's first workgroup
-    ++job_tag;
+    // the next packet, taken by the team's first workgroup.  The clusters of the
+    // packet before have made different numbers of exchanges: all go on from the
+    // largest, so that no word in memory carries a number still to come.
+    ++packet_tag;
     if (tid == 0) {
-      uint32_t j = 0;
-      if (member == 0) {
+      uint32_t j = 0, hi = sum_tag, hh = halo_tag;
+      if (T > 1) {
+        // two buffers: nobody is more than one packet ahead of another
+        unsigned long long* const counters = words + 4 * T + (packet_tag & 1) * 2 * T;
+        put_word(counters + 2 * mate, sum_tag, packet_tag);
+        put_word(counters + 2 * mate + 1, halo_tag, packet_tag);
+        for (int m = 0; m < T; ++m) {
+          uint32_t v = 0, u = 0;
+          if (!get_word(counters + 2 * m, packet_tag, a.stalled, v) ||
+              !get_word(counters + 2 * m + 1, packet_tag, a.stalled, u))
+            break;
+          hi = v > hi ? v : hi;
+          hh = u > hh ? u : hh;
+        }
+      }
+      if (mate == 0) {
         for (;;) {
           j = (uint32_t)atomicAdd(&a.queue[0], 1);
-          if ((int)j >= a.njobs || !a.skip ||
-              __hip_atomic_load(&a.queue[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (int)j)
+          if ((int)j >= a.npackets || !a.skip ||
+              __hip_atomic_load(&a.queue[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > a.packets[j].job)
             break;
-          a.outi[3 * (size_t)j] = kPadding;
+          for (int k = 0; k < a.packets[j].count; ++k) a.outi[3 * (size_t)(a.packets[j].job + k)] = kPadding;
         }
-        if (G > 1) put_word(jobw, j, job_tag);
-      } else if (!get_word(jobw, job_tag, a.stalled, j)) {
-        j = (uint32_t)a.njobs;
+        if (T > 1) put_word(packet_word, j, packet_tag);
+      } else if (!get_word(packet_word, packet_tag, a.stalled, j)) {
+        j = (uint32_t)a.npackets;
       }
-      if (G > 1 && __hip_atomic_load(a.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) j = (uint32_t)a.njobs;
-      s_job = (int)j;
+      if (T > 1 && __hip_atomic_load(a.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) j = (uint32_t)a.npackets;
+      s_word[0] = j;
+      s_word[1] = hi;
+      s_word[2] = hh;
     }
     __syncthreads();
-    const int job = __builtin_amdgcn_readfirstlane(s_job);
-    if (job >= a.njobs) return;
+    const int packet = (int)scalar(s_word[0]);
+    sum_tag = scalar(s_word[1]);
+    halo_tag = scalar(s_word[2]);
+    if (packet >= a.npackets) return;
+    const ClPacket pk = a.packets[packet];
+    const int G = (int)scalar((uint32_t)pk.G), sub = mate / G, member = mate % G;
+    if (sub >= (int)scalar((uint32_t)pk.count)) {
+      __syncthreads();                                // s_word is read
+      continue;
+    }
+    const int job = (int)scalar((uint32_t)pk.job) + sub;
+    unsigned long long* const halo_me = halo_of(mate);
+    const unsigned long long* const halo_dn = halo_of(sub * G + (member + G - 1) % G);
+    const unsigned long long* const halo_up = halo_of(sub * G + (member + 1) % G);
+    // Sum over the cluster, the same bits in every thread of every workgroup.
+    // Two buffers: nobody is more than one sum ahead of another.
+    auto total = [&](double v, double* buf) {
+      const double mine = wg_total<NT>(v, buf);
+      if (G == 1) return mine;
+      ++sum_tag;
+      unsigned long long* const w = words + (sum_tag & 1) * 2 * T + 2 * sub * G;
+      if (tid == 0) put_double(w + 2 * member, 1, mine, sum_tag);
+      const int l = (int)(tid & 63);
+      double part[1];
+      get_doubles<1>(1, sum_tag, a.stalled, part, [&](int) { return l < G; }, [&](int) { return w + 2 * l; });
+      return wave_total(part[0]);
+    };
     const ClJob J = a.jobs[job];
     const ClProblem& pr = a.probs[__builtin_amdgcn_readfirstlane(J.prob)];
     const uint32_t A = scalar(pr.A);
@@ -118,6 +181,10 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
     const uint32_t z1 = scalar((uint32_t)(member + 1) * pr.nz / (uint32_t)G);
     const uint32_t n = (z1 - z0) * A, s0 = z0 * A;
     const uint32_t npad = scalar((uint32_t)pr.npad);
+    // in scalar registers: read where they are used, each would cost a trip to
+    // memory between the sums of every iteration
+    const double tol2 = scalar(pr.tol2), freeze2 = scalar(pr.freeze2);
+    const int max_iter = (int)scalar((uint32_t)pr.max_iter), force_iter = (int)scalar((uint32_t)pr.force_iter);
     const uint32_t* const t_nbr = scalar(pr.nbr) + s0;
     const Double2* const t_wgt = scalar(reinterpret_cast<const Double2*>(pr.wgt)) + s0;
     const double* const t_D = scalar(pr.D) + s0;
@@ -200,15 +267,25 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
     };
     // f(word of S, neighbour's value) for the words of the two halo planes
     auto halo_words = [&](auto&& f) {
-      for (uint32_t i = tid; i < 2 * A; i += NT) {
-        const bool up = i >= A;
-        const uint32_t q = up ? i - A : i;
-        double v;
-        if (G == 1) v = up ? P[q] : P[n - A + q];
-        else
-          v = get_double((up ? halo_up : halo_dn) + ((size_t)(halo_tag & 1) * 2 + (up ? 0 : 1)) * 2 * a.Amax + q, a.Amax,
-                         halo_tag, a.stalled);
-        f(up ? P[n + q] : S[q], v);
+      constexpr int M = 4;
+      for (uint32_t i0 = tid; i0 < 2 * A; i0 += M * NT) {
+        double v[M];
+        auto at = [&](int j) { return i0 + (uint32_t)(j * NT); };
+        if (G == 1) {
+#pragma unroll
+          for (int j = 0; j < M; ++j)
+            if (at(j) < 2 * A) v[j] = at(j) >= A ? P[at(j) - A] : P[n - A + at(j)];
+        } else {
+          get_doubles<M>(a.Amax, halo_tag, a.stalled, v, [&](int j) { return at(j) < 2 * A; },
+                         [&](int j) {
+                           const bool up = at(j) >= A;
+                           return (up ? halo_up : halo_dn) + ((size_t)(halo_tag & 1) * 2 + (up ? 0 : 1)) * 2 * a.Amax +
+                                  (up ? at(j) - A : at(j));
+                         });
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j)
+          if (at(j) < 2 * A) f(at(j) >= A ? P[n + at(j) - A] : S[at(j)], v[j]);
       }
     };
     // the halo planes of the vector whose slab is in P
@@ -225,7 +302,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
     };
 
     // right-hand side
-    double r[K], t[K], x[XREG ? K : 1];
+    double r[K], t[K], x[K];
     double acc = 0.0;
     for (uint32_t e = tid; e < n; e += NT) {
       const double2 v = probe_entry(pr.site[s0 + e], (uint64_t)J.m, 0, pr.g, pr.seed, pr.mask);
@@ -237,8 +314,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
     const double bnorm2 = total(acc, red[0]);
     rows([&](int k, uint32_t e) {
       r[k] = in(e) ? row_of(bw, k, e) : 0.0;
-      if constexpr (XREG) x[k] = 0.0;
-      else if (in(e)) st_nt(&row_of(xw, k, e), 0.0);
+      x[k] = 0.0;
     });
     fill_halo();
     double rho = bnorm2;
@@ -254,7 +330,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
           acc = fma(pk, t[k], acc);
         });
         const double pAp = total(acc, red[0]);
-        if (!(pAp > 0.0) || !isfinite(pAp) || (pr.force_iter > 0 && restarts == 0 && it + 1 == pr.force_iter)) {
+        if (!(pAp > 0.0) || !isfinite(pAp) || (force_iter > 0 && restarts == 0 && it + 1 == force_iter)) {
           state = kBreakdown;
           break;
         }
@@ -264,8 +340,6 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         rows([&](int k, uint32_t e) {
           r[k] = fma(-alpha, t[k], r[k]);
           acc = fma(r[k], r[k], acc);
-          // x on its way while the sum is formed
-          if constexpr (!XREG) t[k] = in(e) ? ld_nt(&row_of(xw, k, e)) : 0.0;
           if (G > 1) {
             if ((uint32_t)(k * NT) < A && e < A) put_halo(0, e, r[k]);
             if ((uint32_t)(k * NT + NT) > n - A && in(e) && e >= n - A) put_halo(1, e - (n - A), r[k]);
@@ -274,15 +348,14 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         const double rho_new = total(acc, red[1]);
         ++it;
         if (!isfinite(rho_new)) state = kBreakdown;
-        else if (rho_new <= (restarts == 0 ? pr.freeze2 : pr.tol2) * bnorm2) state = kFrozen;
-        else if (it >= pr.max_iter) state = kNoConv;
+        else if (rho_new <= (restarts == 0 ? freeze2 : tol2) * bnorm2) state = kFrozen;
+        else if (it >= max_iter) state = kNoConv;
         const double beta = rho_new / rho;
         rho = rho_new;
         // x += alpha p; p = r + beta p, on the halo planes from the neighbours' r
         rows([&](int k, uint32_t e) {
           const double pk = in(e) ? row_of(P, k, e) : 0.0;
-          if constexpr (XREG) x[k] = fma(alpha, pk, x[k]);
-          else if (in(e)) st_nt(&row_of(xw, k, e), fma(alpha, pk, t[k]));
+          x[k] = fma(alpha, pk, x[k]);
           if (in(e)) row_of(P, k, e) = fma(beta, pk, r[k]);
         });
         if (G == 1) __syncthreads();
@@ -295,10 +368,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
       if (state != kFrozen) break;
       // the FP64 true residual b - A x
       rows([&](int k, uint32_t e) {
-        double v;
-        if constexpr (XREG) v = x[k];
-        else v = in(e) ? row_of(xw, k, e) : 0.0;
-        if (in(e)) row_of(P, k, e) = v;
+        if (in(e)) row_of(P, k, e) = x[k];
       });
       fill_halo();
       double a0 = 0.0, a1 = 0.0, a2 = 0.0;
@@ -313,11 +383,11 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
       });
       rt2 = total(a0, red[0]);
       q = total(pr.variational ? a1 + a2 : a1, red[1]);
-      if (rt2 <= pr.tol2 * bnorm2) {
+      if (rt2 <= tol2 * bnorm2) {
         state = kAccepted;
         break;
       }
-      if (restarts >= pr.max_restarts || it >= pr.max_iter || !isfinite(rt2)) {
+      if (restarts >= pr.max_restarts || it >= max_iter || !isfinite(rt2)) {
         state = kNoConv;
         break;
       }
@@ -330,14 +400,10 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
       });
       fill_halo();
     }
-    if (state == kAccepted && a.xout) {
-      if constexpr (XREG)
-        rows([&](int k, uint32_t e) {
-          if (in(e)) row_of(xw, k, e) = x[k];
-        });
-      for (uint32_t e = tid; e < n; e += NT)
-        a.xout[(size_t)J.x + ((size_t)pr.site[s0 + e] << a.logB) * (size_t)J.parts] = xw[e];
-    }
+    if (state == kAccepted && a.xout)
+      rows([&](int k, uint32_t e) {
+        if (in(e)) a.xout[(size_t)J.x + ((size_t)pr.site[s0 + e] << a.logB) * (size_t)J.parts] = x[k];
+      });
     if (tid == 0 && member == 0) {
       if (state != kAccepted) atomicMin(&a.queue[1], job);
       double* const oo = a.out + 3 * (size_t)job;
@@ -349,12 +415,16 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
       oi[1] = it;
       oi[2] = restarts;
     }
-    __syncthreads();                                  // S, red and s_job are free for the next system
+    __syncthreads();                                  // S, red and s_word are free for the next system
   }
 }
 
 // Up to 1024 rows four per thread, up to 2048 eight, then 512 threads: two
-// waves per SIMD, whose 256 registers hold two vectors of 40 rows.
+// waves per SIMD, whose 256 registers hold three vectors of 30 rows, of which some
+// spill (148 bytes a thread in three dimensions, 36 with 26 rows: 17.5 against
+// 16.4 us an iteration at 13125 rows, but 26 rows send more lattices to a second
+// workgroup).  Two vectors of 40 rows with x in memory took 23.0 ms on the 16
+// tori where this took 22.4.
 template <int ND, bool W>
 hipError_t launch_cluster_nd(const ClArgs& a, uint32_t rows, hipStream_t st) {
   const size_t lds = (size_t)cl_lds_rows(rows, a.Amax) * sizeof(double);
@@ -362,12 +432,12 @@ hipError_t launch_cluster_nd(const ClArgs& a, uint32_t rows, hipStream_t st) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)(a.nclusters * a.G);
-    if (a.G == 1) {
+    const unsigned grid = (unsigned)(a.nteams * a.T);
+    if (a.T == 1) {
       kernel<<<grid, nt, lds, st>>>(a);
       return hipGetLastError();
     }
-    // the workgroups of a cluster wait for one another: all must be resident
+    // the workgroups of a team wait for one another: all must be resident
     void* args[] = {const_cast<ClArgs*>(&a)};
     return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(kernel), dim3(grid), dim3((unsigned)nt), args,
                                       (unsigned)lds, st);
@@ -376,7 +446,7 @@ hipError_t launch_cluster_nd(const ClArgs& a, uint32_t rows, hipStream_t st) {
   if (rows <= 2048) return go(k_cluster<ND, W, 256, 8>, 256);
   if (rows <= 4096) return go(k_cluster<ND, W, 512, 8>, 512);
   if (rows <= 8192) return go(k_cluster<ND, W, 512, 16>, 512);
-  if (rows <= 20480) return go(k_cluster<ND, W, 512, 40>, 512);
+  if (rows <= kClMaxRows) return go(k_cluster<ND, W, 512, kClRows>, 512);
   return hipErrorInvalidValue;
 }
 

@@ -63,6 +63,10 @@ __device__ __forceinline__ EoNeighbours eo_neighbours(const Geom& g, int P, uint
 
 // A value that is the same in every lane, in scalar registers.
 __device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ double scalar(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
 template <class T>
 __device__ __forceinline__ const T* scalar(const T* p) {
   const uint64_t v = (uint64_t)p;

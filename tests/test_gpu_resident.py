@@ -92,3 +92,27 @@ def test_lattice_past_every_limit_uses_the_block_solver():
     _, q_o, _ = oracle_trace(OracleOp(dims, 0, mass=2.0), 1, 1e-12, 4018, MASK_Z2)
     assert st["stencil_launches"] > 1
     assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL
+
+
+def test_batch_teams_take_several_packets_of_mixed_cluster_sizes():
+    """Launches with more packets than teams (64 teams of 4 workgroups, 8 of 32),
+    packets of one, two, four and eight workgroups per system behind one another,
+    full and partly filled, at 15360 rows and just past them."""
+    tip = gpu_binding()
+    shapes = ([([48, 48, 48], 1)] * 7 + [([48, 48, 48], 5), ([40, 50, 45], 2)]        # 8 workgroups a system
+              + [([30, 47, 31], 3), ([16, 30, 32], 3), ([16, 31, 31], 3)]             # 4, 1 and 2
+              + [([4 + k % 3, 5, 6 + k % 7], 1 + k % 6) for k in range(66)])
+    ops = [dict(mass=0.4 + 0.002 * k) for k in range(len(shapes))]
+    ns = [n for _, n in shapes]
+    gops = [tip.Operator(d, 0, **o) for (d, _), o in zip(shapes, ops)]
+    out = tip.trace_inv_probe_batch(gops, ns, 1e-12, 4018, mask=MASK_Z2)
+    again = tip.trace_inv_probe_batch(gops, ns, 1e-12, 4018, mask=MASK_Z2)
+    for k, ((dims, n), (_, st)) in enumerate(zip(shapes, out)):
+        assert st["max_true_relres"] <= 1e-12, (dims, n)
+        q, q2 = (np.asarray(s["quadratures"]) for s in (st, again[k][1]))
+        assert np.array_equal(q, q2), (dims, n, "not reproducible")
+        if 1 <= k <= 6:                                      # a large lattice of the same shape as the first
+            q_o = tip.trace_inv_probe(gops[k], n, 1e-12, 4018, mask=MASK_Z2)[1]
+        else:
+            q_o = oracle_trace(OracleOp(dims, 0, **ops[k]), n, 1e-12, 4018, MASK_Z2)[1]
+        assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= REL, (dims, n)
