@@ -711,6 +711,8 @@ struct Solver {
   int gx_p;                   // partials per rhs of the iteration's matvec (gx_m unless pair)
   void *X, *Rv, *Pv, *W, *XH; // FP64 path: X, Rv, Pv, W; mixed: X (FP64) + XH, Rv, Pv, W (FP32)
   void *Xe = nullptr, *Tv = nullptr;   // even-odd: x_e and t_o (half lattice)
+  int group = 1;                // directions whose x updates are made together
+  void* Pg[kDefer] = {};        // where they are kept; the first of every group is Pv
   void *Bh = nullptr, *T64 = nullptr;  // mixed even-odd: b_hat and an FP64 t_o (half lattice)
   double* part;
   CgScalars sc;
@@ -868,7 +870,7 @@ struct Solver {
     // even-odd true residual
     if (const hipError_t e_ = h->partial.ensure(10 * pstride * sizeof(double)); e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipMalloc partials: %s", hipGetErrorString(e_));
-    const size_t scal_bytes = nscal * (13 * sizeof(double) + 4 * sizeof(int)) + 128 + kMaxChunk * sizeof(int);
+    const size_t scal_bytes = nscal * ((13 + kDefer) * sizeof(double) + 6 * sizeof(int)) + 128 + kMaxChunk * sizeof(int);
     if (const hipError_t e_ = h->scal.ensure(scal_bytes); e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipMalloc scalars: %s", hipGetErrorString(e_));
     const size_t host_bytes = nscal * (3 * sizeof(double) + 3 * sizeof(int)) + 128 + kMaxChunk * sizeof(int);
@@ -926,6 +928,20 @@ struct Solver {
       Pv = vb + 2 * vbytes;
       W = vb + 3 * vbytes;
     }
+    // x on the full lattice is written after CG only: until then its memory, two
+    // half vectors or more, holds a group's later directions.  Plain CG
+    // iterates on X itself and has no room to spare.  Where x, r, p, w and t fit
+    // the 256 MB memory-side cache, two more vectors only push others out: 32^4,
+    // past it, 101.9 -> 98.6 ms with groups and 128^3 72.7 -> 72.0, but 16^4 in
+    // mixed precision 11.84 -> 11.92.  TIP_EO_GROUP=1 groups always, 0 never.
+    group = pl.eo && !env_off("TIP_EO_GROUP") &&
+                    (5.0 * (double)(vbytes / 2) > 256.0 * 1048576.0 || env_on("TIP_EO_GROUP"))
+                ? kDefer
+                : 1;
+    const size_t half = vbytes / 2;
+    Pg[0] = Pv;
+    Pg[1] = pl.eo ? X : nullptr;
+    Pg[2] = pl.eo ? (char*)X + half : nullptr;
     part = (double*)h->partial.p;
     double* d = (double*)h->scal.p;
     sc.rho = d;
@@ -940,12 +956,15 @@ struct Solver {
     sc.anorm = d + 10 * nscal;
     sc.xhn = d + 11 * nscal;
     sc.dev = d + 12 * nscal;
-    int* iv = (int*)(d + 13 * nscal);
+    sc.past = d + 13 * nscal;        // kDefer * nscal
+    int* iv = (int*)(d + (13 + kDefer) * nscal);
     sc.state = iv;
     sc.iters = iv + nscal;
     sc.restarts = iv + 2 * nscal;
     sc.ru = iv + 3 * nscal;
-    sc.active = iv + 4 * nscal;
+    sc.from = iv + 4 * nscal;
+    sc.flush = iv + 5 * nscal;
+    sc.active = iv + 6 * nscal;
     sc.n_ru = sc.active + 1;
     sc.ru_count = sc.active + 2;
     sc.ru_lanes = nullptr;
@@ -1037,40 +1056,46 @@ struct Solver {
   // (with ||r||^2), beta, x += alpha p and p = r + beta p, then in mixed
   // precision any pending reliable update.  tv: events around the operator
   // application, or NULL.
-  tip_status enqueue_iteration(int it, const Timed* tv, int64_t rhs0, int nb, void* xdir) {
+  // Iteration it of a chunk: the last of a chunk ends its group, so that x is
+  // complete and the direction back in Pv when the host looks.
+  tip_status enqueue_iteration(int it, int chunk, const Timed* tv, int64_t rhs0, int nb, void* xdir) {
+    const int at = it % group, slot = group > 1 ? at : -1;
+    const bool last = at == group - 1 || it == chunk - 1;
+    void* const Pc = Pg[at];
+    void* const Pn = last ? Pv : Pg[at + 1];
     const Geom& g = geom;
     const MarchMap* mm = pl.use_march ? &pl.mm : nullptr;
     const double* diag = (const double*)h->diag.p;
     if (tv) TIP_HIP(hipEventRecord(tv->a, st));
     if (pl.pair) {
-      TIP_HIP(launch_eo_hop_pair(0, od, g, pl.me2, 1, prec, diag, sc.state, sc.active, Pv, nullptr, Tv, nullptr,
+      TIP_HIP(launch_eo_hop_pair(0, od, g, pl.me2, 1, prec, diag, sc.state, sc.active, Pc, nullptr, Tv, nullptr,
                                  nullptr, st));
       if (tv) TIP_HIP(hipEventRecord(tv->b, st));
-      TIP_HIP(launch_eo_hop_pair(1, od, g, pl.me2, 0, prec, diag, sc.state, sc.active, Tv, Pv, W, part, ran_dev + it,
+      TIP_HIP(launch_eo_hop_pair(1, od, g, pl.me2, 0, prec, diag, sc.state, sc.active, Tv, Pc, W, part, ran_dev + it,
                                  st));
     } else if (pl.wide) {
-      TIP_HIP(launch_eo_hop_wide(0, od, g, pl.me2, 1, diag, sc.state, sc.active, Pv, nullptr, Tv, nullptr, nullptr,
+      TIP_HIP(launch_eo_hop_wide(0, od, g, pl.me2, 1, diag, sc.state, sc.active, Pc, nullptr, Tv, nullptr, nullptr,
                                  st));
       if (tv) TIP_HIP(hipEventRecord(tv->b, st));
-      TIP_HIP(launch_eo_hop_wide(1, od, g, pl.me2, 0, diag, sc.state, sc.active, Tv, Pv, W, part, ran_dev + it, st));
+      TIP_HIP(launch_eo_hop_wide(1, od, g, pl.me2, 0, diag, sc.state, sc.active, Tv, Pc, W, part, ran_dev + it, st));
     } else if (pl.eo) {
       // w_e = S p_e: t_o = D_o^-1 H_oe p_e, then w_e = D_e p_e - H_eo t_o
-      TIP_HIP(launch_eo_hop(0, od, g, pl.me, 1, pl.elem, prec, diag, sc.state, sc.active, Pv, nullptr, Tv,
+      TIP_HIP(launch_eo_hop(0, od, g, pl.me, 1, pl.elem, prec, diag, sc.state, sc.active, Pc, nullptr, Tv,
                             nullptr, nullptr, 0, 0, 0, 0, nullptr, nullptr, st));
       if (tv) TIP_HIP(hipEventRecord(tv->b, st));
-      TIP_HIP(launch_eo_hop(1, od, g, pl.me, 0, pl.elem, prec, diag, sc.state, sc.active, Tv, Pv, W, nullptr,
+      TIP_HIP(launch_eo_hop(1, od, g, pl.me, 0, pl.elem, prec, diag, sc.state, sc.active, Tv, Pc, W, nullptr,
                             nullptr, 0, 0, 0, 0, part, ran_dev + it, st));
     } else {
       if (tv) TIP_HIP(hipEventRecord(tv->b, st));
-      TIP_HIP(launch_stencil(od, g, pl.tm, mm, pl.elem, prec, sc.state, sc.active, Pv, W, part, ran_dev + it,
+      TIP_HIP(launch_stencil(od, g, pl.tm, mm, pl.elem, prec, sc.state, sc.active, Pc, W, part, ran_dev + it,
                              st));
     }
     if (tv) TIP_HIP(hipEventRecord(tv->c, st));
     TIP_HIP(launch_reduce_alpha(sc, pl.B, part, gx_p, st, mixed ? 1 : 0, force_breakdown));
     TIP_HIP(launch_update_r(nvec, pl.logB, pl.elem, prec, sc, Rv, W, part + pstride, st));
     TIP_HIP(launch_reduce_beta(sc, pl.B, part + pstride, gx_u, tol2, max_iter, delta2, st, freeze2, ru_eps,
-                               ru_tau2));
-    TIP_HIP(launch_direction(nvec, pl.logB, pl.elem, prec, sc, xdir, Rv, Pv, st));
+                               ru_tau2, slot, last));
+    TIP_HIP(launch_direction(nvec, pl.logB, pl.elem, prec, sc, xdir, Rv, Pc, Pn, slot, Pg[0], Pg[1], st));
     if (mixed) {
       tip_status s = reliable(rhs0, nb, 0);
       if (s != TIP_OK) return s;
@@ -1106,7 +1131,7 @@ struct Solver {
     }
     tip_status s = TIP_OK;
     for (int it = 0; it < chunk && s == TIP_OK; ++it)
-      s = enqueue_iteration(it, nullptr, rhs0, nb, xdir);
+      s = enqueue_iteration(it, chunk, nullptr, rhs0, nb, xdir);
     hipGraph_t graph = nullptr;
     const hipError_t e = hipStreamEndCapture(st, &graph);
     hipError_t ei = hipErrorUnknown;
@@ -1172,7 +1197,7 @@ struct Solver {
               TIP_HIP(next_event(&tv.c));
               window.push_back(tv);
             }
-            tip_status s = enqueue_iteration(it, g_profiling ? &tv : nullptr, rhs0, nb, xdir);
+            tip_status s = enqueue_iteration(it, chunk, g_profiling ? &tv : nullptr, rhs0, nb, xdir);
             if (s != TIP_OK) return s;
           }
         }

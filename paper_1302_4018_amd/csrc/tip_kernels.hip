@@ -429,6 +429,38 @@ __global__ __launch_bounds__(kBlock) void k_update_r(size_t n, int logB, const C
   if ((int)threadIdx.x < B) partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = acc[0];
 }
 
+// pout = r + beta p for right-hand sides still iterating; x += the outstanding
+// updates of the group's directions p0, p1, p (this iteration's also for a rhs
+// that just converged), in their order and one rounding each, so x is the same
+// as from an update per iteration.  Bound by memory: x is read and written once
+// in kDefer iterations, 13 passes over half vectors in place of 15 for every
+// three, of 39 altogether.  p0 is pout in a group's last pass.
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_direction_group(size_t n, int logB, const CgScalars sc, T* __restrict__ x,
+                                                            const T* __restrict__ r, const T* p, T* pout, int slot,
+                                                            const T* p0, const T* p1) {
+  const int B = 1 << logB;
+  const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+  const int j = threadIdx.x & (B - 1);
+  if (i >= n) return;
+  const bool live = sc.state[j] == kActive, flush = sc.flush[j] != 0;
+  const int from = sc.from[j];
+  const double a0 = flush && slot > 0 && from <= 0 ? sc.past[j] : 0.0;
+  const double a1 = flush && slot > 1 && from <= 1 ? sc.past[B + j] : 0.0;
+  const double a = flush ? sc.xalpha[j] : 0.0;
+  const bool add = a0 != 0.0 || a1 != 0.0 || a != 0.0;
+  if (!add && !live) return;
+  const T pi = live || a != 0.0 ? p[i] : zero<T>();
+  if (add) {
+    T xi = x[i];
+    if (a0 != 0.0) xi = axpy(a0, p0[i], xi);
+    if (a1 != 0.0) xi = axpy(a1, p1[i], xi);
+    if (a != 0.0) xi = axpy(a, pi, xi);
+    x[i] = xi;
+  }
+  if (live) pout[i] = axpy(sc.beta[j], pi, r[i]);
+}
+
 // x += xalpha p (the update of this iteration, also for a rhs that just
 // converged); p = r + beta p for right-hand sides still iterating.
 template <class T>
@@ -565,19 +597,37 @@ __global__ __launch_bounds__(kBlock) void k_reduce_alpha(CgScalars sc, const dou
   lane_alpha(sc, j, pAp, soft, forced);
 }
 
+// The x update of direction `slot` of a group, and whether the coming direction
+// pass adds what is outstanding: after the last direction, and for a rhs about
+// to have a reliable update, which reads x.  Written here, a launch before the
+// pass whose workgroups all read them.
+__device__ __forceinline__ void lane_defer(const CgScalars& sc, int j, int slot, int last) {
+  if (slot < 0) return;
+  if (slot == 0)
+    sc.from[j] = 0;
+  else if (sc.flush[j])
+    sc.from[j] = slot;
+  sc.flush[j] = last || (sc.state[j] == kActive && sc.ru[j] != 0);
+  sc.past[(size_t)slot * gridDim.x + j] = sc.xalpha[j];
+}
+
 // rho' = ||r||^2 over up to 32768 update-pass partials, then lane_beta.
 __global__ __launch_bounds__(kWideBlock) void k_reduce_beta(CgScalars sc, const double* __restrict__ partial, int gx,
                                                         double tol2, int max_iter, double delta2, double first2,
-                                                        double eps, double tau2) {
+                                                        double eps, double tau2, int slot, int last) {
   const int j = blockIdx.x;
   if (sc.state[j] != kActive) {                // uniform per workgroup
-    if (threadIdx.x == 0) sc.xalpha[j] = 0.0;
+    if (threadIdx.x == 0) {
+      sc.xalpha[j] = 0.0;
+      lane_defer(sc, j, slot, last);
+    }
     return;
   }
   const BetaIn in = lane_beta_read(sc, j);    // uniform addresses: one load per wave
   const double rho_new = sum_partials_wide(partial + (size_t)j * gx, gx);
   if (threadIdx.x != 0) return;
   lane_beta(sc, j, in, rho_new, tol2, max_iter, delta2, first2, eps, tau2);
+  lane_defer(sc, j, slot, last);
 }
 
 // Accept a frozen solve when its true residual passes, else restart CG from x.
@@ -1669,11 +1719,15 @@ hipError_t launch_update_r(size_t n, int logB, Elem elem, Prec prec, const CgSca
 }
 
 hipError_t launch_direction(size_t n, int logB, Elem elem, Prec prec, const CgScalars& sc, void* x, const void* r,
-                            void* p, hipStream_t st) {
+                            void* p, void* pout, int slot, const void* p0, const void* p1, hipStream_t st) {
   const unsigned grid = cdiv(n, kBlock);
   return by_elem(elem, prec, [&](auto tv) {
     using T = decltype(tv);
-    k_direction<T><<<grid, kBlock, 0, st>>>(n, logB, sc, (T*)x, (const T*)r, (T*)p);
+    if (slot < 0)
+      k_direction<T><<<grid, kBlock, 0, st>>>(n, logB, sc, (T*)x, (const T*)r, (T*)p);
+    else
+      k_direction_group<T><<<grid, kBlock, 0, st>>>(n, logB, sc, (T*)x, (const T*)r, (const T*)p, (T*)pout, slot,
+                                                    (const T*)p0, (const T*)p1);
   });
 }
 
@@ -1953,9 +2007,10 @@ hipError_t launch_reduce_alpha(const CgScalars& sc, int B, const double* partial
 }
 
 hipError_t launch_reduce_beta(const CgScalars& sc, int B, const double* partial, int gx, double tol2, int max_iter,
-                              double delta2, hipStream_t st, double first2, double eps, double tau2) {
+                              double delta2, hipStream_t st, double first2, double eps, double tau2, int slot,
+                              int last) {
   k_reduce_beta<<<B, kWideBlock, 0, st>>>(sc, partial, gx, tol2, max_iter, delta2, first2 > 0.0 ? first2 : tol2,
-                                          eps, tau2);
+                                          eps, tau2, slot, last);
   return hipGetLastError();
 }
 

@@ -29,6 +29,9 @@ struct OpDev {
 };
 
 // Per right-hand-side CG scalars, device arrays of length B (q: 2B).
+// Directions of a group: x takes their updates in the direction pass of the last.
+constexpr int kDefer = 3;
+
 struct CgScalars {
   double* rho;
   double* alpha;
@@ -50,6 +53,9 @@ struct CgScalars {
   int* n_ru;                   // number of such right-hand sides
   int* ru_count;               // reliable updates done in the block
   int* ru_lanes;               // reliable updates per rhs (batched solver), or null
+  double* past;                // [kDefer][B] x updates of the directions in a group (block solver)
+  int* from;                   // first of them not in x yet
+  int* flush;                  // whether this direction pass adds them to x
 };
 
 // Generic site kernels: workgroup b owns TS = 256/B sites (tile_first_site).
@@ -135,8 +141,9 @@ unsigned update_grid(size_t n);
 unsigned ru_grid(const TileMap& tm);
 hipError_t launch_update_r(size_t n, int logB, Elem elem, Prec prec, const CgScalars& sc, void* r, const void* Ap,
                            double* partial, hipStream_t st);
+// slot: place in a group of kDefer directions, < 0 without groups (p in place)
 hipError_t launch_direction(size_t n, int logB, Elem elem, Prec prec, const CgScalars& sc, void* x, const void* r,
-                            void* p, hipStream_t st);
+                            void* p, void* pout, int slot, const void* p0, const void* p1, hipStream_t st);
 // mixed precision (FP32 CG, FP64 reliable updates); mode 0 = flagged lanes, 1 = frozen lanes
 hipError_t launch_init_mixed(const Geom& g, Elem elem, int logB, int64_t rhs0, int nb, uint64_t seed, int mask,
                              void* x64, void* xh, void* rh, void* ph, hipStream_t st);
@@ -200,7 +207,7 @@ hipError_t launch_reduce_alpha(const CgScalars& sc, int B, const double* partial
 // eps, tau2: residual-replacement bound of mixed precision (eps = 0 turns it off)
 hipError_t launch_reduce_beta(const CgScalars& sc, int B, const double* partial, int gx, double tol2, int max_iter,
                               double delta2, hipStream_t st, double first2 = 0.0, double eps = 0.0,
-                              double tau2 = 0.0);
+                              double tau2 = 0.0, int slot = -1, int last = 1);
 hipError_t launch_reduce_true(const CgScalars& sc, int B, const double* partial, int gx, size_t pstride, double tol2,
                               int max_iter, int max_restarts, hipStream_t st, const double* partial2 = nullptr);
 hipError_t launch_hier_perm(const Geom& g, uint32_t* out, hipStream_t st);

@@ -274,3 +274,35 @@ def test_fp64_covariant_512_thread_hops_match_256(dims, n):
     if orc.V <= 4096:
         est_o, q_o, _ = oracle_trace(orc, n, tol, 4018, MASK_Z4)
         assert _rel(q, q_o) <= REL
+
+
+@pytest.mark.parametrize("slack", [None, "50"])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind,dims", [(0, [8, 16]), (0, [8, 8, 16]), (1, [4, 4, 8]), (1, [8, 4, 4, 8])])
+def test_grouped_directions_leave_nothing_outstanding(kind, dims, precision, slack, monkeypatch):
+    """The block solver adds the x updates of three iterations together.  Masses
+    whose iteration counts differ, so that right-hand sides stop at every place
+    of a group, and restarts from an x that has to be complete; a block wider
+    than its right-hand sides."""
+    from oracle.general import trace_inv_probe as oracle_trace
+    from oracle.mask import MASK_Z4
+    from oracle.operators import Operator as OracleOp
+    tip = gpu_binding()
+    monkeypatch.setenv("TIP_RESIDENT", "0")
+    monkeypatch.setenv("TIP_EO_GROUP", "1")                  # by itself only past the memory-side cache
+    if slack:
+        monkeypatch.setenv("TIP_FREEZE_SLACK", slack)
+    prec = tip.PREC_MIXED if precision == "mixed" else tip.PREC_FP64
+    U = inputs.haar_links(dims, seed=911) if kind else None
+    iters = set()
+    for m0 in (0.05, 0.2, 0.5, 1.1, 3.0):
+        mf = inputs.mass_field(dims, m0=m0, seed=912)
+        gop = tip.Operator(dims, kind, mass_field=to_dev(mf), links=to_dev(U))
+        _, q, st = tip.trace_inv_probe(gop, 5, 1e-12, 4018, mask=MASK_Z4, precision=prec)
+        _, q_o, _ = oracle_trace(OracleOp(dims, kind, mass_field=mf, links=U), 5, 1e-12, 4018, MASK_Z4)
+        # a mass field with negative values (m0 = 0.05) leaves the even-odd reduction, and groups of one
+        assert st["even_odd"] == (1 if mf.min() > 0 else 0) and st["stencil_launches"] > 1
+        assert st["max_true_relres"] <= 1e-12
+        assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= 1e-10, m0
+        iters.add(st["stencil_launches"] % 3)
+    assert len(iters) > 1
