@@ -344,18 +344,17 @@ tip_status tip_apply_operator(const tip_operator* op, int32_t nrhs,
 /* tip_apply_operator for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same kernels and arithmetic (results equal bit for bit),
- * with the caller's mass field and couplings read in place and the
- * workspace (repacked links and the input and output vectors in the kernels'
- * layout) in a fixed device array of the library, 64 MiB per GPU, held from
- * first use until the process ends.  No hipMalloc, hipFree or allocating
+ * with the caller's arrays read in place.  Only an input that overlaps the
+ * output is copied first, into a fixed device array of the library, 64 MiB per
+ * GPU, held until the process ends.  No hipMalloc, hipFree or allocating
  * library routine is called; the first call on a device also resolves the
- * array's device address there (hipGetSymbolAddress).  Lattices whose
- * workspace exceeds 64 MiB (ndim * 9 * V * 16 bytes of links for the
+ * array's device address there (hipGetSymbolAddress) when it is needed.
+ * Lattices past a limit that does not depend on it, 64 MiB for (ndim * 9 * V * 16 bytes of links for the
  * covariant operator plus two vectors of ncomp * V elements, each part
  * rounded up to 256 bytes) fail with TIP_EINVAL before any device work.
- * Calls on one GPU share the array: calls that overlap on one GPU (from
- * several host threads, or on several streams) race and must be serialised
- * by the caller.  Every byte a call reads from the array it wrote earlier in
+ * Calls on one GPU share the array: calls with overlapping arrays that run at
+ * the same time on one GPU (from several host threads, or on several streams)
+ * race and must be serialised by the caller.  Every byte a call reads from the array it wrote earlier in
  * the same call, so nothing carries over between calls.  Synchronises
  * `stream` before returning. */
 tip_status tip_apply_operator_noalloc(const tip_operator* op, int32_t nrhs,

@@ -932,8 +932,8 @@ struct Solver {
     // half vectors or more, holds a group's later directions.  Plain CG
     // iterates on X itself and has no room to spare.  Where x, r, p, w and t fit
     // the 256 MB memory-side cache, two more vectors only push others out: 32^4,
-    // past it, 101.9 -> 98.6 ms with groups and 128^3 72.7 -> 72.0, but 16^4 in
-    // mixed precision 11.84 -> 11.92.  TIP_EO_GROUP=1 groups always, 0 never.
+    // past it, 102.2 -> 99.2 ms with groups (128^3 72.7 -> 72.0 twice, 72.8 -> 72.9
+    // once), but 16^4 in mixed precision 11.84 -> 11.92.  TIP_EO_GROUP=1 groups always, 0 never.
     group = pl.eo && !env_off("TIP_EO_GROUP") &&
                     (5.0 * (double)(vbytes / 2) > 256.0 * 1048576.0 || env_on("TIP_EO_GROUP"))
                 ? kDefer
@@ -3017,8 +3017,8 @@ tip_status tip_apply_operator(const tip_operator* op, int32_t nrhs, const double
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// Operator application without allocation.  Its workspace (repacked links and
-// the block-layout input and output vectors) lives in `scratch`, a file-scope
+// Operator application without allocation.  An input that overlaps the
+// output is copied to `scratch` first, a file-scope
 // device array of kScratchBytes: every GPU the library runs on holds its own
 // copy until the process ends, and calls on one GPU share it (overlapping
 // calls on one GPU race).  In host code the array's name is only a stand-in
