@@ -932,8 +932,8 @@ struct Solver {
     // half vectors or more, holds a group's later directions.  Plain CG
     // iterates on X itself and has no room to spare.  Where x, r, p, w and t fit
     // the 256 MB memory-side cache, two more vectors only push others out: 32^4,
-    // past it, 102.2 -> 99.2 ms with groups (128^3 72.7 -> 72.0 twice, 72.8 -> 72.9
-    // once), but 16^4 in mixed precision 11.84 -> 11.92.  TIP_EO_GROUP=1 groups always, 0 never.
+    // past it, 102.2 -> 99.2 ms with groups (128^3 72.7 -> 72.1, the same
+    // in one comparison of five), but 16^4 in mixed precision 11.84 -> 11.92.  TIP_EO_GROUP=1 groups always, 0 never.
     group = pl.eo && !env_off("TIP_EO_GROUP") &&
                     (5.0 * (double)(vbytes / 2) > 256.0 * 1048576.0 || env_on("TIP_EO_GROUP"))
                 ? kDefer
@@ -1023,7 +1023,7 @@ struct Solver {
     const Geom& g = geom;
     if (pl.eo) {
       const double* diag = (const double*)h->diag.p;
-      TIP_HIP(launch_ru_accumulate(nvec, pl.logB, pl.elem, sc, mode, Xe, XH, st));
+      if (mode == 1) TIP_HIP(launch_ru_accumulate(nvec, pl.logB, pl.elem, sc, Xe, XH, st));
       if (mode == 0) {
         // r_e = b_hat - S x_e in FP64 for the flagged lanes (the kernels return
         // at once while no reliable update is pending: n_ru doubles as the
@@ -1043,7 +1043,7 @@ struct Solver {
                                part + 5 * pstride));
       return TIP_OK;
     }
-    TIP_HIP(launch_ru_accumulate(nelem, pl.logB, pl.elem, sc, mode, X, XH, st));
+    if (mode == 1) TIP_HIP(launch_ru_accumulate(nelem, pl.logB, pl.elem, sc, X, XH, st));
     TIP_HIP(launch_ru_residual(od64, g, pl.tm, pl.elem, sc, mode, rhs0, nb, p->seed, pl.mask, X, Rv, Pv, part,
                                pstride, st));
     TIP_HIP(launch_reduce_ru(sc, pl.B, part, (int)ru_grid(pl.tm), pstride, mode, tol2, max_iter, max_restarts, st));
@@ -1095,7 +1095,8 @@ struct Solver {
     TIP_HIP(launch_update_r(nvec, pl.logB, pl.elem, prec, sc, Rv, W, part + pstride, st));
     TIP_HIP(launch_reduce_beta(sc, pl.B, part + pstride, gx_u, tol2, max_iter, delta2, st, freeze2, ru_eps,
                                ru_tau2, slot, last));
-    TIP_HIP(launch_direction(nvec, pl.logB, pl.elem, prec, sc, xdir, Rv, Pc, Pn, slot, Pg[0], Pg[1], st));
+    TIP_HIP(launch_direction(nvec, pl.logB, pl.elem, prec, sc, xdir, Rv, Pc, Pn, slot, Pg[0], Pg[1],
+                             mixed ? (pl.eo ? Xe : X) : nullptr, st));
     if (mixed) {
       tip_status s = reliable(rhs0, nb, 0);
       if (s != TIP_OK) return s;

@@ -429,6 +429,34 @@ __global__ __launch_bounds__(kBlock) void k_update_r(size_t n, int logB, const C
   if ((int)threadIdx.x < B) partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = acc[0];
 }
 
+// The FP64 form of a vector element.
+template <class T>
+struct Wide {
+  using type = T;
+};
+template <>
+struct Wide<float> {
+  using type = double;
+};
+template <>
+struct Wide<float2> {
+  using type = double2;
+};
+
+// A mixed solve (x64 set) whose rhs is about to have a reliable update: x64 takes
+// the single-precision x here, beside its last update.  In a pass of its own it
+// cost a launch in every iteration, with something to do in one of a dozen: 16^4
+// covariant, 64 probes, 12.10 -> 11.84 ms.
+template <class T>
+__device__ __forceinline__ void keep_x(T xi, T* __restrict__ x, typename Wide<T>::type* __restrict__ x64, size_t i,
+                                       bool wide) {
+  if (wide) {
+    x64[i] = axpy(1.0, from_c<typename Wide<T>::type>(to_c(xi)), x64[i]);
+    xi = zero<T>();
+  }
+  x[i] = xi;
+}
+
 // pout = r + beta p for right-hand sides still iterating; x += the outstanding
 // updates of the group's directions p0, p1, p (this iteration's also for a rhs
 // that just converged), in their order and one rounding each, so x is the same
@@ -438,7 +466,8 @@ __global__ __launch_bounds__(kBlock) void k_update_r(size_t n, int logB, const C
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_direction_group(size_t n, int logB, const CgScalars sc, T* __restrict__ x,
                                                             const T* __restrict__ r, const T* p, T* pout, int slot,
-                                                            const T* p0, const T* p1) {
+                                                            const T* p0, const T* p1,
+                                                            typename Wide<T>::type* __restrict__ x64) {
   const int B = 1 << logB;
   const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
   const int j = threadIdx.x & (B - 1);
@@ -448,7 +477,8 @@ __global__ __launch_bounds__(kBlock) void k_direction_group(size_t n, int logB, 
   const double a0 = flush && slot > 0 && from <= 0 ? sc.past[j] : 0.0;
   const double a1 = flush && slot > 1 && from <= 1 ? sc.past[B + j] : 0.0;
   const double a = flush ? sc.xalpha[j] : 0.0;
-  const bool add = a0 != 0.0 || a1 != 0.0 || a != 0.0;
+  const bool wide = x64 && ru_selected(sc, 0, j);
+  const bool add = a0 != 0.0 || a1 != 0.0 || a != 0.0 || wide;
   if (!add && !live) return;
   const T pi = live || a != 0.0 ? p[i] : zero<T>();
   if (add) {
@@ -456,7 +486,7 @@ __global__ __launch_bounds__(kBlock) void k_direction_group(size_t n, int logB, 
     if (a0 != 0.0) xi = axpy(a0, p0[i], xi);
     if (a1 != 0.0) xi = axpy(a1, p1[i], xi);
     if (a != 0.0) xi = axpy(a, pi, xi);
-    x[i] = xi;
+    keep_x(xi, x, x64, i, wide);
   }
   if (live) pout[i] = axpy(sc.beta[j], pi, r[i]);
 }
@@ -465,7 +495,8 @@ __global__ __launch_bounds__(kBlock) void k_direction_group(size_t n, int logB, 
 // converged); p = r + beta p for right-hand sides still iterating.
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_direction(size_t n, int logB, const CgScalars sc, T* __restrict__ x,
-                                                      const T* __restrict__ r, T* __restrict__ p) {
+                                                      const T* __restrict__ r, T* __restrict__ p,
+                                                      typename Wide<T>::type* __restrict__ x64) {
   const int B = 1 << logB;
   const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
   const int j = threadIdx.x & (B - 1);
@@ -473,8 +504,13 @@ __global__ __launch_bounds__(kBlock) void k_direction(size_t n, int logB, const 
   const double a = sc.xalpha[j];
   const bool live = sc.state[j] == kActive;
   if (a == 0.0 && !live) return;
+  const bool wide = x64 && ru_selected(sc, 0, j);
   const T pi = p[i];
-  if (a != 0.0) x[i] = axpy(a, pi, x[i]);
+  if (a != 0.0 || wide) {
+    T xi = x[i];
+    if (a != 0.0) xi = axpy(a, pi, xi);
+    keep_x(xi, x, x64, i, wide);
+  }
   if (live) p[i] = axpy(sc.beta[j], pi, r[i]);
 }
 
@@ -678,16 +714,15 @@ __global__ __launch_bounds__(kBlock) void k_init_mixed(Geom g, int logB, int64_t
   store_vec<T32, NC>(ph, g.V, logB, s, j, b);
 }
 
-// x64 += xh, xh = 0 for the selected lanes (flat [ncomp][V][B] elements,
-// grid-stride with a stride that is a multiple of 256).  Mode 0 runs after
-// every CG iteration and returns at once when no update is pending.
+// x64 += xh, xh = 0 for the frozen lanes before their final check (flat
+// [ncomp][V][B] elements, grid-stride with a stride that is a multiple of 256);
+// the direction pass does it for reliable updates (keep_x).
 template <class T64, class T32>
-__global__ __launch_bounds__(kBlock) void k_ru_accumulate(size_t n, int logB, const CgScalars sc, int mode,
-                                                          T64* __restrict__ x, T32* __restrict__ xh) {
-  if (mode == 0 && *sc.n_ru == 0) return;
+__global__ __launch_bounds__(kBlock) void k_ru_accumulate(size_t n, int logB, const CgScalars sc, T64* __restrict__ x,
+                                                          T32* __restrict__ xh) {
   const int B = 1 << logB;
   const int j = threadIdx.x & (B - 1);
-  if (!ru_selected(sc, mode, j)) return;
+  if (!ru_selected(sc, 1, j)) return;
   const size_t stride = (size_t)gridDim.x * kBlock;
   for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
     x[i] = axpy(1.0, from_c<T64>(to_c(xh[i])), x[i]);
@@ -1719,15 +1754,16 @@ hipError_t launch_update_r(size_t n, int logB, Elem elem, Prec prec, const CgSca
 }
 
 hipError_t launch_direction(size_t n, int logB, Elem elem, Prec prec, const CgScalars& sc, void* x, const void* r,
-                            void* p, void* pout, int slot, const void* p0, const void* p1, hipStream_t st) {
+                            void* p, void* pout, int slot, const void* p0, const void* p1, void* x64, hipStream_t st) {
   const unsigned grid = cdiv(n, kBlock);
   return by_elem(elem, prec, [&](auto tv) {
     using T = decltype(tv);
     if (slot < 0)
-      k_direction<T><<<grid, kBlock, 0, st>>>(n, logB, sc, (T*)x, (const T*)r, (T*)p);
+      k_direction<T><<<grid, kBlock, 0, st>>>(n, logB, sc, (T*)x, (const T*)r, (T*)p,
+                                               (typename Wide<T>::type*)x64);
     else
       k_direction_group<T><<<grid, kBlock, 0, st>>>(n, logB, sc, (T*)x, (const T*)r, (const T*)p, (T*)pout, slot,
-                                                    (const T*)p0, (const T*)p1);
+                                                    (const T*)p0, (const T*)p1, (typename Wide<T>::type*)x64);
   });
 }
 
@@ -1746,15 +1782,13 @@ hipError_t launch_init_mixed(const Geom& g, Elem elem, int logB, int64_t rhs0, i
   return hipGetLastError();
 }
 
-hipError_t launch_ru_accumulate(size_t n, int logB, Elem elem, const CgScalars& sc, int mode, void* x64, void* xh,
+hipError_t launch_ru_accumulate(size_t n, int logB, Elem elem, const CgScalars& sc, void* x64, void* xh,
                                 hipStream_t st) {
-  // launched every iteration and returning at once while no update is
-  // pending: a smaller grid than the update pass keeps that cheap
   const unsigned grid = std::min<unsigned>(cdiv(n, kBlock), 8192u);
   if (elem == Elem::kReal)
-    k_ru_accumulate<double, float><<<grid, kBlock, 0, st>>>(n, logB, sc, mode, (double*)x64, (float*)xh);
+    k_ru_accumulate<double, float><<<grid, kBlock, 0, st>>>(n, logB, sc, (double*)x64, (float*)xh);
   else
-    k_ru_accumulate<double2, float2><<<grid, kBlock, 0, st>>>(n, logB, sc, mode, (double2*)x64, (float2*)xh);
+    k_ru_accumulate<double2, float2><<<grid, kBlock, 0, st>>>(n, logB, sc, (double2*)x64, (float2*)xh);
   return hipGetLastError();
 }
 

@@ -143,11 +143,11 @@ hipError_t launch_update_r(size_t n, int logB, Elem elem, Prec prec, const CgSca
                            double* partial, hipStream_t st);
 // slot: place in a group of kDefer directions, < 0 without groups (p in place)
 hipError_t launch_direction(size_t n, int logB, Elem elem, Prec prec, const CgScalars& sc, void* x, const void* r,
-                            void* p, void* pout, int slot, const void* p0, const void* p1, hipStream_t st);
+                            void* p, void* pout, int slot, const void* p0, const void* p1, void* x64, hipStream_t st);
 // mixed precision (FP32 CG, FP64 reliable updates); mode 0 = flagged lanes, 1 = frozen lanes
 hipError_t launch_init_mixed(const Geom& g, Elem elem, int logB, int64_t rhs0, int nb, uint64_t seed, int mask,
                              void* x64, void* xh, void* rh, void* ph, hipStream_t st);
-hipError_t launch_ru_accumulate(size_t n, int logB, Elem elem, const CgScalars& sc, int mode, void* x64, void* xh,
+hipError_t launch_ru_accumulate(size_t n, int logB, Elem elem, const CgScalars& sc, void* x64, void* xh,
                                 hipStream_t st);
 hipError_t launch_ru_residual(const OpDev& od64, const Geom& g, const TileMap& tm, Elem elem, const CgScalars& sc,
                               int mode, int64_t rhs0, int nb, uint64_t seed, int mask, const void* x64, void* rh,
