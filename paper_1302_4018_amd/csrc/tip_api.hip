@@ -1931,7 +1931,17 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
   const size_t V = gg.V;
   RunResult rr(n_rhs);
   bool failed = false;
-  hipStream_t st_used = nullptr;
+  // The stream the call queued work on.  What returns early, or with a solve
+  // that was not accepted, waits for it: the gradient's sums may still be queued,
+  // writing the caller's arrays from the solutions in the workspace.
+  struct Queued {
+    hipStream_t st = nullptr;
+    bool any = false;
+    void on(hipStream_t s) { st = s, any = true; }
+    ~Queued() {
+      if (any) (void)hipStreamSynchronize(st);
+    }
+  } queued;
   // Solve right-hand sides [r0, r1) in blocks: rhs r (lane rhs of the kernels)
   // is result slot slot(r); stops at the first block holding a failed solve.
   auto run_range = [&](Solver& sv, int64_t r0, int64_t r1, auto slot) -> tip_status {
@@ -1994,7 +2004,6 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
     const int64_t base = p->m_begin * ncomp;
     auto slot = [&](int64_t r) { return (size_t)(r - base); };
     auto clear = [&](hipStream_t st) -> tip_status {
-      st_used = st;
       if (grad_mass) TIP_HIP(launch_fill(V, grad_mass, 0.0, st));
       if (grad_coupling) TIP_HIP(launch_fill((size_t)gg.ndim * V, grad_coupling, 0.0, st));
       return TIP_OK;
@@ -2002,6 +2011,7 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
     if (res >= 0) {
       ResidentRun rs;
       s = rs.setup(h, p, mask, res, -1);
+      queued.on(rs.st);
       if (s == TIP_OK) s = clear(rs.st);
       if (s == TIP_OK)
         s = run_resident(base, base + n_rhs, 0, 0, false, rs, [&](int, int64_t r) { return slot(r); });
@@ -2011,6 +2021,7 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
       Solver sv;
       sv.need_x = want_grad;
       s = sv.setup(h, p, mask);
+      queued.on(sv.st);
       if (s == TIP_OK) s = clear(sv.st);
       if (s == TIP_OK) s = run_range(sv, base, base + n_rhs, slot);
       if (s != TIP_OK) return s;
@@ -2038,6 +2049,7 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
     if (res >= 0) {
       ResidentRun rs;
       s = rs.setup(h, p, mask, res, 0);
+      queued.on(rs.st);
       if (s == TIP_OK) s = run_resident(i0[0], i1[0], i0[1], i1[1], true, rs, slot);
       if (s != TIP_OK) return s;
       add_stats(rs);
@@ -2049,11 +2061,11 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
         sv.force_elem = c;             // j3 = 0: real, j3 = 1: complex
         sv.rhs_hint = (i1[c] - i0[c]) * ncomp;
         s = sv.setup(h, p, mask);
+        queued.on(sv.st);
         if (s != TIP_OK) return s;
         sv.geom.cls_gamma = cg[c].cls_gamma;
         sv.geom.cls_nbc = cg[c].cls_nbc;
         sv.geom.cls_j3 = c;
-        st_used = sv.st;
         s = run_range(sv, i0[c] * ncomp, i1[c] * ncomp, [&](int64_t r) { return slot(c, r); });
         if (s != TIP_OK) return s;
         add_stats(sv);
@@ -2064,10 +2076,11 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
   s = finish_run(h, p, rr, estimates, stats, t_start);
   if (s == TIP_OK && want_grad) {
     const double f = -1.0 / (double)p->n_vectors;
-    if (grad_mass) TIP_HIP(launch_scale(V, grad_mass, f, st_used));
-    if (grad_coupling) TIP_HIP(launch_scale((size_t)gg.ndim * V, grad_coupling, f, st_used));
-    TIP_HIP(hipStreamSynchronize(st_used));
+    if (grad_mass) TIP_HIP(launch_scale(V, grad_mass, f, queued.st));
+    if (grad_coupling) TIP_HIP(launch_scale((size_t)gg.ndim * V, grad_coupling, f, queued.st));
+    TIP_HIP(hipStreamSynchronize(queued.st));
   }
+  if (s == TIP_OK) queued.any = false;           // waited for above, or with the last launch's results
   return s;
 }
 
@@ -2837,6 +2850,9 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
             TIP_HIP(launch_layout(g, rs.elem, logB, 0, x, x_out, rs.st));
             return TIP_OK;
           });
+    // x_out is written when the call returns, and after an error nothing of it is left queued
+    const hipError_t waited = hipStreamSynchronize(rs.st);
+    if (s == TIP_OK && waited != hipSuccess) s = fail(TIP_EDEVICE, "solve failed: %s", hipGetErrorString(waited));
     if (s != TIP_OK) return s;
     if (q_out) {
       q_out[0] = o.q;

@@ -1,0 +1,66 @@
+"""What calls keep when their lattices are solved in LDS: results complete when
+a call returns, the same failures reported, the same arithmetic for a
+right-hand side whichever run it belongs to, the same arrays allowed."""
+
+import numpy as np
+import pytest
+import torch
+
+from conftest import gpu_binding, to_dev
+from oracle.mask import MASK_Z4
+from oracle.operators import Operator as OracleOp
+from oracle.general import rhs
+from paper_1302_4018_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# even-odd system, scalar and covariant; whole lattice on one CU and on several
+LDS = [([16, 16, 16], 0), ([4, 4, 4, 8], 1), ([9, 7, 15], 0), ([30, 47, 31], 0)]
+
+
+def _op(tip, dims, kind, seed, m0=0.3):
+    w = inputs.couplings(dims, seed=seed)
+    mf = inputs.mass_field(dims, m0=m0, seed=seed + 1)
+    U = inputs.haar_links(dims, seed=seed + 2) if kind else None
+    return (OracleOp(dims, kind, mass_field=mf, coupling=w, links=U),
+            tip.Operator(dims, kind, mass_field=to_dev(mf), coupling=to_dev(w), links=to_dev(U)))
+
+
+@pytest.mark.parametrize("dims,kind", LDS)
+@pytest.mark.parametrize("own", [True, False])
+def test_solve_probe_has_written_x_when_it_returns(dims, kind, own):
+    """On a caller's stream nothing is left queued; on the null stream, where the
+    library works on a stream of its own, x is read at once on another stream,
+    and the handle may go.  A second call needs more workspace than the first."""
+    tip = gpu_binding()
+    orc, gop = _op(tip, dims, kind, 920)
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with tip.OpHandle(gop) as h:
+        x, q, st = h.solve_probe(3, 0, 1e-11, 17, mask=MASK_Z4, stream=stream if own else None)
+        if own:
+            assert stream.query(), "work left on the caller's stream"
+        with torch.cuda.stream(other):
+            xg = x.cpu().numpy()
+        assert st["stencil_launches"] == 1, "not solved in LDS"
+        h.trace_inv_probe(min(orc.V, 16), 1e-6, 17, mask=MASK_Z4, stream=stream if own else None)
+    again = x.cpu().numpy()
+    assert np.array_equal(xg, again)
+    b = rhs(orc.dims, orc.ncomp, 3, 0, 17, MASK_Z4)
+    r = b - orc.apply(xg)
+    assert np.linalg.norm(r) <= 2e-11 * np.linalg.norm(b)
+    assert abs(q - np.vdot(b, xg)) <= 1e-12 * abs(q)
+
+
+@pytest.mark.parametrize("dims,kind,resident", [([16, 16], 0, "1"), ([9, 7, 15], 0, "1"), ([8, 8, 8], 0, "0")])
+def test_gradient_of_a_failed_run_leaves_nothing_queued(dims, kind, resident, monkeypatch):
+    tip = gpu_binding()
+    monkeypatch.setenv("TIP_RESIDENT", resident)
+    _, gop = _op(tip, dims, kind, 930)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with tip.OpHandle(gop) as h:
+        with pytest.raises(tip.TipError) as e:
+            h.trace_inv_probe_grad(70, 1e-12, 17, max_iter=2, stream=stream)
+        assert e.value.status == tip.TIP_ENOCONV
+        assert stream.query(), "work left on the caller's stream"
