@@ -1606,7 +1606,7 @@ struct ResidentRun {
       const double* out = nullptr;
       const int* outi = nullptr;
       double* x = nullptr;
-      tip_status s = eo ? run_eo(c0, d0, nsys0, nsys, parts, cls, x_bytes, logB, cus, ev, &out, &outi, &x)
+      tip_status s = eo ? run_eo(c0, nsys, parts, x_bytes, logB, cus, ev, &out, &outi, &x)
                         : run_plain(c0, d0, nsys0, nsys, parts, cls, x_bytes, logB, cus, ev, &out, &outi, &x);
       if (s == TIP_OK && need_x) s = solved(x, logB, (int)nr);
       if (s != TIP_OK) return s;
@@ -1652,9 +1652,10 @@ struct ResidentRun {
   }
 
   // Systems 0 .. nsys - 1 of a chunk (the first nsys0 from right-hand side c0
-  // on, the others of class 1 from d0 on), solved when it returns.
-  tip_status run_eo(int64_t c0, int64_t d0, int nsys0, int nsys, int parts, bool cls, size_t x_bytes, int logB, int cus,
-                    hipEvent_t* ev, const double** out, const int** outi, double** x) {
+  // on, the others of class 1 from d0 on), solved when it returns.  An even-odd
+  // system has power-of-two sides, so no classes.
+  tip_status run_eo(int64_t c0, int nsys, int parts, size_t x_bytes, int logB, int cus, hipEvent_t* ev,
+                    const double** out, const int** outi, double** x) {
     const ResTables& t = h->res;
     const bool cov = h->kind == TIP_KIND_COVARIANT;
     const size_t slots = (size_t)std::min(nsys, cus * (cov ? res_cov_wgs_per_cu(t.n) : res_wgs_per_cu(t.n)));
@@ -1675,10 +1676,7 @@ struct ResidentRun {
     a.mask = mask;
     a.parts = parts;
     a.rhs0 = c0;
-    a.rhs1 = d0;
-    a.nsys0 = nsys0;
     a.nsys = nsys;
-    a.cls = cls ? 1 : 0;
     a.start_frozen = p->tol >= 1.0 ? 1 : 0;
     a.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)geom.V, 1 << 20);
     a.max_restarts = 8;
@@ -1718,8 +1716,11 @@ struct ResidentRun {
       cg.cls_j3 = c;
       const int64_t j = l / np;
       const int64_t lane = (((j >> logB) * (int64_t)geom.V) << logB) + (j & ((int64_t(1) << logB) - 1));
-      jobs[(size_t)i] = ClJob{0, l % np, np, (int64_t)class_probe((uint64_t)((c ? d0 : c0) + j), cg), lane * np + l % np};
+      jobs[(size_t)i] = ClJob{0, l % np, np, (int64_t)class_probe((uint64_t)((c ? d0 : c0) + j), cg), lane * np + l % np, i};
     }
+    // a job that fails lets the launch skip those behind it: behind it in the
+    // order of probes, whichever class they are of, as the checkpoints stop there
+    if (cls) std::stable_sort(jobs.begin(), jobs.end(), [](const ClJob& a, const ClJob& b) { return a.m < b.m; });
     const ClusterCut cut(geom);
     const int G = cut.pick(nsys, cus);
     std::vector<ClPacket> packets((size_t)nsys);
@@ -2029,8 +2030,8 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
     }
   } else {
     const ClassMap cm{(int64_t)gg.gamma, int64_t(1) << gg.LB};
-    // each class runs up to its own first failure; the checkpoints then stop
-    // at the first probe, in probe order, that is not accepted
+    // each class runs at least up to the first failure in probe order, where the
+    // checkpoints stop
     int64_t i0[2] = {0, 0}, i1[2] = {0, 0};
     Geom cg[2] = {gg, gg};
     for (int c = 0; c < 2; ++c) {
@@ -2210,7 +2211,7 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
     const System& y = systems[k];
     const Key& q = key[(size_t)y.prob];
     const ClusterCut c(hs[(size_t)y.prob]->geom);
-    jobs[k] = ClJob{y.prob, y.part, y.parts, y.m, 0};
+    jobs[k] = ClJob{y.prob, y.part, y.parts, y.m, 0, (int)k};
     // a launch keeps room for its widest plane and its most rows together
     const uint32_t rows = launches.empty() ? 0 : std::max(launches.back().rows, c.rows(q.G));
     const uint32_t A = launches.empty() ? 0 : std::max(launches.back().A, c.A);

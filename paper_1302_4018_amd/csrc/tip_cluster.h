@@ -35,6 +35,7 @@ struct ClJob {
   int prob, part, parts;
   int64_t m;                     // probe index
   int64_t x;                     // first element of its solution in xout (step parts << logB per site)
+  int slot;                      // its place in out and outi
 };
 
 // Systems that a team of T workgroups solves at the same time, T / G of them at
@@ -59,7 +60,7 @@ struct ClArgs {
   double* out;                   // [jobs][3]: quadrature, ||b - A x||^2, ||b||^2
   int* outi;                     // [jobs][3]: state, iterations, restarts
   int* queue;                    // [0] next packet, [1] lowest failed job (packets above it may be skipped)
-  int skip;                      // whether they are
+  int skip;                      // whether they are: jobs are in the order of their probes then
   int* stalled;                  // host memory: set when a wait ran into its limit
 };
 __host__ __device__ inline size_t cl_team_words(int T) { return (size_t)T * 8 + 1; }

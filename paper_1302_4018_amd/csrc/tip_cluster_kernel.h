@@ -135,7 +135,10 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
           if ((int)j >= a.npackets || !a.skip ||
               __hip_atomic_load(&a.queue[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > a.packets[j].job)
             break;
-          for (int k = 0; k < a.packets[j].count; ++k) a.outi[3 * (size_t)(a.packets[j].job + k)] = kPadding;
+          for (int k = 0; k < a.packets[j].count; ++k) {
+            int* const oi = a.outi + 3 * (size_t)a.jobs[a.packets[j].job + k].slot;
+            oi[0] = kPadding, oi[1] = 0, oi[2] = 0;
+          }
         }
         if (T > 1) put_word(packet_word, j, packet_tag);
       } else if (!get_word(packet_word, packet_tag, a.stalled, j)) {
@@ -406,8 +409,8 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
       });
     if (tid == 0 && member == 0) {
       if (state != kAccepted) atomicMin(&a.queue[1], job);
-      double* const oo = a.out + 3 * (size_t)job;
-      int* const oi = a.outi + 3 * (size_t)job;
+      double* const oo = a.out + 3 * (size_t)J.slot;
+      int* const oi = a.outi + 3 * (size_t)J.slot;
       oo[0] = q;
       oo[1] = rt2;
       oo[2] = bnorm2;

@@ -21,20 +21,18 @@ struct ResTables {
   uint32_t n, npad;
 };
 
-// One launch: systems 0 .. nsys-1, system i < nsys0 solving part i % parts (0
+// One launch: systems 0 .. nsys-1, system i solving part i % parts (0
 // real, 1 imaginary) of right-hand side rhs0 + i / parts.  A is real, so the
 // two parts of a complex right-hand side are two real systems, and b^H A^-1 b,
-// real for any b, is the sum of their quadratures.  With cls the
-// right-hand sides are those of the F_3 classes of the conjugate split: class
-// 0 (real, parts = 1) first, then from nsys0 on class 1 (complex) from rhs1.
+// real for any b, is the sum of their quadratures.
 struct ResArgs {
   Geom g;
   ResTables t;
   uint64_t seed;
   int mask;
   int parts;
-  int64_t rhs0, rhs1;
-  int nsys0, nsys, cls;
+  int64_t rhs0;
+  int nsys;
   int start_frozen, max_iter, max_restarts, force_iter;
   double tol2, freeze2;
   const double* links;       // covariant: the even-odd link layout [2][ndim][9][n] double2

@@ -24,13 +24,6 @@
 
 namespace tip {
 
-// Probe of right-hand side i of F_3 class j3 (class_probe with the class a
-// value of the right-hand side).
-__device__ __forceinline__ uint64_t res_class_probe(uint64_t i, uint32_t j3, const Geom& g) {
-  const uint64_t nbc = 1ull << g.LB;
-  return (i / nbc) * (uint64_t)g.gamma + (uint64_t)j3 * nbc + i % nbc;
-}
-
 // NT threads, K rows per thread: thread t owns rows t, t + NT, ...  FULL: the
 // system has exactly NT K rows, so no row is tested.
 template <int ND, bool W, int NT, int K, bool FULL>
@@ -135,12 +128,8 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
       if (tid == 0) oi[0] = kPadding, oi[1] = 0, oi[2] = 0;
       continue;
     }
-    // the second class of right-hand sides follows the first
-    const int c1 = sys >= a.nsys0 ? 1 : 0;
-    const int local = sys - (c1 ? a.nsys0 : 0), parts = c1 ? 2 : a.parts;
-    const int64_t i = (c1 ? a.rhs1 : a.rhs0) + local / parts;
-    const uint64_t m = a.cls ? res_class_probe((uint64_t)i, (uint32_t)c1, a.g) : (uint64_t)i;
-    const int part = local % parts;
+    const int parts = a.parts, part = sys % parts;
+    const uint64_t m = (uint64_t)(a.rhs0 + sys / parts);
     auto entry = [&](uint32_t s) { return probe_entry(s, m, 0, a.g, a.seed, a.mask); };
     double bn = 0.0;
     for (uint32_t e = tid; e < n; e += NT)
@@ -283,7 +272,7 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
         rows([&](int k, uint32_t e) {
           if (in(e)) xe[e] = x[k];
         });
-      const int j = local / parts;
+      const int j = sys / parts;
       const size_t lane = (((size_t)(j >> a.logB) * a.g.V) << a.logB) + (size_t)(j & ((1 << a.logB) - 1));
       for (uint32_t e = tid; e < n; e += NT)
         for (int P = 0; P < 2; ++P) {

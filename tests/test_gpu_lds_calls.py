@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from conftest import gpu_binding, to_dev
-from oracle.mask import MASK_Z4
+from oracle.mask import MASK_Z2, MASK_Z4
 from oracle.operators import Operator as OracleOp
 from oracle.general import rhs
 from paper_1302_4018_amd import inputs
@@ -64,3 +64,34 @@ def test_gradient_of_a_failed_run_leaves_nothing_queued(dims, kind, resident, mo
             h.trace_inv_probe_grad(70, 1e-12, 17, max_iter=2, stream=stream)
         assert e.value.status == tip.TIP_ENOCONV
         assert stream.query(), "work left on the caller's stream"
+
+
+@pytest.mark.parametrize("dims,kind,n", [([9, 7, 15], 0, 945), ([12, 5, 8], 0, 480)])
+@pytest.mark.parametrize("broken", [False, True])
+def test_failure_is_the_first_in_probe_order(dims, kind, n, broken, monkeypatch):
+    """More systems than run at once, some of them stopped at the iteration that
+    most finish before: the probe named, the status, the checkpoints and the
+    residuals up to it are those of one probe at a time, whatever class of the
+    three-colouring it is of."""
+    tip = gpu_binding()
+    _, gop = _op(tip, dims, kind, 940, m0=0.5)
+    with tip.OpHandle(gop) as h:
+        _, q, full = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z2)
+        checked = 0
+        for stop in range(full["max_iters"] - 1, full["max_iters"] - 4, -1):
+            kw = {} if broken else {"max_iter": stop}
+            if broken:
+                monkeypatch.setenv("TIP_FORCE_BREAKDOWN", str(stop + 1))
+            bad = next((m for m in range(n) if h.trace_inv_probe(
+                m + 1, 1e-10, 4018, mask=MASK_Z2, m_begin=m, quadratures=q, raise_on_error=False, **kw)[2]["status"]), n)
+            est, _, st = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z2, raise_on_error=False, **kw)
+            print(f"{dims} stop {stop} broken {broken}: probe {bad} of {n}", flush=True)
+            if bad == n:
+                assert st["status"] == tip.TIP_OK
+                continue
+            checked += 1
+            assert st["status"] == (tip.TIP_EBREAKDOWN if broken else tip.TIP_ENOCONV)
+            assert f"probe {bad} " in tip.tip_last_error()
+            assert len(est) == (bad.bit_length() if bad else 0)        # checkpoints 1, 2, 4, .. up to bad probes
+            assert not np.isnan(st["residuals"][:bad]).any() and np.isnan(st["residuals"][bad]).any()
+        assert checked
