@@ -40,6 +40,20 @@ __device__ __forceinline__ double wg_total(double v, double* red /* [NT / 64] */
   return s;
 }
 
+// Whether a system below `sys` has failed: one load, the same answer in every
+// thread, so that a workgroup skips a system as a whole while others fail.
+// The word is free again after the next barrier of the workgroup.
+template <int NT>
+__device__ __forceinline__ bool wg_failed_before(const int* first_failed, int sys, int* word) {
+  int f = 0;
+  if (threadIdx.x == 0) f = __hip_atomic_load(first_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (NT == 64) return __builtin_amdgcn_readfirstlane(f) < sys;
+  __syncthreads();                                    // the word's last reads
+  if (threadIdx.x == 0) *word = f;
+  __syncthreads();
+  return *word < sys;
+}
+
 // Neighbours along mu of row e of parity P of an even-odd system (n rows, sides
 // powers of two, half-lattice numbering) in the other parity's: along the last
 // dimension slices tau + delta and tau - 1 + delta, delta the parity of P and

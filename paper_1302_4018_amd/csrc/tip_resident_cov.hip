@@ -25,6 +25,7 @@ __global__ __launch_bounds__(NT) void k_resident_cov(const ResArgs a) {
   constexpr int RL = K == 4 ? 2 : 0;                  // rows of r in the LDS that p leaves free (48 KB)
   C* const S = reinterpret_cast<C*>(tip_dyn_lds);     // [3][n]
   __shared__ double red[2][NT / 64];
+  __shared__ int s_failed;
   const uint32_t tid = threadIdx.x;
   const uint32_t n = FULL ? (uint32_t)(NT * K) : a.t.n;
   const uint32_t npad = a.t.npad;
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(NT) void k_resident_cov(const ResArgs a) {
   for (int sys = blockIdx.x; sys < a.nsys; sys += gridDim.x) {
     double* const oo = a.out + 4 * (size_t)sys;
     int* const oi = a.outi + 3 * (size_t)sys;
-    if (__hip_atomic_load(a.first_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < sys) {
+    if (wg_failed_before<NT>(a.first_failed, sys, &s_failed)) {
       if (tid == 0) oi[0] = kPadding, oi[1] = 0, oi[2] = 0;
       continue;
     }

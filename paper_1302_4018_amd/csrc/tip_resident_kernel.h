@@ -34,6 +34,7 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
   constexpr int RL = K >= 32 ? 7 : 0;                 // rows of r in the LDS that p leaves free (28 KB)
   double* S = reinterpret_cast<double*>(tip_dyn_lds);
   __shared__ double red[2][NT / 64];
+  __shared__ int s_failed;
   const uint32_t tid = threadIdx.x;
   const uint32_t n = FULL ? (uint32_t)(NT * K) : a.t.n;
   const uint32_t npad = FULL ? (uint32_t)((NT * K + 2047) & ~2047) : a.t.npad;
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(NT) void k_resident(const ResArgs a) {
   for (int sys = blockIdx.x; sys < a.nsys; sys += gridDim.x) {
     double* const oo = a.out + 3 * (size_t)sys;
     int* const oi = a.outi + 3 * (size_t)sys;
-    if (__hip_atomic_load(a.first_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < sys) {
+    if (wg_failed_before<NT>(a.first_failed, sys, &s_failed)) {
       if (tid == 0) oi[0] = kPadding, oi[1] = 0, oi[2] = 0;
       continue;
     }

@@ -66,7 +66,10 @@ def test_gradient_of_a_failed_run_leaves_nothing_queued(dims, kind, resident, mo
         assert stream.query(), "work left on the caller's stream"
 
 
-@pytest.mark.parametrize("dims,kind,n", [([9, 7, 15], 0, 945), ([12, 5, 8], 0, 480)])
+@pytest.mark.parametrize("dims,kind,n", [([9, 7, 15], 0, 945), ([12, 5, 8], 0, 480),
+                                         # one, four and eight waves a system
+                                         ([16, 16], 0, 256), ([8, 16, 16], 0, 1500), ([16, 16, 16], 0, 800),
+                                         ([4, 4, 4, 8], 1, 200), ([8, 8, 8, 8], 1, 160)])
 @pytest.mark.parametrize("broken", [False, True])
 def test_failure_is_the_first_in_probe_order(dims, kind, n, broken, monkeypatch):
     """More systems than run at once, some of them stopped at the iteration that
