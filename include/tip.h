@@ -337,18 +337,23 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
                            double* x_out, double* q_out, tip_stats* stats);
 
 /* y = A x for nrhs vectors.  x, y: DEVICE [nrhs][V][ncomp] complex128 for the
- * covariant operator, [nrhs][V] float64 for the scalar one. */
+ * covariant operator, [nrhs][V] float64 for the scalar one.  y may overlap x (the
+ * vectors are then taken in order, each read before its result is written) and
+ * the operator's arrays, which are read as they are when the call begins. */
 tip_status tip_apply_operator(const tip_operator* op, int32_t nrhs,
                               const double* x, double* y, void* stream);
 
 /* tip_apply_operator for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same kernels and arithmetic (results equal bit for bit),
- * with the caller's arrays read in place.  Only an input that overlaps the
- * output is copied first, into a fixed device array of the library, 64 MiB per
- * GPU, held until the process ends.  No hipMalloc, hipFree or allocating
- * library routine is called; the first call on a device also resolves the
- * array's device address there (hipGetSymbolAddress) when it is needed.
+ * with the caller's arrays read in place.  Only what overlaps the output goes
+ * through a fixed device array of the library, 64 MiB per GPU, held until the
+ * process ends: links and input vectors are copied there first; where y
+ * overlaps the mass field or the couplings, results are made there and copied to
+ * y one vector after another, and a later vector sees what they left of those
+ * two.  No hipMalloc, hipFree or allocating library routine is called; the first
+ * call on a device also resolves the array's device address there
+ * (hipGetSymbolAddress) when it is needed.
  * Lattices past a limit that does not depend on it, 64 MiB for (ndim * 9 * V * 16 bytes of links for the
  * covariant operator plus two vectors of ncomp * V elements, each part
  * rounded up to 256 bytes) fail with TIP_EINVAL before any device work.

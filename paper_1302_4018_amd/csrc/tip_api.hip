@@ -2774,8 +2774,9 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
 
 // y = A x (tip_apply_operator, tip_apply_operator_noalloc).  The kernel reads
 // and writes the caller's arrays in place, one launch for all right-hand
-// sides; where x and y overlap each input vector is copied to `stage` first,
-// one right-hand side after another.
+// sides.  With a stage_in or stage_out the right-hand sides go one after
+// another, each input copied to stage_in first, each output written to stage_out
+// and copied to y: for arrays that overlap y.
 tip_status validate_apply(const tip_operator* op, int32_t nrhs, const double* x, const double* y, Geom* g) {
   tip_status s = validate_op(op, g);
   if (s != TIP_OK) return s;
@@ -2786,25 +2787,46 @@ tip_status validate_apply(const tip_operator* op, int32_t nrhs, const double* x,
 size_t apply_bytes(const Geom& g) {                      // one vector
   return (size_t)g.ncomp * g.V * (g.ncomp == 3 ? sizeof(double2) : sizeof(double));
 }
-bool apply_overlaps(const Geom& g, int32_t nrhs, const double* x, const double* y) {
-  const uintptr_t a = (uintptr_t)x, b = (uintptr_t)y, n = (uintptr_t)nrhs * apply_bytes(g);
-  return a < b + n && b < a + n;
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+  return a && p < q + nb && q < p + na;
 }
-tip_status run_apply(const tip_operator* op, const Geom& g, int32_t nrhs, const double* x, double* y, void* stage,
-                     hipStream_t st) {
+// What y overlaps: the input vectors and the operator's arrays, of which y may
+// be a part as of any other memory.
+struct ApplyOverlap {
+  bool x, mass_field, coupling, links;
+  size_t mass_bytes, coupling_bytes, link_bytes;
+  ApplyOverlap(const tip_operator* op, const Geom& g, int32_t nrhs, const double* x_, const double* y) {
+    const size_t n = (size_t)nrhs * apply_bytes(g), V = g.V, nd = (size_t)g.ndim;
+    mass_bytes = V * sizeof(double);
+    coupling_bytes = nd * V * sizeof(double);
+    link_bytes = op->kind == TIP_KIND_COVARIANT ? nd * 9 * V * sizeof(double2) : 0;
+    x = overlap(x_, n, y, n);
+    mass_field = overlap(op->mass_field, mass_bytes, y, n);
+    coupling = overlap(op->coupling, coupling_bytes, y, n);
+    links = link_bytes && overlap(op->links, link_bytes, y, n);
+  }
+};
+tip_status run_apply(const tip_operator* op, const Geom& g, int32_t nrhs, const double* x, double* y, void* stage_in,
+                     void* stage_out, hipStream_t st) {
   const size_t bytes = apply_bytes(g);
   auto launch = [&](int n, const void* in, void* out) {
     return launch_apply(g, op->kind, n, op->mass_field, op->mass, op->coupling, op->links, in, out, st);
   };
-  if (!apply_overlaps(g, nrhs, x, y)) {
+  auto copy = [&](void* to, const void* from) { return hipMemcpyAsync(to, from, bytes, hipMemcpyDeviceToDevice, st); };
+  if (!stage_in && !stage_out) {
     if (launch(nrhs, x, y) != hipSuccess) return fail(TIP_EDEVICE, "apply launch failed");
   } else {
-    for (int32_t k = 0; k < nrhs; ++k)
-      if (hipMemcpyAsync(stage, (const char*)x + k * bytes, bytes, hipMemcpyDeviceToDevice, st) != hipSuccess ||
-          launch(1, stage, (char*)y + k * bytes) != hipSuccess) {
-        (void)hipStreamSynchronize(st);                  // stage goes when this returns
+    for (int32_t k = 0; k < nrhs; ++k) {
+      const char* const xk = (const char*)x + k * bytes;
+      char* const yk = (char*)y + k * bytes;
+      if ((stage_in && copy(stage_in, xk) != hipSuccess) ||
+          launch(1, stage_in ? stage_in : xk, stage_out ? stage_out : yk) != hipSuccess ||
+          (stage_out && copy(yk, stage_out) != hipSuccess)) {
+        (void)hipStreamSynchronize(st);                  // the stages go when this returns
         return fail(TIP_EDEVICE, "apply launch failed");
       }
+    }
   }
   if (hipStreamSynchronize(st) != hipSuccess) return fail(TIP_EDEVICE, "apply failed on the device");
   return TIP_OK;
@@ -3024,20 +3046,37 @@ tip_status tip_apply_operator(const tip_operator* op, int32_t nrhs, const double
   Geom g;
   tip_status s = validate_apply(op, nrhs, x, y, &g);
   if (s != TIP_OK) return s;
-  DevBuf stage;
-  if (apply_overlaps(g, nrhs, x, y)) {
+  // arrays of the operator that y overlaps are copied: A is the operator of the
+  // call's beginning for every right-hand side
+  const ApplyOverlap ov(op, g, nrhs, x, y);
+  const hipStream_t st = (hipStream_t)stream;
+  if (!ov.x && !ov.mass_field && !ov.coupling && !ov.links) return run_apply(op, g, nrhs, x, y, nullptr, nullptr, st);
+  tip_operator o = *op;
+  DevBuf stage, kept[3];
+  const StreamWait wait{st};
+  if (ov.x)
     if (const hipError_t e_ = stage.ensure(apply_bytes(g)); e_ != hipSuccess)
       return fail(TIP_ENOMEM, "hipMalloc apply buffer: %s", hipGetErrorString(e_));
-  }
-  return run_apply(op, g, nrhs, x, y, stage.p, (hipStream_t)stream);
+  auto keep = [&](bool any, DevBuf& buf, const double*& a, size_t n) -> tip_status {
+    if (!any) return TIP_OK;
+    if (const hipError_t e_ = buf.ensure(n); e_ != hipSuccess)
+      return fail(TIP_ENOMEM, "hipMalloc apply buffer: %s", hipGetErrorString(e_));
+    TIP_HIP(hipMemcpyAsync(buf.p, a, n, hipMemcpyDeviceToDevice, st));
+    a = (const double*)buf.p;
+    return TIP_OK;
+  };
+  s = keep(ov.mass_field, kept[0], o.mass_field, ov.mass_bytes);
+  if (s == TIP_OK) s = keep(ov.coupling, kept[1], o.coupling, ov.coupling_bytes);
+  if (s == TIP_OK) s = keep(ov.links, kept[2], o.links, ov.link_bytes);
+  if (s != TIP_OK) return s;
+  return run_apply(&o, g, nrhs, x, y, stage.p, nullptr, st);
 }
 
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// Operator application without allocation.  An input that overlaps the
-// output is copied to `scratch` first, a file-scope
-// device array of kScratchBytes: every GPU the library runs on holds its own
+// Operator application without allocation.  What overlaps the output goes
+// through `scratch`, a file-scope device array of kScratchBytes: every GPU the library runs on holds its own
 // copy until the process ends, and calls on one GPU share it (overlapping
 // calls on one GPU race).  In host code the array's name is only a stand-in
 // for the variable; its device address is taken once per device with
@@ -3087,19 +3126,29 @@ tip_status tip_apply_operator_noalloc(const tip_operator* op, int32_t nrhs, cons
   tip_status s = validate_apply(op, nrhs, x, y, &g);
   if (s != TIP_OK) return s;
   // lattices are accepted up to the size whose links and two vectors fit the
-  // scratch; only an input that overlaps the output uses it
+  // scratch; only arrays that overlap the output use it: links are copied to it,
+  // an input vector is copied first, and with a mass field or couplings in the
+  // output's place a result is made there and copied (so a later right-hand side
+  // sees what earlier results left of these two)
+  const ApplyOverlap ov(op, g, nrhs, x, y);
   const size_t bytes = apply_bytes(g);
-  const size_t link_bytes = op->kind == TIP_KIND_COVARIANT ? (size_t)g.ndim * 9 * g.V * sizeof(double2) : 0;
-  const size_t need = align256(link_bytes) + 2 * align256(bytes);
+  const size_t need = align256(ov.link_bytes) + 2 * align256(bytes);
   if (need > kScratchBytes)
     return fail(TIP_EINVAL, "lattice needs %zu bytes of workspace; the no-allocation scratch holds %zu", need,
                 kScratchBytes);
-  void* stage = nullptr;
-  if (apply_overlaps(g, nrhs, x, y)) {
-    s = scratch_address(&stage);
-    if (s != TIP_OK) return s;
+  const bool fields = ov.mass_field || ov.coupling;
+  if (!ov.x && !fields && !ov.links) return run_apply(op, g, nrhs, x, y, nullptr, nullptr, (hipStream_t)stream);
+  void* base = nullptr;
+  s = scratch_address(&base);
+  if (s != TIP_OK) return s;
+  char* const in = (char*)base + align256(ov.link_bytes);
+  tip_operator o = *op;
+  if (ov.links) {
+    TIP_HIP(hipMemcpyAsync(base, op->links, ov.link_bytes, hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    o.links = (const double*)base;
   }
-  return run_apply(op, g, nrhs, x, y, stage, (hipStream_t)stream);
+  return run_apply(&o, g, nrhs, x, y, ov.x ? in : nullptr, fields ? in + align256(bytes) : nullptr,
+                   (hipStream_t)stream);
 }
 
 tip_status tip_hier_perm(int32_t ndim, const int64_t* dims, uint32_t* P_out, void* stream) {

@@ -98,3 +98,39 @@ def test_failure_is_the_first_in_probe_order(dims, kind, n, broken, monkeypatch)
             assert len(est) == (bad.bit_length() if bad else 0)        # checkpoints 1, 2, 4, .. up to bad probes
             assert not np.isnan(st["residuals"][:bad]).any() and np.isnan(st["residuals"][bad]).any()
         assert checked
+
+
+@pytest.mark.parametrize("kind,nrhs", [(0, 1), (0, 5), (1, 1), (1, 5)])
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("array", ["mass_field", "coupling", "links"])
+def test_output_may_overlap_the_operators_arrays(array, noalloc, kind, nrhs):
+    """y lies over the beginning of one of them, which the call reads as it was.
+    Without allocation a later vector sees a mass field or couplings that earlier
+    results have overwritten, so there one vector."""
+    import ctypes
+    tip = gpu_binding()
+    if array == "links" and kind == 0:
+        pytest.skip("no links")
+    if noalloc and array != "links":
+        nrhs = 1
+    orc, gop = _op(tip, [7, 6, 10], kind, 950)
+    src = getattr(gop, array)
+    rng = np.random.default_rng(951)
+    shape = (nrhs, orc.V, 3) if kind else (nrhs, orc.V)
+    x = rng.standard_normal(shape) + (1j * rng.standard_normal(shape) if kind else 0.0)
+    xd = to_dev(x)
+    flat = src.reshape(-1) if not src.is_complex() else torch.view_as_real(src).reshape(-1)
+    n = x.size * (2 if kind else 1)
+    mem = torch.zeros(max(n, flat.numel()), dtype=torch.float64, device="cuda")
+    mem[:flat.numel()] = flat
+    s = gop.c_struct()
+    setattr(s, array, mem.data_ptr())
+    fn = tip.lib.tip_apply_operator_noalloc if noalloc else tip.lib.tip_apply_operator
+    torch.cuda.synchronize()
+    assert fn(ctypes.byref(s), nrhs, ctypes.c_void_p(xd.data_ptr()), ctypes.c_void_p(mem.data_ptr()), None) == tip.TIP_OK
+    y = mem[:n].cpu().numpy()
+    y = (y.view(np.complex128) if kind else y).reshape(shape)
+    for j in range(nrhs):
+        want = orc.apply(x[j])
+        # at most 2 (2 ndim + 1) products of 3 terms per component, each rounded once
+        assert np.abs(y[j] - want).max() <= 64 * 2.0 ** -53 * 16 * np.abs(x[j]).max() * 3, j
