@@ -1493,6 +1493,9 @@ tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std:
   *stalled = 0;
   *out = (double*)(hb + tab + 64);
   *outi = (int*)(*out + 3 * nj);
+  // another limit of the kernel's waits (TIP_CLUSTER_POLLS), for tests
+  int polls = kClPolls;
+  if (const char* e = std::getenv("TIP_CLUSTER_POLLS")) polls = std::max(1, std::atoi(e));
   char* db = (char*)dev.p;
   TIP_HIP(hipMemcpyAsync(db, hb, tab, hipMemcpyHostToDevice, st));
   *xout = x_bytes ? (double*)(db + o_x) : nullptr;
@@ -1519,6 +1522,7 @@ tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std:
     a.outi = *outi;
     a.skip = skip ? 1 : 0;
     a.stalled = stalled;
+    a.polls = polls;
     TIP_HIP(launch_cl_reset(a.words, team_words(l, nt) + halo_words(l, nt), a.queue, st));
     TIP_HIP(launch_cluster(l.ndim, a, l.rows, l.weighted, st));
   }

@@ -54,7 +54,7 @@ struct ClArgs {
   uint32_t Amax;                 // widest plane of the launch
   double* ws;                    // per workgroup: b, ws_rows values
   size_t ws_rows;
-  unsigned long long* words;     // per team: two buffers of T sums and of T pairs of counters, the packet
+  unsigned long long* words;     // per team: two buffers of T sums and of T pairs of counters, the packet, T beats
   unsigned long long* halo;      // per workgroup [2][2][2][Amax]
   double* xout;                  // or null
   double* out;                   // [jobs][3]: quadrature, ||b - A x||^2, ||b||^2
@@ -62,8 +62,10 @@ struct ClArgs {
   int* queue;                    // [0] next packet, [1] lowest failed job (packets above it may be skipped)
   int skip;                      // whether they are: jobs are in the order of their probes then
   int* stalled;                  // host memory: set when a wait ran into its limit
+  int polls;                     // the limit
 };
-__host__ __device__ inline size_t cl_team_words(int T) { return (size_t)T * 8 + 1; }
+__host__ __device__ inline size_t cl_team_words(int T) { return (size_t)T * 9 + 1; }
+constexpr int kClPolls = 1 << 22;            // some seconds
 
 // Team and place in it of workgroup b.  Workgroups go round robin over the XCDs
 // (b mod 8), each with its own L2: the workgroups in one place of their teams,

@@ -34,26 +34,39 @@ __device__ __forceinline__ void put_double(unsigned long long* w, size_t hi, dou
   put_word(w, (uint32_t)__double2loint(v), tag);
   put_word(w + hi, (uint32_t)__double2hiint(v), tag);
 }
-// Waits for the word's tag, at most kClPolls polls and not past another
-// thread's stall: every wait ends.
-constexpr int kClPolls = 1 << 22;
-__device__ __forceinline__ bool get_word(const unsigned long long* w, uint32_t tag, int* stalled, uint32_t& v) {
-  for (int n = 0; n < kClPolls; ++n) {
+// Waits for the word's tag, at most `polls` polls and not past another
+// thread's stall.  A word whose writer may be in the middle of a solve comes with
+// the writer's beat: the count starts again whenever that has changed.  A solve
+// makes at most max_iter iterations, so every wait ends.
+__device__ __forceinline__ bool get_word(const unsigned long long* w, uint32_t tag, int* stalled, int polls,
+                                         const unsigned long long* beat, uint32_t& v) {
+  unsigned long long seen = 0;
+  for (int n = 0;;) {
     const unsigned long long x = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     v = (uint32_t)x;
     if ((uint32_t)(x >> 32) == tag) return true;
-    if ((n & 1023) == 1023 && __hip_atomic_load(stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) return false;
+    const bool last = ++n >= polls;
+    if (!last && (n & 1023) != 0) continue;
+    if (__hip_atomic_load(stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) return false;
+    const unsigned long long b = beat ? __hip_atomic_load(beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    if (b != seen) {
+      seen = b;
+      n = 0;
+    } else if (last) {
+      break;
+    }
   }
   __hip_atomic_store(stalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   return false;
 }
+constexpr int kClBeat = 64;                  // iterations between a workgroup's beats, 2 ms at the most
 // M numbers at once, word i at w(i) and w(i) + hi where want(i): every word is
 // asked for before any is waited for, so that M numbers cost one trip to
 // memory, not 2 M.  NaN when the wait ran into its limit; the solve then ends as
 // a breakdown.
 template <int M, class Want, class At>
-__device__ __forceinline__ void get_doubles(size_t hi, uint32_t tag, int* stalled, double (&out)[M], Want&& want,
-                                            At&& w) {
+__device__ __forceinline__ void get_doubles(size_t hi, uint32_t tag, int* stalled, int polls, double (&out)[M],
+                                            Want&& want, At&& w) {
   bool got[M];
 #pragma unroll
   for (int i = 0; i < M; ++i) {
@@ -77,7 +90,7 @@ __device__ __forceinline__ void get_doubles(size_t hi, uint32_t tag, int* stalle
         all = all && got[i];
       }
     if (all) return;
-    const bool last = n >= kClPolls;
+    const bool last = n >= polls;
     if (last) __hip_atomic_store(stalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (last || ((n & 1023) == 1023 && __hip_atomic_load(stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))) {
 #pragma unroll
@@ -105,8 +118,10 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
   double* const bw = a.ws + (size_t)blockIdx.x * a.ws_rows;
   unsigned long long* const words = a.words + (size_t)team * cl_team_words(T);
   unsigned long long* const packet_word = words + 8 * T;
+  unsigned long long* const beats = packet_word + 1;
   auto halo_of = [&](int m) { return a.halo + ((size_t)m * a.nteams + team) * 8 * (size_t)a.Amax; };
   uint32_t sum_tag = 0, halo_tag = 0, packet_tag = 0;
+  unsigned long long beat = 0;
 
   for (;;) {
     // the next packet, taken by the team's first workgroup.  The clusters of the
@@ -122,8 +137,10 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         put_word(counters + 2 * mate + 1, halo_tag, packet_tag);
         for (int m = 0; m < T; ++m) {
           uint32_t v = 0, u = 0;
-          if (!get_word(counters + 2 * m, packet_tag, a.stalled, v) ||
-              !get_word(counters + 2 * m + 1, packet_tag, a.stalled, u))
+          // workgroups without a system in a packet, or done with theirs, wait here
+          // for whole solves
+          if (!get_word(counters + 2 * m, packet_tag, a.stalled, a.polls, beats + m, v) ||
+              !get_word(counters + 2 * m + 1, packet_tag, a.stalled, a.polls, beats + m, u))
             break;
           hi = v > hi ? v : hi;
           hh = u > hh ? u : hh;
@@ -141,7 +158,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
           }
         }
         if (T > 1) put_word(packet_word, j, packet_tag);
-      } else if (!get_word(packet_word, packet_tag, a.stalled, j)) {
+      } else if (!get_word(packet_word, packet_tag, a.stalled, a.polls, nullptr, j)) {
         j = (uint32_t)a.npackets;
       }
       if (T > 1 && __hip_atomic_load(a.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) j = (uint32_t)a.npackets;
@@ -174,7 +191,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
       if (tid == 0) put_double(w + 2 * member, 1, mine, sum_tag);
       const int l = (int)(tid & 63);
       double part[1];
-      get_doubles<1>(1, sum_tag, a.stalled, part, [&](int) { return l < G; }, [&](int) { return w + 2 * l; });
+      get_doubles<1>(1, sum_tag, a.stalled, a.polls, part, [&](int) { return l < G; }, [&](int) { return w + 2 * l; });
       return wave_total(part[0]);
     };
     const ClJob J = a.jobs[job];
@@ -279,7 +296,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
           for (int j = 0; j < M; ++j)
             if (at(j) < 2 * A) v[j] = at(j) >= A ? P[at(j) - A] : P[n - A + at(j)];
         } else {
-          get_doubles<M>(a.Amax, halo_tag, a.stalled, v, [&](int j) { return at(j) < 2 * A; },
+          get_doubles<M>(a.Amax, halo_tag, a.stalled, a.polls, v, [&](int j) { return at(j) < 2 * A; },
                          [&](int j) {
                            const bool up = at(j) >= A;
                            return (up ? halo_up : halo_dn) + ((size_t)(halo_tag & 1) * 2 + (up ? 0 : 1)) * 2 * a.Amax +
@@ -350,6 +367,8 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         });
         const double rho_new = total(acc, red[1]);
         ++it;
+        if (tid == 0 && G < T && it % kClBeat == 0)
+          __hip_atomic_store(beats + mate, ++beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (!isfinite(rho_new)) state = kBreakdown;
         else if (rho_new <= (restarts == 0 ? freeze2 : tol2) * bnorm2) state = kFrozen;
         else if (it >= max_iter) state = kNoConv;

@@ -9,7 +9,7 @@ import torch
 from conftest import gpu_binding, to_dev
 from oracle.mask import MASK_Z2, MASK_Z4
 from oracle.operators import Operator as OracleOp
-from oracle.general import rhs
+from oracle.general import rhs, trace_inv_probe as oracle_trace
 from paper_1302_4018_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -134,3 +134,25 @@ def test_output_may_overlap_the_operators_arrays(array, noalloc, kind, nrhs):
         want = orc.apply(x[j])
         # at most 2 (2 ndim + 1) products of 3 terms per component, each rounded once
         assert np.abs(y[j] - want).max() <= 64 * 2.0 ** -53 * 16 * np.abs(x[j]).max() * 3, j
+
+
+def test_a_long_solve_in_a_batch_outlasts_no_wait(monkeypatch):
+    """Clusters without a system wait for the whole solve of their team's others,
+    here many times the limit that a single exchange has; the solve runs to
+    max_iter and is reported as such, the other problems are whole."""
+    tip = gpu_binding()
+    dims = [9, 7, 15]
+    rng = np.random.default_rng(960)
+    w = 10.0 ** rng.uniform(-6, 6, size=(3, 945))
+    hard = tip.Operator(dims, 0, mass=1e-9, coupling=to_dev(w))
+    orc, easy = _op(tip, [7, 6, 11], 0, 961)
+    ns = [2, 1, 6]
+    tip.trace_inv_probe_batch([easy] * 3, ns, 1e-11, 4018, mask=MASK_Z2)                   # the kernel is on the device
+    monkeypatch.setenv("TIP_CLUSTER_POLLS", "2048")
+    out = tip.trace_inv_probe_batch([easy, hard, easy], ns, 1e-11, 4018, mask=MASK_Z2, max_iter=4000,
+                                    raise_on_error=False)
+    assert [st["status"] for _, st in out] == [tip.TIP_OK, tip.TIP_ENOCONV, tip.TIP_OK], tip.tip_last_error()
+    assert out[1][1]["max_iters"] == 4000
+    for k in (0, 2):
+        q_o = oracle_trace(orc, ns[k], 1e-11, 4018, MASK_Z2)[1]
+        assert np.max(np.abs(out[k][1]["quadratures"] - q_o) / np.abs(q_o)) <= 1e-10
