@@ -1454,11 +1454,14 @@ struct ClusterLaunch {
 // Runs the launches one after another on st and waits for them.  host holds
 // the tables on their way to the device and the results (out, outi); dev the
 // tables, the exchange words and the vectors.  xout: solutions, or null.
+// gave_up: set when the workgroups of a cluster could not run together, because
+// something else held CUs for longer than their waits last; the call then takes
+// the block solver, whose workgroups wait for nobody.
 tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std::vector<ClProblem>& probs,
                        const std::vector<ClJob>& jobs, const std::vector<ClPacket>& packets,
                        const std::vector<ClusterLaunch>& launches, bool skip,
                        size_t x_bytes, int logB, hipEvent_t ev0, hipEvent_t ev1, double** out, int** outi,
-                       double** xout) {
+                       double** xout, bool* gave_up) {
   int devid = 0, cus = 0;
   TIP_HIP(hipGetDevice(&devid));
   TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, devid));
@@ -1524,11 +1527,19 @@ tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std:
     a.stalled = stalled;
     a.polls = polls;
     TIP_HIP(launch_cl_reset(a.words, team_words(l, nt) + halo_words(l, nt), a.queue, st));
-    TIP_HIP(launch_cluster(l.ndim, a, l.rows, l.weighted, st));
+    if (const hipError_t e = launch_cluster(l.ndim, a, l.rows, l.weighted, st); e != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipStreamSynchronize(st);
+      *gave_up = true;
+      return fail(TIP_EDEVICE, "cluster launch failed: %s", hipGetErrorString(e));
+    }
   }
   if (ev1) TIP_HIP(hipEventRecord(ev1, st));
   TIP_HIP(hipStreamSynchronize(st));
-  if (*stalled) return fail(TIP_EDEVICE, "a workgroup waited too long for its cluster");
+  if (*stalled) {
+    *gave_up = true;
+    return fail(TIP_EDEVICE, "a workgroup waited too long for its cluster");
+  }
   return TIP_OK;
 }
 
@@ -1549,6 +1560,7 @@ struct ResidentRun {
   Geom geom;                     // with the call's probe kind and class
   hipStream_t st = nullptr;
   Elem elem = Elem::kReal;
+  bool gave_up = false;          // run failed as run_cluster describes
   int64_t launches = 0, matvecs = 0, restarts = 0;
   double seconds = 0.0, bytes = 0.0, op_bytes = 0.0;
 
@@ -1733,7 +1745,7 @@ struct ResidentRun {
     double* o = nullptr;
     int* oi = nullptr;
     tip_status s = run_cluster(h->vec, h->host, st, probs, jobs, packets, launches, true, x_bytes, logB, ev[0], ev[1],
-                               &o, &oi, x);
+                               &o, &oi, x, &gave_up);
     *out = o;
     *outi = oi;
     return s;
@@ -2013,16 +2025,20 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
       if (grad_coupling) TIP_HIP(launch_fill((size_t)gg.ndim * V, grad_coupling, 0.0, st));
       return TIP_OK;
     };
-    if (res >= 0) {
+    bool lds = res >= 0;
+    if (lds) {
       ResidentRun rs;
       s = rs.setup(h, p, mask, res, -1);
       queued.on(rs.st);
       if (s == TIP_OK) s = clear(rs.st);
       if (s == TIP_OK)
         s = run_resident(base, base + n_rhs, 0, 0, false, rs, [&](int, int64_t r) { return slot(r); });
-      if (s != TIP_OK) return s;
-      add_stats(rs);
-    } else {
+      if (s != TIP_OK && !rs.gave_up) return s;
+      if (s == TIP_OK) add_stats(rs);
+      lds = s == TIP_OK;
+    }
+    if (!lds) {
+      rr = RunResult(n_rhs);
       Solver sv;
       sv.need_x = want_grad;
       s = sv.setup(h, p, mask);
@@ -2051,14 +2067,18 @@ tip_status run_probe(tip_op_handle h, const tip_params* p, double* estimates, do
       const int64_t m = (int64_t)class_probe((uint64_t)(r / ncomp), cg[c]);
       return (size_t)((m - p->m_begin) * ncomp + r % ncomp);
     };
-    if (res >= 0) {
+    bool lds = res >= 0;
+    if (lds) {
       ResidentRun rs;
       s = rs.setup(h, p, mask, res, 0);
       queued.on(rs.st);
       if (s == TIP_OK) s = run_resident(i0[0], i1[0], i0[1], i1[1], true, rs, slot);
-      if (s != TIP_OK) return s;
-      add_stats(rs);
-    } else {
+      if (s != TIP_OK && !rs.gave_up) return s;
+      if (s == TIP_OK) add_stats(rs);
+      lds = s == TIP_OK;
+    }
+    if (!lds) {
+      rr = RunResult(n_rhs);
       for (int c = 0; c < 2; ++c) {
         failed = false;
         if (i0[c] >= i1[c]) continue;
@@ -2142,7 +2162,7 @@ struct BatchClass {
 // launch takes the largest clusters first, and among them the longest solves.
 tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>>& hs, const tip_params* params,
                           const std::vector<int>& masks, const std::vector<char>& clustered, hipStream_t st,
-                          std::vector<RunResult>& results) {
+                          std::vector<RunResult>& results, bool* gave_up) {
   struct System {
     int prob, part, parts;
     int64_t m;
@@ -2244,7 +2264,8 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
     for (hipEvent_t& e : ev) TIP_HIP(hipEventCreate(&e));
   double *out = nullptr, *x = nullptr;
   int* outi = nullptr;
-  tip_status s = run_cluster(work, host, st, probs, jobs, packets, launches, false, 0, 0, ev[0], ev[1], &out, &outi, &x);
+  tip_status s = run_cluster(work, host, st, probs, jobs, packets, launches, false, 0, 0, ev[0], ev[1], &out, &outi, &x,
+                             gave_up);
   if (s != TIP_OK) return s;
   std::vector<double> bn2(0), rt2(0);
   for (size_t i = 0; i < results.size(); ++i)
@@ -2337,7 +2358,10 @@ tip_status run_batch(const tip_operator* ops, const tip_params* params, int32_t 
     clustered[(size_t)i] = hs[(size_t)i]->kind == TIP_KIND_SCALAR && g.ndim >= 2 && ClusterCut(g).least() > 0 &&
                            !env_off("TIP_RESIDENT");
   }
-  if (const tip_status s = batch_clusters(hs, params, masks, clustered, st, results); s != TIP_OK) return s;
+  bool gave_up = false;
+  if (const tip_status s = batch_clusters(hs, params, masks, clustered, st, results, &gave_up); s != TIP_OK && !gave_up)
+    return s;
+  if (gave_up) clustered.assign((size_t)count, 0);
   // classes of right-hand sides
   std::vector<BatchClass> classes;
   for (int32_t i = 0; i < count; ++i) {
@@ -2880,24 +2904,26 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
     // x_out is written when the call returns, and after an error nothing of it is left queued
     const hipError_t waited = hipStreamSynchronize(rs.st);
     if (s == TIP_OK && waited != hipSuccess) s = fail(TIP_EDEVICE, "solve failed: %s", hipGetErrorString(waited));
-    if (s != TIP_OK) return s;
-    if (q_out) {
-      q_out[0] = o.q;
-      q_out[1] = o.qim;
+    if (s != TIP_OK && !rs.gave_up) return s;
+    if (s == TIP_OK) {
+      if (q_out) {
+        q_out[0] = o.q;
+        q_out[1] = o.qim;
+      }
+      if (stats) {
+        std::memset(stats, 0, sizeof *stats);
+        stats->solves = 1;
+        stats->total_iters = o.iters;
+        stats->max_iters = o.iters;
+        stats->max_true_relres = o.relres;
+        stats->max_quad_err_bound = o.relres * o.relres * (double)g.V / h->lambda_lb;
+        rs.fill_stats(stats);
+        stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
+      }
+      if (o.state == kBreakdown) return fail(TIP_EBREAKDOWN, "solve broke down (p^H A p <= 0)");
+      if (o.state != kAccepted) return fail(TIP_ENOCONV, "solve did not converge within max_iter");
+      return TIP_OK;
     }
-    if (stats) {
-      std::memset(stats, 0, sizeof *stats);
-      stats->solves = 1;
-      stats->total_iters = o.iters;
-      stats->max_iters = o.iters;
-      stats->max_true_relres = o.relres;
-      stats->max_quad_err_bound = o.relres * o.relres * (double)g.V / h->lambda_lb;
-      rs.fill_stats(stats);
-      stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
-    }
-    if (o.state == kBreakdown) return fail(TIP_EBREAKDOWN, "solve broke down (p^H A p <= 0)");
-    if (o.state != kAccepted) return fail(TIP_ENOCONV, "solve did not converge within max_iter");
-    return TIP_OK;
   }
   Solver sv;
   sv.need_x = true;

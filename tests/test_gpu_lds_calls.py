@@ -156,3 +156,34 @@ def test_a_long_solve_in_a_batch_outlasts_no_wait(monkeypatch):
     for k in (0, 2):
         q_o = oracle_trace(orc, ns[k], 1e-11, 4018, MASK_Z2)[1]
         assert np.max(np.abs(out[k][1]["quadratures"] - q_o) / np.abs(q_o)) <= 1e-10
+
+
+@pytest.mark.parametrize("dims,mask", [([30, 47, 31], MASK_Z4), ([30, 47, 31], MASK_Z2)])
+def test_clusters_that_cannot_run_together_leave_the_call_to_the_block_solver(dims, mask, monkeypatch):
+    """A limit of one poll stands for CUs that something else holds: every kind of
+    call is answered all the same."""
+    tip = gpu_binding()
+    orc, gop = _op(tip, dims, 0, 970, m0=0.6)
+    n = 4
+    _, q_o, _ = oracle_trace(orc, n, 1e-11, 4018, mask)
+    with tip.OpHandle(gop) as h:
+        _, q0, st0 = h.trace_inv_probe(n, 1e-11, 4018, mask=mask)
+        _, _, gm0, gw0, _ = h.trace_inv_probe_grad(n, 1e-11, 4018, mask=mask)
+        assert st0["stencil_launches"] == 1
+        monkeypatch.setenv("TIP_CLUSTER_POLLS", "1")
+        _, q, st = h.trace_inv_probe(n, 1e-11, 4018, mask=mask)
+        _, _, gm, gw, _ = h.trace_inv_probe_grad(n, 1e-11, 4018, mask=mask)
+        x, qx, stx = h.solve_probe(0, 0, 1e-11, 4018, mask=mask)
+    assert st["stencil_launches"] > 1 and stx["stencil_launches"] > 1
+    assert st["solves"] == st0["solves"] and st["status"] == tip.TIP_OK
+    assert np.max(np.abs(q - q_o) / np.abs(q_o)) <= 1e-10
+    assert abs(qx - q_o[0]) <= 1e-10 * abs(q_o[0])
+    # two solutions of residual 1e-11 differ by at most 2e-11 sqrt(V) / min m, their squares by twice that times |x|
+    lam = float(gop.mass_field.min())
+    bound = 4 * (4e-11 * np.sqrt(orc.V) / lam) * np.sqrt(float(gm0.abs().max())) + 1e-20
+    assert float((gm - gm0).abs().max()) <= bound and float((gw - gw0).abs().max()) <= 4 * bound
+    # the batch's block solver counts its launches only while it times them: none in LDS
+    out = tip.trace_inv_probe_batch([gop, gop], [n, 2], 1e-11, 4018, mask=mask)
+    for (_, s), k in zip(out, (n, 2)):
+        assert s["status"] == tip.TIP_OK and s["stencil_launches"] == 0
+        assert np.max(np.abs(s["quadratures"] - q_o[:k]) / np.abs(q_o[:k])) <= 1e-10
