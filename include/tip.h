@@ -328,8 +328,9 @@ tip_status trace_inv_probe_grad(tip_op_handle h, const tip_params* p, double* es
 /* One solve A x = b_{m,comp} on a prepared handle, for checks of the solver
  * and for callers that need the solution itself.  Uses tol, max_iter, seed,
  * mask, precision and stream of p; its probe-count fields and rhs_block are
- * ignored: the solve runs in a block of the library's default size, so it
- * repeats the arithmetic of trace_inv_probe for this right-hand side.
+ * ignored: the solve runs as the library's default launch shape has it, so it
+ * repeats the arithmetic of trace_inv_probe for this right-hand side (but for
+ * runs that reuse conjugate F_3 columns, whose shapes follow their counts).
  * x_out: DEVICE, [V][ncomp] complex128 when the solve is complex (covariant
  * operator, or Z4 mask), else [V] float64.  q_out: HOST [2] = b^H x, or NULL.
  * stats may be NULL.  Status as trace_inv_probe for a single solve. */

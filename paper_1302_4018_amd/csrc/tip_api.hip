@@ -1737,8 +1737,15 @@ struct ResidentRun {
     // a job that fails lets the launch skip those behind it: behind it in the
     // order of probes, whichever class they are of, as the checkpoints stop there
     if (cls) std::stable_sort(jobs.begin(), jobs.end(), [](const ClJob& a, const ClJob& b) { return a.m < b.m; });
+    // Sums depend on the cut, so G depends on the operator alone: a right-hand
+    // side is solved with the same arithmetic in a long run, a resumed one and
+    // by itself.  The least G is the one for many systems (512 of 48^3: 55 ms, 79
+    // with twice the CUs each; of 21x34x15: 2.5 ms, 4.6) and costs few at the
+    // most 1.8 times the best (one of 48^3: 3.2 ms against 1.9; 32 of 21x34x15:
+    // 1.11 against 0.97).  The probe classes follow the number of systems, as
+    // their blocks do.
     const ClusterCut cut(geom);
-    const int G = cut.pick(nsys, cus);
+    const int G = cls ? cut.pick(nsys, cus) : cut.least();
     std::vector<ClPacket> packets((size_t)nsys);
     for (int i = 0; i < nsys; ++i) packets[(size_t)i] = ClPacket{i, 1, G};
     const std::vector<ClusterLaunch> launches{{geom.ndim, h->has_coupling, G, cut.rows(G), cut.A, 0, nsys}};

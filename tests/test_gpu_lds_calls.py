@@ -187,3 +187,19 @@ def test_clusters_that_cannot_run_together_leave_the_call_to_the_block_solver(di
     for (_, s), k in zip(out, (n, 2)):
         assert s["status"] == tip.TIP_OK and s["stencil_launches"] == 0
         assert np.max(np.abs(s["quadratures"] - q_o[:k]) / np.abs(q_o[:k])) <= 1e-10
+
+
+@pytest.mark.parametrize("dims,n", [([21, 34, 15], 80), ([12000, 1], 60), ([12, 48, 48], 20)])
+def test_arithmetic_of_a_right_hand_side_does_not_depend_on_its_run(dims, n):
+    """A whole run, a resumed one and single solves of a lattice that more CUs
+    would take when few systems are solved: the same quadratures bit for bit."""
+    tip = gpu_binding()
+    _, gop = _op(tip, dims, 0, 980, m0=0.5)
+    with tip.OpHandle(gop) as h:
+        _, q, st = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z4)
+        assert st["stencil_launches"] == 1, "not solved in LDS"
+        _, half, _ = h.trace_inv_probe(n // 2, 1e-10, 4018, mask=MASK_Z4)
+        _, rest, _ = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z4, m_begin=n // 2, quadratures=half)
+        assert np.array_equal(half, q[:n // 2]) and np.array_equal(rest, q)
+        for m in (0, 1, n - 1):
+            assert h.solve_probe(m, 0, 1e-10, 4018, mask=MASK_Z4)[1] == q[m], m
