@@ -1438,7 +1438,7 @@ ClProblem cluster_problem(const tip_op_s* h, const tip_params* p, int mask, cons
   pr.start_frozen = p->tol >= 1.0 ? 1 : 0;
   pr.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)geom.V, 1 << 20);
   pr.max_restarts = 8;
-  pr.variational = p->precision == TIP_PREC_MIXED ? 1 : 0;
+  pr.mixed = p->precision == TIP_PREC_MIXED ? 1 : 0;
   return pr;
 }
 

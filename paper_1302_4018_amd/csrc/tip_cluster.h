@@ -25,7 +25,8 @@ struct ClProblem {
   double tol2, freeze2;
   uint64_t seed;
   int mask, start_frozen, max_iter, max_restarts, force_iter;
-  int variational;               // report b . x + x . r instead of b . x
+  int mixed;                     // what mixed precision promises: the quadrature b . x + x . r instead of b . x, and
+                                 // restarts in place of breakdowns
   uint32_t A, nz;
 };
 constexpr uint32_t kClPad = 2048;

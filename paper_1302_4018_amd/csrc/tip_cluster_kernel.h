@@ -204,6 +204,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
     // in scalar registers: read where they are used, each would cost a trip to
     // memory between the sums of every iteration
     const double tol2 = scalar(pr.tol2), freeze2 = scalar(pr.freeze2);
+    const bool mixed = scalar((uint32_t)pr.mixed) != 0;
     const int max_iter = (int)scalar((uint32_t)pr.max_iter), force_iter = (int)scalar((uint32_t)pr.force_iter);
     const uint32_t* const t_nbr = scalar(pr.nbr) + s0;
     const Double2* const t_wgt = scalar(reinterpret_cast<const Double2*>(pr.wgt)) + s0;
@@ -351,7 +352,9 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         });
         const double pAp = total(acc, red[0]);
         if (!(pAp > 0.0) || !isfinite(pAp) || (force_iter > 0 && restarts == 0 && it + 1 == force_iter)) {
-          state = kBreakdown;
+          // asked for in mixed precision: no breakdown, but a restart from the FP64
+          // residual, as the single-precision passes make of it
+          state = mixed ? kFrozen : kBreakdown;
           break;
         }
         const double alpha = rho / pAp;
@@ -404,7 +407,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         a2 = fma(xk, r[k], a2);
       });
       rt2 = total(a0, red[0]);
-      q = total(pr.variational ? a1 + a2 : a1, red[1]);
+      q = total(mixed ? a1 + a2 : a1, red[1]);
       if (rt2 <= tol2 * bnorm2) {
         state = kAccepted;
         break;

@@ -203,3 +203,28 @@ def test_arithmetic_of_a_right_hand_side_does_not_depend_on_its_run(dims, n):
         assert np.array_equal(half, q[:n // 2]) and np.array_equal(rest, q)
         for m in (0, 1, n - 1):
             assert h.solve_probe(m, 0, 1e-10, 4018, mask=MASK_Z4)[1] == q[m], m
+
+
+@pytest.mark.parametrize("resident", ["1", "0"])
+def test_mixed_batch_restarts_where_fp64_breaks_down(resident, monkeypatch):
+    """p^H A p <= 0 in a mixed batch, forced at iteration 3 and on an indefinite
+    operator: a restart from the FP64 residual, and TIP_ENOCONV when the budget of
+    restarts is spent; in FP64 a breakdown.  In LDS as in blocks."""
+    tip = gpu_binding()
+    monkeypatch.setenv("TIP_RESIDENT", resident)
+    orc, gop = _op(tip, [7, 6, 11], 0, 990)
+    neg = tip.Operator([9, 5, 6], 0, mass=-20.0)
+
+    def run(precision):
+        return tip.trace_inv_probe_batch([gop, neg], [6, 3], 1e-11, 4018, mask=MASK_Z2, precision=precision,
+                                         raise_on_error=False)
+    assert [s["status"] for _, s in run(tip.PREC_FP64)] == [tip.TIP_OK, tip.TIP_EBREAKDOWN]
+    assert [s["status"] for _, s in run(tip.PREC_MIXED)] == [tip.TIP_OK, tip.TIP_ENOCONV]
+    if resident == "0":
+        return                                               # the batch's blocks have no forced breakdown
+    monkeypatch.setenv("TIP_FORCE_BREAKDOWN", "3")
+    assert [s["status"] for _, s in run(tip.PREC_FP64)] == [tip.TIP_EBREAKDOWN] * 2
+    st = run(tip.PREC_MIXED)[0][1]
+    assert st["status"] == tip.TIP_OK and st["restarts"] >= st["solves"] and st["max_true_relres"] <= 1e-11
+    q_o = oracle_trace(orc, 6, 1e-11, 4018, MASK_Z2)[1]
+    assert np.max(np.abs(st["quadratures"] - q_o) / np.abs(q_o)) <= 1e-10
