@@ -72,32 +72,37 @@ def test_gradient_of_a_failed_run_leaves_nothing_queued(dims, kind, resident, mo
                                          ([4, 4, 4, 8], 1, 200), ([8, 8, 8, 8], 1, 160)])
 @pytest.mark.parametrize("broken", [False, True])
 def test_failure_is_the_first_in_probe_order(dims, kind, n, broken, monkeypatch):
-    """More systems than run at once, some of them stopped at the iteration that
-    most finish before: the probe named, the status, the checkpoints and the
-    residuals up to it are those of one probe at a time, whatever class of the
+    """More systems than run at once, stopped at an iteration that most finish
+    before: the probe named, the status, the checkpoints and the residuals up to
+    it follow from the iterations of each probe by itself, whatever class of the
     three-colouring it is of."""
     tip = gpu_binding()
-    _, gop = _op(tip, dims, kind, 940, m0=0.5)
-    with tip.OpHandle(gop) as h:
-        _, q, full = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z2)
-        checked = 0
-        for stop in range(full["max_iters"] - 1, full["max_iters"] - 4, -1):
-            kw = {} if broken else {"max_iter": stop}
-            if broken:
-                monkeypatch.setenv("TIP_FORCE_BREAKDOWN", str(stop + 1))
-            bad = next((m for m in range(n) if h.trace_inv_probe(
-                m + 1, 1e-10, 4018, mask=MASK_Z2, m_begin=m, quadratures=q, raise_on_error=False, **kw)[2]["status"]), n)
-            est, _, st = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z2, raise_on_error=False, **kw)
-            print(f"{dims} stop {stop} broken {broken}: probe {bad} of {n}", flush=True)
-            if bad == n:
-                assert st["status"] == tip.TIP_OK
-                continue
-            checked += 1
-            assert st["status"] == (tip.TIP_EBREAKDOWN if broken else tip.TIP_ENOCONV)
-            assert f"probe {bad} " in tip.tip_last_error()
-            assert len(est) == (bad.bit_length() if bad else 0)        # checkpoints 1, 2, 4, .. up to bad probes
-            assert not np.isnan(st["residuals"][:bad]).any() and np.isnan(st["residuals"][bad]).any()
-        assert checked
+    late_ones = 0
+    for seed in (940, 941, 942, 943):
+        _, gop = _op(tip, dims, kind, seed, m0=0.5)
+        with tip.OpHandle(gop) as h:
+            _, q, _ = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z2)
+            iters = [h.trace_inv_probe(m + 1, 1e-10, 4018, mask=MASK_Z2, m_begin=m, quadratures=q)[2]["max_iters"]
+                     for m in range(n)]
+            # the stops whose first failure comes latest, and latest among the probes solved in real arithmetic
+            first = {v: next(m for m in range(n) if iters[m] > v) for v in set(iters) if 0 < v < max(iters)}
+            late = sorted(first, key=first.get)[-2:]
+            real = sorted((v for v in first if first[v] % 3 == 0), key=first.get)[-1:]
+            for stop in set(late + real):
+                bad, kw = first[stop], {}
+                if broken:
+                    monkeypatch.setenv("TIP_FORCE_BREAKDOWN", str(stop + 1))
+                else:
+                    kw = {"max_iter": stop}
+                est, _, st = h.trace_inv_probe(n, 1e-10, 4018, mask=MASK_Z2, raise_on_error=False, **kw)
+                monkeypatch.delenv("TIP_FORCE_BREAKDOWN", raising=False)
+                print(f"{dims} seed {seed} stop {stop} broken {broken}: probe {bad} of {n}", flush=True)
+                assert st["status"] == (tip.TIP_EBREAKDOWN if broken else tip.TIP_ENOCONV)
+                assert f"probe {bad} " in tip.tip_last_error()
+                assert len(est) == bad.bit_length()                # checkpoints 1, 2, 4, .. up to bad probes
+                assert not np.isnan(st["residuals"][:bad]).any() and np.isnan(st["residuals"][bad]).any()
+                late_ones += bad >= 16
+    assert late_ones or not any(d % 3 == 0 for d in dims)      # lattices with two classes have late ones
 
 
 @pytest.mark.parametrize("kind,nrhs", [(0, 1), (0, 5), (1, 1), (1, 5)])
