@@ -283,7 +283,9 @@ typedef struct {
  * candidate launch configuration and returns the fastest in best: rhs_block in
  * {16, 32, 64} unless p->rhs_block fixes it, and on 4-D power-of-two lattices
  * round_tiles in {library choice, 64, 128, 256, 512} unless p->round_tiles
- * fixes it.  Every candidate runs twice (the first run warms up) and keeps
+ * fixes it.  Where p as it is would be solved in LDS, that run is timed too: best
+ * then has rhs_block = round_tiles = 0 when it is the fastest; tried lists the
+ * candidates only.  Every candidate runs twice (the first run warms up) and keeps
  * the other fields of p (precision, mask, probe, tol, stream).  tried: HOST
  * [max_tried] candidates in the order timed, or NULL with max_tried = 0;
  * n_tried: how many were timed (may exceed max_tried), or NULL.  Copy the
@@ -299,7 +301,9 @@ tip_status tip_autotune(tip_op_handle h, const tip_params* p, int64_t sample_vec
  * per block in {16, 32, 64} unless params[0].rhs_block fixes it, times sites
  * per work item in {256, 512, 1024, 2048} unless params[0].item_sites fixes
  * it.  Every candidate runs twice (the first run warms up); the fastest goes
- * to best (its rhs_block and item_sites; round_tiles and march_tc are 0).
+ * to best (its rhs_block and item_sites; round_tiles and march_tc are 0).  A
+ * batch whose problems are all solved in LDS is the same run for every candidate:
+ * it is timed once, and best is the library's choice.
  * tried / max_tried / n_tried as in tip_autotune.  Copy the result into every
  * params[i].rhs_block and params[0].item_sites. */
 tip_status tip_autotune_batch(const tip_operator* ops, const tip_params* params, int32_t count,

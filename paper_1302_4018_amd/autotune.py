@@ -34,7 +34,10 @@ def _load(path):
 
 def tuned(handle, tol=1e-10, seed=0, mask=tip.MASK_DEFAULT, precision=tip.PREC_FP64, probe=tip.PROBE_HIERARCHICAL,
           sample_vectors=64, path=None, retune=False):
-    """kwargs (rhs_block, round_tiles, march_tc) for trace_inv_probe on this handle."""
+    """kwargs (rhs_block, round_tiles, march_tc) for trace_inv_probe on this handle;
+    all 0 where no fixed launch shape is faster (lattices solved in LDS).  A file
+    written before the tuner compared with that run holds fixed shapes for such
+    lattices: retune=True replaces its entry."""
     path = path or cache_path()
     key = _key(handle.op, precision, mask, probe)
     table = _load(path)

@@ -233,3 +233,34 @@ def test_mixed_batch_restarts_where_fp64_breaks_down(resident, monkeypatch):
     assert st["status"] == tip.TIP_OK and st["restarts"] >= st["solves"] and st["max_true_relres"] <= 1e-11
     q_o = oracle_trace(orc, 6, 1e-11, 4018, MASK_Z2)[1]
     assert np.max(np.abs(st["quadratures"] - q_o) / np.abs(q_o)) <= 1e-10
+
+
+@pytest.mark.parametrize("dims,kind,mixed", [([16, 16, 16], 0, False), ([4, 4, 4, 8], 1, False), ([9, 7, 15], 0, False),
+                                             ([16, 16, 16], 0, True)])
+def test_autotuning_does_not_leave_the_lds_solvers(dims, kind, mixed, tmp_path):
+    """The fixed launch shapes it times are the block solver's, so what no shape
+    fixes is among what it chooses from."""
+    tip = gpu_binding()
+    from paper_1302_4018_amd import autotune
+    _, gop = _op(tip, dims, kind, 1000)
+    prec = tip.PREC_MIXED if mixed else tip.PREC_FP64
+    with tip.OpHandle(gop) as h:
+        best, tried = h.autotune(1e-10, 4018, sample_vectors=16, precision=prec)
+        assert sorted({t["rhs_block"] for t in tried}) == [16, 32, 64]
+        assert best["seconds_per_solve"] <= min(t["seconds_per_solve"] for t in tried)
+        if mixed:
+            assert best in tried
+            return
+        assert best["rhs_block"] == best["round_tiles"] == 0
+        kw = autotune.tuned(h, 1e-10, 4018, sample_vectors=16, path=str(tmp_path / "tune.json"))
+        assert h.trace_inv_probe(16, 1e-10, 4018, **kw)[2]["stencil_launches"] == 1
+        fixed, tried = h.autotune(1e-10, 4018, sample_vectors=16, rhs_block=16)
+        assert fixed["rhs_block"] == 16 and fixed in tried
+
+
+def test_batch_autotuning_of_lds_problems_is_not_noise():
+    tip = gpu_binding()
+    ops = [_op(tip, d, 0, 1010)[1] for d in ([9, 7, 15], [8, 8, 8])]
+    best, tried = tip.tip_autotune_batch(ops, [8, 8], 1e-10, 4018, sample_vectors=8)
+    assert len(tried) == 12 and len({t["seconds_per_solve"] for t in tried}) == 1
+    assert (best["rhs_block"], best["item_sites"]) == (32, 512)
