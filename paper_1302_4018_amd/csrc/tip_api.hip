@@ -165,6 +165,7 @@ class Pool {
       (void)hipGetLastError();
       trim();
       e = alloc(want, pinned, p);
+      if (e != hipSuccess) (void)hipGetLastError();      // reported here, not by the next launch
     }
     if (e == hipSuccess) *n = want;
     return e;
@@ -1549,6 +1550,7 @@ tip_status run_cluster(DevBuf& dev, HostPinned& host, hipStream_t st, const std:
 // class c in order and stops being called for it after the first that was not
 // accepted; solved(x, logB, nb) is called after each launch with its solutions
 // ([nblk][V][2^logB] of the element type, nb right-hand sides; one class only).
+constexpr size_t kSolutionBytes = size_t(256) << 20;
 struct ResidentResult {
   int state, iters, restarts;
   double q, qim, relres;         // b^H x; real for the scalar operator, which is real and symmetric
@@ -1593,17 +1595,19 @@ struct ResidentRun {
     int dev = 0, cus = 0;
     TIP_HIP(hipGetDevice(&dev));
     TIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // solutions are kept in blocks of 64 right-hand sides, at most 1 GiB of them
+    // solutions are kept in blocks of 64 right-hand sides, at most kSolutionBytes
+    // of them, and fewer where the device has less to give; the gradient's sums go
+    // block by block whatever their number
     int logB = 0;
     while (logB < 6 && (int64_t(1) << logB) < r1 - r0) ++logB;
     int64_t chunk = 1 << 14;
     if (need_x) {
-      const int64_t blk = (int64_t)std::max<size_t>(1, (size_t(1) << 30) / (V * esz << logB));
+      const int64_t blk = (int64_t)std::max<size_t>(1, kSolutionBytes / (V * esz << logB));
       chunk = std::min<int64_t>(chunk, blk << logB);
     }
     const int64_t chunk1 = std::min(chunk, s1 - s0);
     chunk = std::min(chunk, r1 - r0);
-    const size_t x_bytes = need_x ? (((size_t)chunk + (size_t(1) << logB) - 1) >> logB) * (V * esz << logB) : 0;
+    auto x_bytes = [&] { return need_x ? (((size_t)chunk + (size_t(1) << logB) - 1) >> logB) * (V * esz << logB) : size_t(0); };
     hipEvent_t ev[2] = {nullptr, nullptr};
     if (g_profiling)
       for (int k = 0; k < 2; ++k) {
@@ -1615,15 +1619,20 @@ struct ResidentRun {
         ev[k] = h->events[(size_t)k];
       }
     bool failed[2] = {false, false};
-    for (int64_t c0 = r0, d0 = s0; (c0 < r1 && !failed[0]) || (d0 < s1 && !failed[1]); c0 += chunk, d0 += chunk1) {
+    int64_t c0 = r0, d0 = s0;
+    while ((c0 < r1 && !failed[0]) || (d0 < s1 && !failed[1])) {
       const int64_t nr = failed[0] ? 0 : std::max<int64_t>(0, std::min(chunk, r1 - c0));
       const int64_t ns = failed[1] ? 0 : std::max<int64_t>(0, std::min(chunk1, s1 - d0));
       const int nsys0 = (int)(nr * parts), nsys = nsys0 + (int)(ns * 2);
       const double* out = nullptr;
       const int* outi = nullptr;
       double* x = nullptr;
-      tip_status s = eo ? run_eo(c0, nsys, parts, x_bytes, logB, cus, ev, &out, &outi, &x)
-                        : run_plain(c0, d0, nsys0, nsys, parts, cls, x_bytes, logB, cus, ev, &out, &outi, &x);
+      tip_status s = eo ? run_eo(c0, nsys, parts, x_bytes(), logB, cus, ev, &out, &outi, &x)
+                        : run_plain(c0, d0, nsys0, nsys, parts, cls, x_bytes(), logB, cus, ev, &out, &outi, &x);
+      if (s == TIP_ENOMEM && need_x && chunk >> logB > 1) {
+        chunk = (chunk >> (logB + 1)) << logB;
+        continue;
+      }
       if (s == TIP_OK && need_x) s = solved(x, logB, (int)nr);
       if (s != TIP_OK) return s;
       int most = 0;
@@ -1663,6 +1672,8 @@ struct ResidentRun {
         TIP_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
         seconds += ms * 1e-3;
       }
+      c0 += chunk;
+      d0 += chunk1;
     }
     return TIP_OK;
   }

@@ -264,3 +264,23 @@ def test_batch_autotuning_of_lds_problems_is_not_noise():
     best, tried = tip.tip_autotune_batch(ops, [8, 8], 1e-10, 4018, sample_vectors=8)
     assert len(tried) == 12 and len({t["seconds_per_solve"] for t in tried}) == 1
     assert (best["rhs_block"], best["item_sites"]) == (32, 512)
+
+
+def test_gradient_keeps_a_bounded_number_of_solutions():
+    """4096 probes of 32^3: 1 GiB of solutions if all were kept.  The sums over
+    probes against the block solver's, which keeps one block."""
+    tip = gpu_binding()
+    _, gop = _op(tip, [32, 32, 32], 0, 1020)
+    n, tol = 4096, 1e-10
+    with tip.OpHandle(gop) as h:
+        h.trace_inv_probe(4, tol, 4018)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        _, _, gm, gw, st = h.trace_inv_probe_grad(n, tol, 4018)
+        used = before - torch.cuda.mem_get_info()[0]
+        assert st["stencil_launches"] < 64, "not solved in LDS"
+        assert used <= 512 << 20, used
+        _, _, gm_b, gw_b, _ = h.trace_inv_probe_grad(n, tol, 4018, rhs_block=64)
+    lam = float(gop.mass_field.min())
+    from conftest import assert_gradient_entries
+    assert_gradient_entries(gm.cpu().numpy(), gw.cpu().numpy(), gm_b.cpu().numpy(), gw_b.cpu().numpy(), tol, gop.V, lam)
