@@ -266,6 +266,13 @@ typedef struct tip_op_s* tip_op_handle;
 tip_status tip_op_create(const tip_operator* op, void* stream, tip_op_handle* out);
 tip_status tip_op_destroy(tip_op_handle h);
 
+/* Memory that destroyed handles and finished calls held is kept for the next
+ * ones: at most 512 MiB per device in blocks of up to 128 MiB, 32 MiB of pinned
+ * host memory, 16 streams.  It is freed when an allocation of the library fails,
+ * and by this call, which may be made at any time from any thread; memory in use
+ * is not touched. */
+void tip_release_memory(void);
+
 /* trace_inv_probe on a prepared handle (no repack inside the call). */
 tip_status trace_inv_probe_op(tip_op_handle h, const tip_params* p,
                               double* estimates, tip_stats* stats);

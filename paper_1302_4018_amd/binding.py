@@ -92,6 +92,7 @@ def _load():
         "tip_stream_ceiling": (ctypes.c_int, [ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
                                               P(ctypes.c_double), P(ctypes.c_double), ctypes.c_void_p]),
         "tip_set_profiling": (None, [ctypes.c_int32]),
+        "tip_release_memory": (None, []),
         "tip_last_error": (ctypes.c_char_p, []),
     }
     for name, (res, args) in sig.items():
@@ -468,6 +469,11 @@ def tip_stream_ceiling(kind, nbytes, reps=10, grid=0, stream=None):
 
 def tip_set_profiling(on):
     lib.tip_set_profiling(1 if on else 0)
+
+
+def tip_release_memory():
+    """Frees the memory that the library keeps of destroyed handles and finished calls."""
+    lib.tip_release_memory()
 
 
 def tip_last_error():

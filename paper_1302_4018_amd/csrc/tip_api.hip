@@ -125,13 +125,15 @@ std::mutex g_device_mu;
 // Device memory, pinned host memory and non-blocking streams that a handle or
 // a call is done with, kept for the next one: a call that builds its own
 // operator spent 0.4-0.8 ms on allocating, freeing and creating them.  What is
-// kept is bounded (kPoolBytes a device, kPoolPinned, kPoolStreams; what has lain
-// longest goes first), nothing is given in that still has work queued on it (the
-// giver has synchronised), and all memory kept is freed when an allocation
-// fails.  One lock for all threads.
+// kept is bounded (kPoolBytes a device, kPoolPinned, kPoolBlocks, kPoolStreams;
+// what has lain longest goes first), nothing is given in that still has work
+// queued on it (the giver has synchronised), and all memory kept is freed when an
+// allocation fails or the caller asks for it (tip_release_memory).  One lock for
+// all threads.  Giving allocates nothing: destructors do it.
 constexpr size_t kPoolBytes = size_t(512) << 20, kPoolBlock = size_t(128) << 20;
 constexpr size_t kPoolPinned = size_t(32) << 20, kPoolPinnedBlock = size_t(8) << 20;
 constexpr size_t kPoolStreams = 16;
+constexpr size_t kPoolBlocks = 1024;             // looked through on every take: a microsecond
 
 class Pool {
  public:
@@ -178,28 +180,29 @@ class Pool {
       keep = hipPointerGetAttributes(&at, p) == hipSuccess;
       if (keep) dev = at.device;
     }
-    std::vector<Block> out;
-    if (keep && n <= (pinned ? kPoolPinnedBlock : kPoolBlock)) {
-      std::lock_guard<std::mutex> lk(mu_);
-      kept_.push_back({p, n, dev});
-      size_t sum = 0;
-      for (const Block& b : kept_)
-        if (b.dev == dev) sum += b.n;
-      for (auto it = kept_.begin(); sum > (pinned ? kPoolPinned : kPoolBytes);) {
-        if (it->dev != dev) {
-          ++it;
-          continue;
-        }
-        sum -= it->n;
-        out.push_back(*it);
-        it = kept_.erase(it);
-      }
-    } else {
-      out.push_back({p, n, pinned ? -1 : 0});
+    if (!keep || n > (pinned ? kPoolPinnedBlock : kPoolBlock)) {
+      std::lock_guard<std::mutex> lk(g_device_mu);
+      release({p, n, pinned ? -1 : 0});
+      return;
     }
-    if (out.empty()) return;
-    std::lock_guard<std::mutex> lk(g_device_mu);
-    for (const Block& b : out) (void)(b.dev < 0 ? hipHostFree(b.p) : hipFree(b.p));
+    Block gone{p, n, dev};
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (kept_.size() < kPoolBlocks) {
+        kept_.push_back(gone);                   // within the reserved length
+        gone.p = nullptr;
+      } else {                                   // the oldest of all makes room
+        const Block oldest = kept_.front();
+        kept_.erase(kept_.begin());
+        kept_.push_back(gone);
+        gone = oldest;
+      }
+    }
+    while (gone.p || over(dev, pinned ? kPoolPinned : kPoolBytes, &gone)) {
+      std::lock_guard<std::mutex> lk(g_device_mu);
+      release(gone);
+      gone.p = nullptr;
+    }
   }
   hipStream_t take_stream() {
     int dev = 0;
@@ -233,6 +236,21 @@ class Pool {
     std::lock_guard<std::mutex> lk(g_device_mu);
     (void)hipStreamDestroy(s);
   }
+  // Gives everything kept back to the device and the system.
+  void clear() {
+    std::lock_guard<std::mutex> lk(g_device_mu);
+    trim();
+    for (;;) {
+      hipStream_t s = nullptr;
+      {
+        std::lock_guard<std::mutex> lk2(mu_);
+        if (streams_.empty()) return;
+        s = streams_.back().s;
+        streams_.pop_back();
+      }
+      (void)hipStreamDestroy(s);
+    }
+  }
 
  private:
   struct Block {
@@ -247,13 +265,38 @@ class Pool {
   static hipError_t alloc(size_t n, bool pinned, void** p) {
     return pinned ? hipHostMalloc(p, n, hipHostMallocDefault) : hipMalloc(p, n);
   }
-  void trim() {
-    std::vector<Block> all;
-    {
-      std::lock_guard<std::mutex> lk(mu_);
-      all.swap(kept_);
+  Pool() {
+    kept_.reserve(kPoolBlocks);
+    streams_.reserve(kPoolStreams);
+  }
+  // with g_device_mu held
+  static void release(const Block& b) { (void)(b.dev < 0 ? hipHostFree(b.p) : hipFree(b.p)); }
+  // Takes out the oldest block of a device that keeps more than `most` bytes.
+  bool over(int dev, size_t most, Block* gone) {
+    std::lock_guard<std::mutex> lk(mu_);
+    size_t sum = 0;
+    auto oldest = kept_.end();
+    for (auto it = kept_.begin(); it != kept_.end(); ++it)
+      if (it->dev == dev) {
+        sum += it->n;
+        if (oldest == kept_.end()) oldest = it;
+      }
+    if (sum <= most) return false;
+    *gone = *oldest;
+    kept_.erase(oldest);
+    return true;
+  }
+  void trim() {                                  // with g_device_mu held
+    for (;;) {
+      Block b{};
+      {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (kept_.empty()) return;
+        b = kept_.back();
+        kept_.pop_back();
+      }
+      release(b);
     }
-    for (const Block& b : all) (void)(b.dev < 0 ? hipHostFree(b.p) : hipFree(b.p));
   }
   std::mutex mu_;
   std::vector<Block> kept_;
@@ -1295,6 +1338,8 @@ int32_t tip_num_checkpoints(int64_t n_vectors) { return num_checkpoints(n_vector
 const char* tip_last_error(void) { return g_err.c_str(); }
 
 void tip_set_profiling(int32_t on) { g_profiling = on ? 1 : 0; }
+
+void tip_release_memory(void) { Pool::get().clear(); }
 
 tip_status tip_op_create(const tip_operator* op, void* stream, tip_op_handle* out) {
   if (!out) return fail(TIP_EINVAL, "out is NULL");
