@@ -2330,26 +2330,27 @@ tip_status batch_clusters(const std::vector<std::unique_ptr<tip_op_s, HandleDel>
   tip_status s = run_cluster(work, host, st, probs, jobs, packets, launches, false, 0, 0, ev[0], ev[1], &out, &outi, &x,
                              gave_up);
   if (s != TIP_OK) return s;
-  std::vector<double> bn2(0), rt2(0);
+  // parts of a right-hand side together; slots of the problems one after another
+  std::vector<size_t> at(results.size(), 0);
+  size_t slots = 0;
   for (size_t i = 0; i < results.size(); ++i)
-    if (clustered[i]) {
-      RunResult& rr = results[i];
-      rt2.assign(rr.qre.size(), 0.0);
-      bn2.assign(rr.qre.size(), 0.0);
-      for (size_t k = 0; k < systems.size(); ++k) {
-        const System& y = systems[k];
-        if (y.prob != (int)i) continue;
-        const double* o = out + 3 * k;
-        const int* oi = outi + 3 * k;
-        if (y.part == 0 || rr.state[y.slot] == kAccepted) rr.state[y.slot] = oi[0];
-        rr.iters[y.slot] = std::max(rr.iters[y.slot], oi[1]);
-        rr.qre[y.slot] += o[0];
-        rt2[y.slot] += o[1];
-        bn2[y.slot] += o[2];
-        rr.acc.restarts += oi[2];
-      }
-      for (size_t k = 0; k < rt2.size(); ++k) rr.relres[k] = bn2[k] > 0.0 ? std::sqrt(rt2[k] / bn2[k]) : 0.0;
-    }
+    if (clustered[i]) at[i] = slots, slots += results[i].qre.size();
+  std::vector<double> rt2(slots, 0.0), bn2(slots, 0.0);
+  for (size_t k = 0; k < systems.size(); ++k) {
+    const System& y = systems[k];
+    RunResult& rr = results[(size_t)y.prob];
+    const double* o = out + 3 * k;
+    const int* oi = outi + 3 * k;
+    if (y.part == 0 || rr.state[y.slot] == kAccepted) rr.state[y.slot] = oi[0];
+    rr.iters[y.slot] = std::max(rr.iters[y.slot], oi[1]);
+    rr.qre[y.slot] += o[0];
+    rt2[at[(size_t)y.prob] + y.slot] += o[1];
+    bn2[at[(size_t)y.prob] + y.slot] += o[2];
+    rr.acc.restarts += oi[2];
+  }
+  for (size_t i = 0; i < results.size(); ++i)
+    for (size_t k = 0; clustered[i] && k < results[i].qre.size(); ++k)
+      results[i].relres[k] = bn2[at[i] + k] > 0.0 ? std::sqrt(rt2[at[i] + k] / bn2[at[i] + k]) : 0.0;
   float ms = 0.f;
   if (ev[0]) TIP_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
   double bytes = 0.0;

@@ -311,3 +311,14 @@ def test_kept_memory_is_bounded_and_given_back():
     assert before - free() <= 8 << 20
     assert np.max(np.abs(q - oracle_trace(orc, 4, 1e-11, 7, MASK_Z2)[1]) / np.abs(q)) <= 1e-10
     assert np.array_equal(tip.trace_inv_probe(small, 4, 1e-11, 7, mask=MASK_Z2)[1], q)
+
+
+def test_time_of_a_batch_grows_with_its_problems_not_their_square():
+    tip = gpu_binding()
+    ops = [tip.Operator([5, 3, 4], 0, mass=0.5 + 0.0001 * k) for k in range(4000)]
+
+    def seconds(n):
+        return min(tip.trace_inv_probe_batch(ops[:n], [60] * n, 1e-10, 7)[0][1]["seconds"] for _ in range(4))
+    seconds(4000)
+    few, many = seconds(1000), seconds(4000)
+    assert many <= 6.5 * few, (few, many)      # 4 when linear; the scan over all systems for each problem made it 9.4
