@@ -454,9 +454,8 @@ template <int ND, bool W>
 hipError_t launch_cluster_nd(const ClArgs& a, uint32_t rows, hipStream_t st) {
   const size_t lds = (size_t)cl_lds_rows(rows, a.Amax) * sizeof(double);
   auto go = [&](auto kernel, int nt) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    // the same for every launch: other threads launch the same kernel with other needs
+    if (const hipError_t e = allow_lds(kernel, kClLdsRows * sizeof(double)); e != hipSuccess) return e;
     const unsigned grid = (unsigned)(a.nteams * a.T);
     if (a.T == 1) {
       kernel<<<grid, nt, lds, st>>>(a);

@@ -7,6 +7,13 @@
 
 namespace tip {
 
+// Lets a kernel be launched with up to `bytes` of dynamic LDS.
+template <class K>
+hipError_t allow_lds(K kernel, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
+}
+
 // Sum over a wave, in every lane: DPP adds inside rows of 16, across them,
 // and the last lane's total read back.  The order is fixed.
 template <int CTRL, int ROWS>

@@ -324,9 +324,9 @@ hipError_t launch_cov_nd(const ResArgs& a, unsigned grid, hipStream_t st) {
   size_t lds = (size_t)n * 3 * sizeof(double2);
   if (n == 2048) lds += 2 * 512 * 3 * sizeof(double2);       // rows of r
   auto go = [&](auto kernel, int nt) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    // a kernel's need is the same in every launch, but for systems of less than 64
+    // rows, which need no allowance
+    if (const hipError_t e = n < 64 ? hipSuccess : allow_lds(kernel, lds); e != hipSuccess) return e;
     kernel<<<grid, nt, lds, st>>>(a);
     return hipGetLastError();
   };

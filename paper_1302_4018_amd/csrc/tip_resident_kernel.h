@@ -304,9 +304,9 @@ hipError_t launch_resident_nd(const ResArgs& a, unsigned grid, hipStream_t st) {
   size_t lds = ((size_t)n + 1) * sizeof(double);
   if (n == 16384) lds += 7 * 512 * sizeof(double);           // rows of r
   auto go = [&](auto kernel, int nt) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    // a kernel's need is the same in every launch, but for systems of less than 64
+    // rows, which need no allowance
+    if (const hipError_t e = n < 64 ? hipSuccess : allow_lds(kernel, lds); e != hipSuccess) return e;
     kernel<<<grid, nt, lds, st>>>(a);
     return hipGetLastError();
   };

@@ -322,3 +322,40 @@ def test_time_of_a_batch_grows_with_its_problems_not_their_square():
     seconds(4000)
     few, many = seconds(1000), seconds(4000)
     assert many <= 6.5 * few, (few, many)      # 4 when linear; the scan over all systems for each problem made it 9.4
+
+
+def test_host_threads_share_kernels_and_kept_memory():
+    """Threads with streams of their own, in lattices of different sizes for the
+    same kernels, handles made and destroyed all along: every result is what the
+    call alone gives, bit for bit."""
+    import threading
+    tip = gpu_binding()
+    cases = [([48, 48, 48], 0), ([9, 7, 15], 0), ([16, 16, 16], 0), ([4, 4, 4, 8], 1)]
+    ops = [_op(tip, d, k, 1040 + i)[1] for i, (d, k) in enumerate(cases)]
+
+    def call(i, stream):
+        with tip.OpHandle(ops[i], stream=stream) as h:
+            q = h.trace_inv_probe(3, 1e-10, 7, mask=MASK_Z4, stream=stream)[1]
+            x = h.solve_probe(1, 0, 1e-10, 7, mask=MASK_Z4, stream=stream)[0].cpu().numpy()
+        b = [s["quadratures"] for _, s in tip.trace_inv_probe_batch([ops[1], ops[0]][:1 + i % 2], [4, 2][:1 + i % 2],
+                                                                    1e-10, 7, mask=MASK_Z2, stream=stream)]
+        return q, x, *b
+    want = [call(i, None) for i in range(len(cases))]
+    wrong = []
+
+    def work(t):
+        stream = torch.cuda.Stream()
+        try:
+            for r in range(8):
+                i = (t + r) % len(cases)
+                if not all(np.array_equal(g, w) for g, w in zip(call(i, stream), want[i])):
+                    wrong.append((t, r, cases[i]))
+        except Exception as e:                                   # noqa: BLE001
+            wrong.append((t, repr(e)))
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong
