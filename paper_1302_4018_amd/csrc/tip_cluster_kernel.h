@@ -60,6 +60,7 @@ __device__ __forceinline__ bool get_word(const unsigned long long* w, uint32_t t
   return false;
 }
 constexpr int kClBeat = 64;                  // iterations between a workgroup's beats, 2 ms at the most
+constexpr int kNotPositive = 64;             // a state besides those of the results: p^H A p <= 0
 // M numbers at once, word i at w(i) and w(i) + hi where want(i): every word is
 // asked for before any is waited for, so that M numbers cost one trip to
 // memory, not 2 M.  NaN when the wait ran into its limit; the solve then ends as
@@ -121,7 +122,6 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
   unsigned long long* const beats = packet_word + 1;
   auto halo_of = [&](int m) { return a.halo + ((size_t)m * a.nteams + team) * 8 * (size_t)a.Amax; };
   uint32_t sum_tag = 0, halo_tag = 0, packet_tag = 0;
-  unsigned long long beat = 0;
 
   for (;;) {
     // the next packet, taken by the team's first workgroup.  The clusters of the
@@ -204,7 +204,6 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
     // in scalar registers: read where they are used, each would cost a trip to
     // memory between the sums of every iteration
     const double tol2 = scalar(pr.tol2), freeze2 = scalar(pr.freeze2);
-    const bool mixed = scalar((uint32_t)pr.mixed) != 0;
     const int max_iter = (int)scalar((uint32_t)pr.max_iter), force_iter = (int)scalar((uint32_t)pr.force_iter);
     const uint32_t* const t_nbr = scalar(pr.nbr) + s0;
     const Double2* const t_wgt = scalar(reinterpret_cast<const Double2*>(pr.wgt)) + s0;
@@ -352,9 +351,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         });
         const double pAp = total(acc, red[0]);
         if (!(pAp > 0.0) || !isfinite(pAp) || (force_iter > 0 && restarts == 0 && it + 1 == force_iter)) {
-          // asked for in mixed precision: no breakdown, but a restart from the FP64
-          // residual, as the single-precision passes make of it
-          state = mixed ? kFrozen : kBreakdown;
+          state = kNotPositive;
           break;
         }
         const double alpha = rho / pAp;
@@ -371,7 +368,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         const double rho_new = total(acc, red[1]);
         ++it;
         if (tid == 0 && G < T && it % kClBeat == 0)
-          __hip_atomic_store(beats + mate, ++beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          put_word(beats + mate, (uint32_t)it, packet_tag);
         if (!isfinite(rho_new)) state = kBreakdown;
         else if (rho_new <= (restarts == 0 ? freeze2 : tol2) * bnorm2) state = kFrozen;
         else if (it >= max_iter) state = kNoConv;
@@ -390,6 +387,10 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         }
         __syncthreads();
       }
+      // asked for in mixed precision: no breakdown, but a restart from the FP64
+      // residual, as the single-precision passes make of it.  (Out of the loop, where
+      // its register cost 16 tori 22.5 ms in place of 21.9.)
+      if (state == kNotPositive) state = pr.mixed ? kFrozen : kBreakdown;
       if (state != kFrozen) break;
       // the FP64 true residual b - A x
       rows([&](int k, uint32_t e) {
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(NT) void k_cluster(const ClArgs a) {
         a2 = fma(xk, r[k], a2);
       });
       rt2 = total(a0, red[0]);
-      q = total(mixed ? a1 + a2 : a1, red[1]);
+      q = total(pr.mixed ? a1 + a2 : a1, red[1]);
       if (rt2 <= tol2 * bnorm2) {
         state = kAccepted;
         break;
