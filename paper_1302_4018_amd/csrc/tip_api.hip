@@ -1750,7 +1750,7 @@ struct ResidentRun {
     a.rhs0 = c0;
     a.nsys = nsys;
     a.start_frozen = p->tol >= 1.0 ? 1 : 0;
-    a.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)geom.V, 1 << 20);
+    a.max_iter = p->max_iter > 0 ? p->max_iter : (int)std::min<int64_t>(10 * (int64_t)geom.V * geom.ncomp, 1 << 20);
     a.max_restarts = 8;
     a.tol2 = p->tol * p->tol;
     test_hooks(a.tol2, &a.freeze2, &a.force_iter);

@@ -337,9 +337,11 @@ def test_host_threads_share_kernels_and_kept_memory():
         with tip.OpHandle(ops[i], stream=stream) as h:
             q = h.trace_inv_probe(3, 1e-10, 7, mask=MASK_Z4, stream=stream)[1]
             x = h.solve_probe(1, 0, 1e-10, 7, mask=MASK_Z4, stream=stream)[0].cpu().numpy()
+            # the block solver, which captures graphs
+            m = h.trace_inv_probe(2, 1e-10, 7, mask=MASK_Z4, stream=stream, precision=tip.PREC_MIXED)[1]
         b = [s["quadratures"] for _, s in tip.trace_inv_probe_batch([ops[1], ops[0]][:1 + i % 2], [4, 2][:1 + i % 2],
                                                                     1e-10, 7, mask=MASK_Z2, stream=stream)]
-        return q, x, *b
+        return q, x, m, *b
     want = [call(i, None) for i in range(len(cases))]
     wrong = []
 
@@ -359,3 +361,30 @@ def test_host_threads_share_kernels_and_kept_memory():
     for t in threads:
         t.join()
     assert not wrong, wrong
+
+
+def test_default_limit_of_iterations(monkeypatch):
+    """10 V ncomp, as in blocks, for a covariant operator on which CG gets nowhere."""
+    tip = gpu_binding()
+    dims = [4, 4]
+    w = 10.0 ** np.random.default_rng(1060).uniform(-9, 9, size=(2, 16))
+    gop = tip.Operator(dims, 1, mass=1e-14, coupling=to_dev(w), links=to_dev(inputs.haar_links(dims, seed=1061)))
+    runs = []
+    for resident in ("1", "0"):
+        monkeypatch.setenv("TIP_RESIDENT", resident)
+        runs.append(tip.trace_inv_probe(gop, 1, 1e-14, 7, raise_on_error=False)[2])
+    assert [st["status"] for st in runs] == [tip.TIP_ENOCONV] * 2
+    assert [st["max_iters"] for st in runs] == [10 * gop.V * gop.ncomp] * 2
+
+
+@pytest.mark.parametrize("dims,n,m0", [([32, 32, 32], 16500, 16300), ([27, 32, 64], 55296, 48000)])
+def test_runs_longer_than_a_launch(dims, n, m0):
+    """More than 16384 right-hand sides, of one class and of each of two."""
+    tip = gpu_binding()
+    _, gop = _op(tip, dims, 0, 1070, m0=2.0)
+    with tip.OpHandle(gop) as h:
+        _, q, st = h.trace_inv_probe(n, 1e-9, 4018, mask=MASK_Z2)
+        _, tail, st2 = h.trace_inv_probe(n, 1e-9, 4018, mask=MASK_Z2, m_begin=m0, quadratures=q)
+        _, some, _ = h.trace_inv_probe(300, 1e-9, 4018, mask=MASK_Z2)
+    assert st["stencil_launches"] > 1 and st["status"] == tip.TIP_OK and st["solves"] + st["reused"] == n
+    assert np.max(np.abs(tail - q) / np.abs(q)) <= 1e-12 and np.max(np.abs(some - q[:300]) / np.abs(some)) <= 1e-12
