@@ -2955,7 +2955,11 @@ tip_status tip_solve_probe(tip_op_handle h, const tip_params* p, int64_t m, int3
   if (m < 0 || m >= (int64_t)g.V) return fail(TIP_EINVAL, "probe %lld outside [0, V)", (long long)m);
   if (comp < 0 || comp >= g.ncomp) return fail(TIP_EINVAL, "comp = %d out of range", comp);
   if (!x_out) return fail(TIP_EINVAL, "x_out is NULL");
-  if (const int res = resident_system(h, &one); res >= 0) {
+  // a complex probe (a column of the three-colouring other than its first) does
+  // not fit a real x_out: the block solver, whose check of the residual refuses it
+  const bool refused = g.has3 && one.probe == TIP_PROBE_HIERARCHICAL && !complex_solves(h, &one, mask) &&
+                       m % (int64_t)g.gamma >= (int64_t(1) << g.LB);
+  if (const int res = resident_system(h, &one); res >= 0 && !refused) {
     ResidentRun rs;
     ResidentResult o{};
     s = rs.setup(h, &one, mask, res, -1);

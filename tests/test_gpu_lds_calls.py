@@ -388,3 +388,27 @@ def test_runs_longer_than_a_launch(dims, n, m0):
         _, some, _ = h.trace_inv_probe(300, 1e-9, 4018, mask=MASK_Z2)
     assert st["stencil_launches"] > 1 and st["status"] == tip.TIP_OK and st["solves"] + st["reused"] == n
     assert np.max(np.abs(tail - q) / np.abs(q)) <= 1e-12 and np.max(np.abs(some - q[:300]) / np.abs(some)) <= 1e-12
+
+
+@pytest.mark.parametrize("dims", [[9, 7, 5], [6, 10]])
+def test_solve_probe_refuses_complex_probes_in_real_arithmetic(dims, monkeypatch):
+    """With a real mask x is real; the probes of the three-colouring's other columns
+    are not.  Refused in blocks, so in LDS: not the solution of their real part."""
+    tip = gpu_binding()
+    _, gop = _op(tip, dims, 0, 1080)
+    runs = []
+    for resident in ("1", "0"):
+        monkeypatch.setenv("TIP_RESIDENT", resident)
+        with tip.OpHandle(gop) as h:
+            _, q, _ = h.trace_inv_probe(24, 1e-11, 4018, mask=MASK_Z2)
+            run = []
+            for m in range(24):
+                try:
+                    qm = h.solve_probe(m, 0, 1e-11, 4018, mask=MASK_Z2)[1]
+                    assert abs(qm - q[m]) <= 1e-10 * abs(q[m]), m
+                    run.append(True)
+                except tip.TipError as e:
+                    assert e.status == tip.TIP_ENOCONV
+                    run.append(False)
+        runs.append(run)
+    assert runs[0] == runs[1] and True in runs[0] and False in runs[0]
