@@ -412,3 +412,53 @@ def test_solve_probe_refuses_complex_probes_in_real_arithmetic(dims, monkeypatch
                     run.append(False)
         runs.append(run)
     assert runs[0] == runs[1] and True in runs[0] and False in runs[0]
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_lds_and_block_solvers_agree_over_what_both_take(seed, monkeypatch):
+    """Sides of 1 to 16 in two to four dimensions, every kind of probe and mask, with
+    and without fields, negative couplings, resumed runs: status, counts and
+    quadratures of the two routes.  Each solution's residual is at most 1e-12 of
+    ||b||, so a quadrature's relative error at most 1e-12 times the condition number,
+    which stays below 500 here (masses of 0.2 and more, weights up to 1.5)."""
+    import random
+    tip = gpu_binding()
+    rng = random.Random(seed)
+    for k in range(20):
+        kind = rng.choice([0, 0, 0, 1])
+        pow2 = rng.random() < 0.5
+        while True:
+            dims = [rng.choice([1, 2, 4, 8, 16]) if pow2 else rng.randint(1, 13) for _ in range(rng.choice([2, 3, 4]))]
+            V = int(np.prod(dims))
+            if 4 <= V <= (1024 if kind else 4096):
+                break
+        kinds = [tip.PROBE_HIERARCHICAL] * 3 + [tip.PROBE_RANDOM]
+        if all(d & (d - 1) == 0 for d in dims):
+            kinds += [tip.PROBE_NATURAL, tip.PROBE_STOPPED, tip.PROBE_FOURIER]
+        probe = rng.choice(kinds)
+        mask = rng.choice([1, 2] if probe == tip.PROBE_RANDOM else [0, 1, 2])
+        n = min(V, rng.choice([1, 2, 5, 17, 40]))
+        begin = rng.randint(0, n - 1) if rng.random() < 0.3 else 0
+        negative = rng.random() < 0.25
+        w = inputs.couplings(dims, seed=k) if negative or rng.random() < 0.6 else None
+        if negative:
+            w = w * np.where(np.random.default_rng(k).random(w.shape) < 0.1, -0.1, 1.0)
+        U = inputs.haar_links(dims, seed=k) if kind else None
+        gop = tip.Operator(dims, kind, mass=3.0 if negative else rng.choice([0.2, 1.0]), coupling=to_dev(w), links=to_dev(U),
+                           mass_field=to_dev(inputs.mass_field(dims, m0=3.0 if negative else 0.5, seed=k))
+                           if rng.random() < 0.5 else None)
+        kw = dict(mask=mask, probe=probe, stop_levels=rng.randint(0, 4) if probe == tip.PROBE_STOPPED else 0)
+        print(f"case {seed}.{k}: {dims} kind {kind} {kw} n {n} begin {begin} negative {negative}", flush=True)
+        runs = []
+        for resident in ("1", "0"):
+            monkeypatch.setenv("TIP_RESIDENT", resident)
+            with tip.OpHandle(gop) as h:
+                first = h.trace_inv_probe(begin, 1e-12, 7, **kw)[1] if begin else None
+                runs.append(h.trace_inv_probe(n, 1e-12, 7, m_begin=begin, quadratures=first, **kw))
+        (est, q, st), (est_b, q_b, st_b) = runs
+        assert all(st[f] == st_b[f] for f in ("status", "solves", "reused", "n_checkpoints_done"))
+        assert st["max_true_relres"] <= 1e-12
+        if kind == 0 or (not negative and all(d > 1 and d & (d - 1) == 0 for d in dims)):
+            assert st["stencil_launches"] == 1, "not solved in LDS"
+        assert np.max(np.abs(q - q_b) / np.abs(q_b)) <= 1e-9 and np.max(np.abs(est - est_b) / np.abs(est_b)) <= 1e-9
+        assert np.array_equal(np.isnan(st["residuals"]), np.isnan(st_b["residuals"]))
