@@ -25,7 +25,9 @@
  *   32768 scalar, 4096 covariant) or of up to 32 CUs (scalar, other sides), 2 to 4
  *   dimensions, are solved there, whole solves in one launch, unless the caller fixes rhs_block,
  *   round_tiles or march_tc; stencil_launches then counts these launches and
- *   matvecs the iterations of each launch's longest solve.
+ *   matvecs the iterations of each launch's longest solve.  MIXED single calls keep
+ *   the blocks, which on such lattices are several times slower than FP64 (weighted
+ *   32^3, 512 probes: 38 ms against 3.0).
  *
  * Conventions shared by every entry point
  * ---------------------------------------

@@ -976,8 +976,8 @@ struct Solver {
     // half vectors or more, holds a group's later directions.  Plain CG
     // iterates on X itself and has no room to spare.  Where x, r, p, w and t fit
     // the 256 MB memory-side cache, two more vectors only push others out: 32^4,
-    // past it, 102.2 -> 99.2 ms with groups (128^3 72.7 -> 72.1, the same
-    // in one comparison of five), but 16^4 in mixed precision 11.84 -> 11.92.  TIP_EO_GROUP=1 groups always, 0 never.
+    // past it, 102.2 -> 99.2 ms with groups (128^3 and 32^4 in mixed precision: no
+    // difference beyond the noise), but 16^4 in mixed precision 11.84 -> 11.92.  TIP_EO_GROUP=1 groups always, 0 never.
     group = pl.eo && !env_off("TIP_EO_GROUP") &&
                     (5.0 * (double)(vbytes / 2) > 256.0 * 1048576.0 || env_on("TIP_EO_GROUP"))
                 ? kDefer
@@ -1389,8 +1389,8 @@ struct ClusterCut {
       if (fits(G)) return G;
     return 0;
   }
-  // Workgroups per system when nsys systems share `cus` CUs.  More than the
-  // least while CUs would stay idle, and while the rows that one of them is
+  // Workgroups per system of the probe classes when nsys systems share `cus` CUs.
+  // More than the least while CUs would stay idle, and while the rows that one of them is
   // spared are worth the exchanges: two per iteration, 3-4 us together, the
   // time of about 3000 rows.
   int pick(int64_t nsys, int cus) const {

@@ -7,11 +7,12 @@
 // boundary planes of r: a neighbour forms p = r + beta p on its halo planes by
 // itself.  All exchanges go through self-validating words in memory, 3-4 us an
 // iteration; the workgroups of a cluster are resident together by a cooperative
-// launch, and every wait has a limit.
+// launch, and every wait has a limit: for whole solves one that starts again while
+// they make progress.  A launch that ran into it is left to the block solver.
 //
 // Bound, like the resident solver, by the tables each CU reads from L2: 20 ndim
 // + 4 bytes per row and iteration with couplings.  The least G that holds a
-// lattice is used; more only when CUs would idle.  Measured (block solver ->
+// lattice is used; more only in probe classes, when CUs would idle.  Measured (block solver ->
 // this): 16 uneven 3-D tori, sides 8..48, 1180 systems, 86.5 -> 21.9 ms in FP64
 // and, in place of the single-precision passes, 76.9 -> 21.9 ms; 21x34x15, 50
 // probes, set-up included, 8.4 -> 1.03 ms.  An iteration of one system alone

@@ -7,7 +7,7 @@
 // 144 bytes per row and hop.  Up to 2048 rows (8^4): 512 threads with four rows
 // each, two waves per SIMD at 256 registers; the loop over dimensions is not
 // unrolled, so that two links are in registers at a time, one on its way.  8^4
-// with couplings, 64 probes (192 systems, one per CU): 0.82 ms in the kernel, 9.4
+// with couplings, 64 probes (192 systems, one per CU): 0.82 ms in the kernel, 8.8
 // of the 16 lines an XCD's L2 delivers per cycle; estimate and gradient, operator
 // set-up included, 3.35 -> 1.64 ms.
 #include <algorithm>

@@ -10,7 +10,8 @@
 //
 // What bounds it is the operator's tables, read from L2 by every workgroup:
 // 16 ndim + 8 bytes per row and hop.  At 32^3 with couplings an iteration moves
-// 2.3 MB per CU in 25.6 us: 10 of the 16 lines an XCD's L2 delivers per cycle.
+// 2.3 MB per CU in 25.6 us: over the whole kernel 8.7 of the 16 lines that an XCD's
+// L2 delivers per cycle.
 // Measured, one call with a prepared operator (block solver -> this): 16^2, 256
 // probes 2.66 -> 0.051 ms; 32^3 with couplings, 512 probes 36.8 -> 3.5 ms.  On
 // the way, 32^3: tables hoisted out of the iteration by the compiler and spilled
